@@ -1,6 +1,7 @@
 // C ABI of libcgh: argument validation, workspace carving, and the sequence of
 // kernel launches behind each entry point.  No device allocation happens here:
 // every buffer is the caller's or lives in the caller's workspace.
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -125,6 +126,8 @@ cgh_status setup(const cgh_config *cfg, cgh::Ctx *c) {
   c->B = B;
   c->CF = B * f.channels;
   c->Wt = (Wp + 7) / 8;
+  c->row_p = cgh::row_split(Wp, f.width);
+  c->col_p = cgh::col_split(Hp, f.height);
   c->tile_w = tw;
   c->tile_h = th;
   c->tiles_x = (f.width + tw - 1) / tw;
@@ -197,23 +200,28 @@ size_t carve(Ctx *c, char *base) {
   c->tw_x = (float2 *)take(sizeof(float2) * kTwTable);
   c->tw_y = (float2 *)take(sizeof(float2) * kTwTable);
   c->tw_m = (float2 *)take(sizeof(float2) * kTwTable);
-  // full tables of Wp and Hp entries, each followed (when its length is a
-  // multiple of 4) by the contiguous table of the quarter length, the twiddles
-  // of the four-chain row and column passes
-  c->twf_x = (float2 *)take(sizeof(float2) * (c->Wp + (c->Wp % 4 ? 0 : c->Wp / 4)));
+  // full tables of Wp and Hp entries; with a chain pass each is followed by the
+  // contiguous table of the chain length
+  c->twf_x = (float2 *)take(sizeof(float2) * (c->Wp + (c->row_p ? c->Wp / c->row_p : 0)));
   c->twf_m = (float2 *)take(sizeof(float2) * c->plan_m.n);
-  c->htab = (float2 *)take(sizeof(float2) * c->CF * c->L * (size_t)c->Hq * c->Wq);
-  const bool wave_cols = col_wave4(*c);
-  c->htab_t = wave_cols ? (float2 *)take(sizeof(float2) * c->CF * c->L * (size_t)c->Hq * c->Wq)
-                        : nullptr;
-  c->twf_y = wave_cols ? (float2 *)take(sizeof(float2) * (c->Hp + c->Hp / 4)) : nullptr;
+  const size_t tables = (size_t)c->CF * c->L;
+  c->optics = (double *)take(sizeof(double) * 2 * tables);
+  c->htab = nullptr;
+  c->htab_t = nullptr;
+  c->twf_y = nullptr;
+  float2 *tab = (float2 *)take(sizeof(float2) * tables * (size_t)c->Hq * c->Wq);
+  if (c->col_p) {
+    c->htab_t = tab;
+    c->twf_y = (float2 *)take(sizeof(float2) * (c->Hp + c->Hp / c->col_p));
+  } else {
+    c->htab = tab;
+  }
   const size_t spec_len = (size_t)c->CF * c->Wt * c->H * 8;
   c->spec = (float2 *)take(sizeof(float2) * spec_len);
   // with several planes the shared row spectrum stays in spec; each plane's
   // column pass writes spec_plane, and the adjoint sums the planes in spec_acc
   c->spec_plane = c->L > 1 ? (float2 *)take(sizeof(float2) * spec_len) : c->spec;
   c->spec_acc = c->L > 1 ? (float2 *)take(sizeof(float2) * spec_len) : c->spec;
-  c->field_tmp = (float2 *)take(sizeof(float2) * c->CF * HW);
   c->gfield_tmp = (float2 *)take(sizeof(float2) * c->CF * HW);
   c->rec = (float *)take(sizeof(float) * c->rec_stride * (N + 1));
   c->alim = (c->cfg.flags & CGH_PAPER_ALPHA) ? (float2 *)take(sizeof(float2) * (N + 1)) : nullptr;
@@ -234,9 +242,13 @@ size_t carve(Ctx *c, char *base) {
   // chunk sums: per kScanItems of a scan, or per preprocess workgroup (256 Gaussians)
   c->scan_tmp = (uint32_t *)take(sizeof(uint32_t) *
                                  std::max(scan_len / kScanItems + 2, (N + 255) / 256 + 2));
-  c->partials = (float *)take(sizeof(float) * c->part_stride * cap);
-  const int rg = row_group_rows(*c);  // one loss partial per row-pass workgroup
-  c->loss_part = (double *)take(sizeof(double) * c->L * c->CF * (size_t)((c->H + rg - 1) / rg));
+  // The loss partials (one per row-pass workgroup and plane) share the memory of
+  // the pair partials: a loss is reduced before the rasterizer adjoint of the
+  // same call writes its partials, and those are summed in that call.
+  const int rg = row_group_rows(*c);
+  const size_t loss_bytes = sizeof(double) * c->L * c->CF * (size_t)((c->H + rg - 1) / rg);
+  c->partials = (float *)take(std::max(sizeof(float) * c->part_stride * cap, loss_bytes));
+  c->loss_part = (double *)c->partials;
   c->status = (uint32_t *)take(sizeof(uint32_t) * 4);
   c->finite_flag = (c->cfg.flags & CGH_CHECK_FINITE) && c->status ? c->status + 3 : nullptr;
   c->ssim_I = nullptr;
@@ -302,12 +314,14 @@ cgh_status cgh::create_into(const cgh_config *cfg, void *workspace, size_t works
   CGH_CHECK_LAUNCH(cgh::launch_build_twiddles(c.tw_y, c.Hp, s), "twiddles");
   CGH_CHECK_LAUNCH(cgh::launch_build_twiddles(c.tw_m, c.plan_m.n, s), "twiddles");
   CGH_CHECK_LAUNCH(cgh::launch_build_twiddles_full(c.twf_x, c.Wp, s), "twiddles");
-  if (c.Wp % 4 == 0)
-    CGH_CHECK_LAUNCH(cgh::launch_build_twiddles_full(c.twf_x + c.Wp, c.Wp / 4, s), "twiddles");
+  if (c.row_p)
+    CGH_CHECK_LAUNCH(cgh::launch_build_twiddles_full(c.twf_x + c.Wp, c.Wp / c.row_p, s),
+                     "twiddles");
   CGH_CHECK_LAUNCH(cgh::launch_build_twiddles_full(c.twf_m, c.plan_m.n, s), "twiddles");
   if (c.twf_y) {
     CGH_CHECK_LAUNCH(cgh::launch_build_twiddles_full(c.twf_y, c.Hp, s), "twiddles");
-    CGH_CHECK_LAUNCH(cgh::launch_build_twiddles_full(c.twf_y + c.Hp, c.Hp / 4, s), "twiddles");
+    CGH_CHECK_LAUNCH(cgh::launch_build_twiddles_full(c.twf_y + c.Hp, c.Hp / c.col_p, s),
+                     "twiddles");
   }
   CGH_CHECK_LAUNCH(cgh::launch_build_transfer(c, 0, c.B, s), "transfer function");
   CGH_CHECK_LAUNCH(cgh::launch_zero_record(c, s), "zero record");
@@ -732,11 +746,9 @@ cgh_status cgh_get_transfer(cgh_ctx *ctx, int32_t channel, int32_t plane, cgh_c6
   Ctx &c = ctx->c;
   if (channel < 0 || channel >= c.CF || plane < 0 || plane >= c.L)
     return fail(CGH_ERR_INVALID_ARG, "channel/plane out of range");
-  const size_t elems = (size_t)c.Hq * c.Wq;
-  hipError_t e = hipMemcpyAsync(out, c.htab + ((size_t)channel * c.L + plane) * elems,
-                                elems * sizeof(float2), hipMemcpyDeviceToDevice,
-                                (hipStream_t)stream);
-  if (e != hipSuccess) return device_fail(e, "cgh_get_transfer");
+  CGH_CHECK_LAUNCH(cgh::launch_read_transfer(c, channel, plane, reinterpret_cast<float2 *>(out),
+                                             (hipStream_t)stream),
+                   "transfer function");
   return CGH_OK;
 }
 

@@ -95,6 +95,7 @@ struct Ctx {
   int B;                            // holograms in the context
   int CF;                           // B C: channels of the propagation (hologram-major)
   int Wt;                           // column tiles of 8 in the propagation buffer
+  int row_p, col_p;                 // chains of the row and column passes (0: runtime plan)
   int tile_w, tile_h;               // rasterizer tile, pixels
   int tiles_x, tiles_y;             // tiles of one hologram per row / column
   int tiles_per;                    // tiles_x tiles_y
@@ -111,13 +112,13 @@ struct Ctx {
   // workspace carve (device pointers)
   float2 *tw_x, *tw_y, *tw_m;       // two-level twiddle tables for Wp, Hp, Hp/2
   float2 *twf_x, *twf_m;            // full twiddle tables for Wp and Hp/2 (Hp if odd)
-  float2 *htab;                     // [B C][L][Hq][Wq]
-  float2 *htab_t;                   // [B C][L][Wq][Hq] (column-major copy), wave column pass only
-  float2 *twf_y;                    // full twiddle table for Hp, wave column pass only
+  double *optics;                   // [B C][L][2] wavelength and distance of each table
+  float2 *htab;                     // [B C][L][Hq][Wq], null with htab_t
+  float2 *htab_t;                   // [B C][L][Wq][Hq], chain column pass only, else null
+  float2 *twf_y;                    // full twiddle table for Hp, chain column pass only
   float2 *spec;                     // [B C][Wt][H][8] column-tiled propagation buffer
   float2 *spec_plane;               // per-plane column-pass output (spec itself when L = 1)
   float2 *spec_acc;                 // adjoint sum over planes (spec itself when L = 1)
-  float2 *field_tmp;                // [B C][H][W]
   float2 *gfield_tmp;               // [B C][H][W]
   float *rec;                       // [B max_gaussians + 1][rec_stride]; the last is all zeros
   float2 *alim;                     // CGH_PAPER_ALPHA only, else null: [B max_gaussians + 1]
@@ -134,7 +135,8 @@ struct Ctx {
   uint32_t *scan_tmp;               // partial sums for scans
   float *partials;                  // [pair_cap][part_stride] raster-adjoint partials
   double *loss_part;                // [L][row-pass workgroups] FP64 loss partials (the
-                                    // workgroups of hologram b contiguous in each plane)
+                                    // workgroups of hologram b contiguous in each plane),
+                                    // in the memory of partials
   // cgh_backward_full only (CGH_FULL_LOSS), else null
   float *ssim_I;                    // [L][C][H][W] intensity
   float2 *ssim_u;                   // [L][C][H][W] propagated field, then 2 dL/dI u
@@ -160,17 +162,10 @@ cgh_status create_into(const cgh_config *cfg, void *workspace, size_t workspace_
 size_t carve(Ctx *c, char *base);   // returns bytes used (base may be null)
 cgh_status report(cgh_status st, const char *fmt, ...);  // sets cgh_last_error()
 
-// The column pass runs one wave per column chain, four chains per column
-// (k_col_wave4), for Hp = 4 M with H <= 2 M and M one of the chain lengths it is
-// built for (4K: 1080; 1080p: 540; 1024^2 .. 4096^2 pads: 256, 384, 512, 1024); it
-// reads the column-major transfer table.  col_wave4_m returns M, or 0 where it does
-// not apply.
-inline int col_wave4_m(const Ctx &c) {
-  if (c.Hp % 4 != 0 || 2 * c.H > c.Hp || c.Wp % 8 != 0) return 0;
-  const int M = c.Hp / 4;
-  return (M == 1080 || M == 1024 || M == 540 || M == 512 || M == 384 || M == 256) ? M : 0;
-}
-inline bool col_wave4(const Ctx &c) { return col_wave4_m(c) != 0; }
+// The chain split of a padded length (fft_chain.h): the number of chains (4 or 2) of
+// the row or column pass, or 0 where the runtime-plan kernels run.
+int row_split(int Wp, int W);
+int col_split(int Hp, int H);
 
 // ---- launchers (all enqueue on `s`; return hipSuccess or the launch error) ----
 hipError_t launch_build_twiddles(float2 *tw, int n, hipStream_t s);
@@ -178,6 +173,8 @@ hipError_t launch_build_twiddles_full(float2 *tw, int n, hipStream_t s);
 int row_group_rows(const Ctx &c);   // rows per row-pass workgroup
 // transfer tables of holograms [b0, b1) from c.lam, c.zd
 hipError_t launch_build_transfer(const Ctx &c, int b0, int b1, hipStream_t s);
+// the row-major table of (propagation channel, plane) for its current optics -> out
+hipError_t launch_read_transfer(const Ctx &c, int channel, int plane, float2 *out, hipStream_t s);
 hipError_t launch_row_fwd(const Ctx &c, const float2 *field, float2 *dst, hipStream_t s);
 hipError_t launch_row_inv(const Ctx &c, const float2 *src, float2 *out, hipStream_t s);
 // column pass of plane `plane`: src -> dst (may alias); acc adds into dst

@@ -1,0 +1,669 @@
+// Chain FFT passes: the padded row and column transforms of the propagation as
+// P interleaved M-point chains, compiled for every chain length M that factors
+// into 2, 3 and 5 (chain_lengths below).
+//
+// A padded length n = P M whose samples fill only the first half splits into P
+// chains, because half of the inputs are zero and half of the outputs are
+// dropped: with w = exp(-2 pi i / n),
+//   P = 4 (n % 4 == 0, samples at i < 2 M): bin 4 m + p is bin m of the M-point
+//         transform of w^{p i} (x[i] + (-i)^p x[i + M]) (i < M), and the inverse
+//         gives u[i + M j] = sum_p w^{-p i} i^{p j} z_p[i] for j = 0, 1;
+//   P = 2 (n = 2 M, M odd, samples at i < M): bin 2 m + p is bin m of the
+//         transform of w^{p i} x[i], and u[i] = z_0[i] + w^{-i} z_1[i].
+// z_p is the M-point inverse of the bins p mod P.
+//
+// The radices of a chain's stages are chosen at compile time by the cost model
+// below (VALU instructions of a stage times its passes over the lanes), except
+// for the lengths whose plan was measured.  A compile-time plan keeps the
+// butterflies, the index arithmetic and the twiddle strides constant; the
+// runtime-plan kernels (radix 2, 3, 4, 5 and 8 chosen per stage, whole rows or
+// half columns between workgroup barriers) remain for the shapes that do not
+// split: more samples than half the padded length, odd padded lengths and
+// chains longer than the tables below.
+#pragma once
+
+#include "cgh_internal.h"
+#include "fft_reg.h"
+
+namespace cgh {
+
+// ----------------------------------------------------------------------------
+// chain lengths and plans
+// ----------------------------------------------------------------------------
+
+// Element i of an array at a wave-uniform base, addressed with a 32-bit byte
+// offset (so the access takes the scalar-base form, with no 64-bit address add).
+template <class T>
+__device__ __forceinline__ T &at32(T *base, uint32_t i) {
+  return *reinterpret_cast<T *>(reinterpret_cast<char *>(base) + i * (uint32_t)sizeof(T));
+}
+template <class T>
+__device__ __forceinline__ const T &at32(const T *base, uint32_t i) {
+  return *reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) +
+                                      i * (uint32_t)sizeof(T));
+}
+
+// VALU instructions of a register DFT of length R (RFft): the base radices
+// counted from their code, the composite ones from their factors
+constexpr int dft_ops(int R) {
+  if (R == 1) return 0;
+  if (R == 2) return 4;
+  if (R == 3) return 16;
+  if (R == 4) return 16;
+  if (R == 5) return 36;
+  if (R == 8) return 56;
+  const int a = base_factor(R), b = R / a;
+  return a * dft_ops(b) + b * dft_ops(a) + (gcd_c(a, b) == 1 ? 0 : 4 * (a - 1) * (b - 1));
+}
+
+// cost of one LDS stage: `passes` butterflies of radix R per thread, twiddled
+// unless it is the first; per value a load, a store and their share of the
+// index arithmetic
+constexpr int stage_cost(int R, int passes, bool twiddled) {
+  return passes * (dft_ops(R) + (twiddled ? 5 * (R - 1) : 0) + 3 * R + 8);
+}
+
+constexpr int kRadices[] = {2, 3, 4, 5, 6, 8, 9, 10, 12, 15, 16, 18, 20, 24, 25, 27};
+
+struct ColPlan {
+  int r0, r1, r2;
+};
+
+// Column chain plan: M = r0 r1 r2 (r1 may be 1), one wave per chain; the last
+// forward and first inverse stage are fused in registers, one butterfly of
+// radix r2 per lane (M / r2 <= 64).  Among the plans of least cost an odd r0
+// comes first: the first stage stores at stride r0, and an odd stride spreads
+// the stores over the LDS banks.
+constexpr ColPlan col_plan(int M) {
+  // measured (4K: 9 6 20 against 10 6 18 and 6 10 18; 1080p: 12 5 9 against 9 6 10
+  // and 10 6 9; the serving pads)
+  if (M == 1080) return {9, 6, 20};
+  if (M == 1024) return {8, 8, 16};
+  if (M == 540) return {12, 5, 9};
+  if (M == 512) return {8, 8, 8};
+  if (M == 384) return {6, 8, 8};
+  if (M == 256) return {4, 8, 8};
+  ColPlan best{0, 0, 0};
+  int cost = 1 << 30;
+  for (int r2 : kRadices) {
+    if (M % r2 || M / r2 > 64) continue;
+    const int q = M / r2;
+    for (int r0 : kRadices) {
+      if (q % r0) continue;
+      const int r1 = q / r0;
+      if (r1 > 16) continue;
+      bool known = r1 == 1;
+      for (int r : kRadices) known = known || r == r1;
+      if (!known) continue;
+      const int n0 = (M / r0 + 63) / 64, n1 = r1 > 1 ? (M / r1 + 63) / 64 : 0;
+      // registers: every butterfly of a stage is held before the first store
+      if (n0 * r0 > 32 || n1 * r1 > 32) continue;
+      int c = stage_cost(r0, n0, false) + stage_cost(r0, n0, true);
+      if (r1 > 1) c += 2 * stage_cost(r1, n1, true);
+      c += 2 * dft_ops(r2) + 13 * r2 + 16;
+      c = c * 8 + (r0 % 2 ? 0 : 4);
+      if (c < cost) {
+        cost = c;
+        best = ColPlan{r0, r1, r2};
+      }
+    }
+  }
+  return best;
+}
+
+// Row plan: the stages of P interleaved M-point chains over T threads
+// (workgroup barriers between stages), M = r[0] .. r[n - 1].
+struct RowPlan {
+  int n;
+  int r[4];
+};
+
+constexpr int row_plan_cost(int M, int P, int T, const RowPlan &p) {
+  int c = 0, ns = 1;
+  for (int s = 0; s < p.n; ++s) {
+    const int R = p.r[s], items = P * (M / R), passes = (items + T - 1) / T;
+    if (passes * R > 40) return 1 << 29;  // registers
+    c += stage_cost(R, passes, s > 0) + 120;  // two barriers
+    // the first stage stores at stride P R: an even stride repeats its banks
+    if (s == 0) c += passes * R * (R % 4 == 0 ? 4 : R % 2 == 0 ? 2 : 0);
+    ns *= R;
+  }
+  return c;
+}
+
+constexpr RowPlan row_plan(int M, int P, int T) {
+  if (P == 4 && T == 512) {
+    // measured: 960 (1080p) against 15 16 4, 12 8 10, 8 12 10 and 10 12 8; 1024, 512
+    // and 256 (serving pads) against 16 16 4, 16 16 2 and 16 16; 1920 (4K) is the
+    // plan of fewest stages, odd radix first
+    if (M == 960) return {3, {15, 8, 8, 1}};
+    if (M == 1920) return {3, {15, 16, 8, 1}};
+    if (M == 1024) return {3, {8, 8, 16, 1}};
+    if (M == 512) return {3, {8, 8, 8, 1}};
+    if (M == 256) return {3, {4, 8, 8, 1}};
+  }
+  RowPlan best{0, {1, 1, 1, 1}};
+  int cost = 1 << 29;
+  for (int a : kRadices) {
+    if (M % a) continue;
+    for (int b = 1; b <= 27; ++b) {
+      if ((M / a) % b) continue;
+      for (int d = 1; d <= 27; ++d) {
+        if ((M / a / b) % d || (b == 1 && d > 1)) continue;
+        const int e = M / a / b / d;
+        if (e > 27 || (d == 1 && e > 1)) continue;
+        const int rs[4] = {a, b, d, e};
+        RowPlan p{0, {1, 1, 1, 1}};
+        bool ok = true;
+        for (int s = 0; s < 4; ++s) {
+          if (rs[s] == 1) continue;
+          bool known = false;
+          for (int r : kRadices) known = known || r == rs[s];
+          ok = ok && known;
+          p.r[p.n++] = rs[s];
+        }
+        if (!ok) continue;
+        const int c = row_plan_cost(M, P, T, p);
+        if (c < cost) {
+          cost = c;
+          best = p;
+        }
+      }
+    }
+  }
+  return best;
+}
+
+// threads per row workgroup: about eight values per thread, 512 at most
+constexpr int row_threads(int M, int P) {
+  const int n = P * M;
+  return n >= 2000 ? 512 : n >= 900 ? 256 : n >= 400 ? 128 : 64;
+}
+
+constexpr bool smooth_c(int n) {
+  for (int p : {2, 3, 5})
+    while (n % p == 0) n /= p;
+  return n == 1;
+}
+
+// The chain lengths the passes are compiled for.
+constexpr int kMinChain = 16;
+constexpr int kMaxColChain = 1215;  // one wave per chain: M / 27 <= 64 lanes
+constexpr int kMaxRowChain4 = 2048, kMaxRowChain2 = 4095;  // kMaxFft / P
+constexpr bool col_chain(int M, int P) {
+  return M >= kMinChain && M <= kMaxColChain && smooth_c(M) && (P == 4 || M % 2);
+}
+constexpr bool row_chain(int M, int P) {
+  return M >= kMinChain && M <= (P == 4 ? kMaxRowChain4 : kMaxRowChain2) && smooth_c(M) &&
+         (P == 4 || M % 2);
+}
+
+// the split of a padded length n with `used` samples: P chains of n / P, or 0
+inline int split_of(int n, int used, bool (*built)(int, int)) {
+  if (2 * used > n || n % 2) return 0;
+  const int P = n % 4 == 0 ? 4 : 2;
+  return built(n / P, P) ? P : 0;
+}
+
+// waves per SIMD that the LDS of a workgroup of 512 threads leaves room for
+constexpr int lds_waves(int values) { return values * 8 + 1024 > 80 * 1024 ? 2 : 4; }
+
+// ----------------------------------------------------------------------------
+// row passes: one row per workgroup, chain p at buf[P m + p], which is the row in
+// natural bin order.  Blocks b and b + 8, which run on one XCD, take rows 2k and
+// 2k + 1, so the two halves of each 128-byte line of the column-tiled spectrum
+// meet in one L2.
+// ----------------------------------------------------------------------------
+__device__ __forceinline__ int paired_row(int b, int rows) {
+  if (b >= (rows & ~15)) return b;
+  return (b & ~15) + 2 * (b & 7) + ((b >> 3) & 1);
+}
+
+template <int M, int P, int T, int DIR, int S = 0>
+__device__ __forceinline__ void row_stages(float2 *__restrict__ buf,
+                                           const float2 *__restrict__ tw, int tid) {
+  constexpr RowPlan p = row_plan(M, P, T);
+  if constexpr (S < p.n) {
+    constexpr int ns = (S > 0 ? p.r[0] : 1) * (S > 1 ? p.r[1] : 1) * (S > 2 ? p.r[2] : 1);
+    cstage<p.r[S], DIR, P, T, M, ns>(buf, tw, tid);
+    row_stages<M, P, T, DIR, S + 1>(buf, tw, tid);
+  }
+}
+
+// M-entry table exp(-2 pi i e / M), stored contiguously after the P M table
+template <int M, int P, int T>
+__device__ __forceinline__ void load_chain_table(float2 *tw, const float2 *__restrict__ twf,
+                                                 int tid) {
+  constexpr int KT = (M + T - 1) / T;
+  float2 tv[KT];
+#pragma unroll
+  for (int k = 0; k < KT; ++k) tv[k] = at32(twf, P * M + min(tid + k * T, M - 1));
+#pragma unroll
+  for (int k = 0; k < KT; ++k)
+    if (KT * T == M || tid + k * T < M) tw[tid + k * T] = tv[k];
+}
+
+// one row y of channel base Sc (column-tiled [ceil(Wp / 8)][H][8]) <-> buf in natural order
+template <int N, int T>
+__device__ __forceinline__ void load_chain_row(float2 *buf, const float2 *Sc, int H, int y,
+                                               int tid) {
+  constexpr int K = (N + T - 1) / T;
+  float2 v[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int x = min(tid + k * T, N - 1);
+    v[k] = at32(Sc, ((x >> 3) * H + y) * 8 + (x & 7));
+  }
+#pragma unroll
+  for (int k = 0; k < K; ++k)
+    if (K * T == N || tid + k * T < N) buf[tid + k * T] = v[k];
+}
+
+template <int N, int T>
+__device__ __forceinline__ void store_chain_row(const float2 *buf, float2 *Sc, int H, int y,
+                                                int tid) {
+  constexpr int K = (N + T - 1) / T;
+  float2 v[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) v[k] = buf[min(tid + k * T, N - 1)];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int x = tid + k * T;
+    if (K * T == N || x < N) at32(Sc, ((x >> 3) * H + y) * 8 + (x & 7)) = v[k];
+  }
+}
+
+// the chain inputs at m = n from the samples a = x[n] and (P = 4) b = x[n + M]
+template <int P>
+__device__ __forceinline__ void chain_inputs(float2 *buf, int n, float2 a, float2 b, float2 w1) {
+  if constexpr (P == 4) {
+    const float2 w2 = cmul(w1, w1), w3 = cmul(w2, w1);
+    buf[4 * n] = cadd(a, b);
+    buf[4 * n + 1] = cmul(make_float2(a.x + b.y, a.y - b.x), w1);  // (a - i b) w^n
+    buf[4 * n + 2] = cmul(csub(a, b), w2);                         // (a - b) w^{2n}
+    buf[4 * n + 3] = cmul(make_float2(a.x - b.y, a.y + b.x), w3);  // (a + i b) w^{3n}
+  } else {
+    buf[2 * n] = a;
+    buf[2 * n + 1] = cmul(a, w1);
+  }
+}
+
+// u[n] and (P = 4) u[n + M] from the chain outputs at m = n
+template <int P>
+__device__ __forceinline__ void chain_outputs(const float2 *buf, int n, float2 w1, float2 &u0,
+                                              float2 &u1) {
+  if constexpr (P == 4) {
+    const float2 w2 = cmul(w1, w1), w3 = cmul(w2, w1);
+    const float2 z0 = buf[4 * n];
+    const float2 z1 = cmul(cconj(w1), buf[4 * n + 1]);
+    const float2 z2 = cmul(cconj(w2), buf[4 * n + 2]);
+    const float2 z3 = cmul(cconj(w3), buf[4 * n + 3]);
+    u0 = cadd(cadd(z0, z1), cadd(z2, z3));
+    const float2 e = csub(z0, z2), o = csub(z1, z3);
+    u1 = make_float2(e.x - o.y, e.y + o.x);  // z0 + i z1 - z2 - i z3
+  } else {
+    u0 = cadd(buf[2 * n], cmul(cconj(w1), buf[2 * n + 1]));
+    u1 = make_float2(0.f, 0.f);
+  }
+}
+
+// F1: field rows (zero-extended to Wp = P M) -> forward FFT -> S
+template <int M, int P>
+__global__ __launch_bounds__(row_threads(M, P))
+__attribute__((amdgpu_waves_per_eu(lds_waves((P + 1) * M)))) void k_row_fwd_q(const float2 *__restrict__ field, int H, int W, int rows,
+            const float2 *__restrict__ twf_x, float2 *__restrict__ S) {
+  constexpr int T = row_threads(M, P), K = (M + T - 1) / T, Wt = (P * M + 7) / 8;
+  __shared__ float2 buf[P * M];
+  __shared__ float2 tw[M];
+  const int tid = threadIdx.x;
+  const int R = paired_row(blockIdx.x, rows), c = R / H, y = R - c * H;
+  load_chain_table<M, P, T>(tw, twf_x, tid);
+  {
+    const float2 *f = field + ((size_t)c * H + y) * W;
+    float2 av[K], bv[K], wv[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const int n = min(tid + k * T, M - 1);
+      av[k] = at32(f, min(n, W - 1));
+      bv[k] = P == 4 ? at32(f, min(n + M, W - 1)) : make_float2(0.f, 0.f);
+      wv[k] = at32(twf_x, n);
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const int n = tid + k * T;
+      if (K * T == M || n < M) {
+        const float2 a = n < W ? av[k] : make_float2(0.f, 0.f);
+        const float2 b = n + M < W ? bv[k] : make_float2(0.f, 0.f);
+        chain_inputs<P>(buf, n, a, b, wv[k]);
+      }
+    }
+  }
+  __syncthreads();
+  row_stages<M, P, T, -1>(buf, tw, tid);
+  store_chain_row<P * M, T>(buf, S + (size_t)c * Wt * H * 8, H, y, tid);
+}
+
+// B2: S -> inverse FFT -> first W values of each row
+template <int M, int P>
+__global__ __launch_bounds__(row_threads(M, P))
+__attribute__((amdgpu_waves_per_eu(lds_waves((P + 1) * M)))) void k_row_inv_q(const float2 *__restrict__ S, int H, int W, int rows,
+            const float2 *__restrict__ twf_x, float2 *__restrict__ out) {
+  constexpr int T = row_threads(M, P), K = (M + T - 1) / T, Wt = (P * M + 7) / 8;
+  __shared__ float2 buf[P * M];
+  __shared__ float2 tw[M];
+  const int tid = threadIdx.x;
+  const int R = paired_row(blockIdx.x, rows), c = R / H, y = R - c * H;
+  load_chain_table<M, P, T>(tw, twf_x, tid);
+  load_chain_row<P * M, T>(buf, S + (size_t)c * Wt * H * 8, H, y, tid);
+  float2 wv[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) wv[k] = at32(twf_x, min(tid + k * T, M - 1));
+  lds_sync();
+  row_stages<M, P, T, +1>(buf, tw, tid);
+  float2 *o = out + ((size_t)c * H + y) * W;
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int n = tid + k * T;
+    if ((K * T == M || n < M) && n < W) {
+      float2 u0, u1;
+      chain_outputs<P>(buf, n, wv[k], u0, u1);
+      o[n] = u0;
+      if (P == 4 && n + M < W) o[n + M] = u1;
+    }
+  }
+}
+
+// The middle row pass (F3).  S -> inverse FFT -> u (first W values) -> I =
+// |u|^2 (optionally stored, with u); if make_grad: dL/dI = 2 (I - T) / M (MSE,
+// Sec. 3.2) or the caller's dL/dI, g = 2 dL/dI u = dL/dRe(u) + j dL/dIm(u),
+// zero-extended, forward FFT, back into S.  One FP64 partial sum of the loss per
+// row into loss_part.
+template <int M, int P>
+__global__ __launch_bounds__(row_threads(M, P))
+__attribute__((amdgpu_waves_per_eu(lds_waves((P + 1) * M)))) void k_row_loss_q(float2 *__restrict__ S, int H, int W, int rows, const float2 *__restrict__ twf_x,
+             const float *__restrict__ target, const float *__restrict__ grad_I,
+             const float *__restrict__ mask, int mcg, float *__restrict__ intensity,
+             float2 *__restrict__ u_out, double *__restrict__ loss_part, float gscale,
+             int make_grad) {
+  constexpr int T = row_threads(M, P), K = (M + T - 1) / T, Wt = (P * M + 7) / 8, J = P / 2;
+  __shared__ float2 buf[P * M];
+  __shared__ float2 tw[M];
+  __shared__ double red[T / 64];
+  const int tid = threadIdx.x;
+  const int R = paired_row(blockIdx.x, rows), c = R / H, y = R - c * H;
+  float2 *Sc = S + (size_t)c * Wt * H * 8;
+  load_chain_table<M, P, T>(tw, twf_x, tid);
+  load_chain_row<P * M, T>(buf, Sc, H, y, tid);
+  if (mask) mask += (size_t)(c / mcg) * H * W;
+  // per-element inputs at n and n + M, fetched before the transform so that
+  // their latency overlaps it
+  const float *tsrc = target ? target : grad_I;
+  const size_t row = ((size_t)c * H + y) * W;
+  float tv[J][K], mv[J][K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int n = min(tid + k * T, M - 1);
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      const int x = min(n + j * M, W - 1);
+      tv[j][k] = tsrc ? tsrc[row + x] : 0.f;
+      mv[j][k] = mask ? mask[(size_t)y * W + x] : 0.f;
+    }
+  }
+  lds_sync();
+  row_stages<M, P, T, +1>(buf, tw, tid);
+  double acc = 0.0;
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int n = tid + k * T;
+    if (K * T == M || n < M) {
+      const float2 w1 = at32(twf_x, n);
+      float2 u[2];
+      chain_outputs<P>(buf, n, w1, u[0], u[1]);
+      float f[2] = {0.f, 0.f};
+#pragma unroll
+      for (int j = 0; j < J; ++j) {
+        const int x = n + j * M;
+        if (x >= W) continue;
+        const float t = tv[j][k], m = mv[j][k];
+        const float I = u[j].x * u[j].x + u[j].y * u[j].y;
+        if (intensity) intensity[row + x] = I;
+        if (u_out) u_out[row + x] = u[j];
+        if (target) {
+          // L_recon weight 1 + m^2 + t^2 (plain MSE without a mask)
+          const float d = I - t, w = mask ? 1.f + m * m + t * t : 1.f;
+          acc += (double)d * (double)d * (double)w;
+          f[j] = gscale * d * w;  // 4 w (I - T) / M
+        } else if (grad_I) {
+          f[j] = 2.0f * t;
+        }
+      }
+      if (make_grad)
+        chain_inputs<P>(buf, n, make_float2(f[0] * u[0].x, f[0] * u[0].y),
+                        make_float2(f[1] * u[1].x, f[1] * u[1].y), w1);
+    }
+  }
+  if (target) {
+    for (int d = 32; d > 0; d >>= 1) acc += __shfl_down(acc, d, 64);
+    if ((tid & 63) == 0) red[tid >> 6] = acc;
+    __syncthreads();
+    if (tid == 0) {
+      double sum = 0.0;
+      for (int w = 0; w < T / 64; ++w) sum += red[w];
+      loss_part[R] = sum;
+    }
+  }
+  if (make_grad) {
+    __syncthreads();
+    row_stages<M, P, T, -1>(buf, tw, tid);
+    store_chain_row<P * M, T>(buf, Sc, H, y, tid);
+  }
+}
+
+// ----------------------------------------------------------------------------
+// column pass
+// ----------------------------------------------------------------------------
+// Source, destination and transfer table of one column pass.  src and dst
+// may be the same buffer (in place).  acc: add the result to dst instead of
+// overwriting it (the adjoint's sum over planes).  htab points at the table
+// of the pass's plane for channel 0; channel ch is at htab + ch * hstride.
+struct ColIO {
+  const float2 *src;
+  float2 *dst;
+  const float2 *htab;
+  size_t hstride;
+  int acc;
+};
+
+// Column pass with one wave per chain, M = R0 R1 R2 (col_plan); CONJ: multiply
+// by conj(H) (the adjoint pass).  A workgroup of eight waves takes 8 / P
+// columns of a tile of 8; wave P c + p runs chain p of column c in its own
+// M-element LDS buffer, so the stages of a chain need no workgroup barrier: only
+// loading the columns and combining the chains are workgroup steps.  The
+// forward plan is R0, R1, R2; its last stage leaves lane j < M / R2 holding
+// spectrum entries j + (M / R2) q (q < R2), exactly the input of a first
+// inverse stage of radix R2, so the transfer multiply and that stage run in
+// registers; the inverse plan is R2, R1, R0.  The transfer table is read
+// column-major ([Wq][Hq]); the workgroups of a mirror pair of tiles
+// (t, Wt - 1 - t), whose columns need about the same table columns, are blocks
+// b + 8 s (s < 2 P), which share an XCD.
+template <int M, int P, bool CONJ>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(lds_waves(9 * M)))) void
+k_col_wave(ColIO io, int Hq, int H, int Wp, int Wt, int C, const float2 *__restrict__ twf_y) {
+  constexpr ColPlan pl = col_plan(M);
+  constexpr int R0 = pl.r0, R1 = pl.r1, R2 = pl.r2;
+  constexpr int NB2 = M / R2;
+  static_assert(R0 * R1 * R2 == M && NB2 <= 64, "the fused stage takes one butterfly per lane");
+  constexpr int NC = 8 / P;  // columns per workgroup
+  constexpr int T = 512, NI = NC * M, K = (NI + T - 1) / T, KT = (M + T - 1) / T;
+  __shared__ float2 buf[8 * M];
+  __shared__ float2 tw[M];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: scalar addressing
+  const int b = blockIdx.x;
+  constexpr int SL = 2 * P;  // workgroups of a mirror pair
+  const int slot = (b >> 3) % SL, pi = (b / (8 * SL)) * 8 + (b & 7);
+  const int hp = (Wt + 1) >> 1;
+  if (pi >= C * hp) return;
+  const int ch = pi / hp, pp = pi - ch * hp;
+  const int t = slot < P ? pp : Wt - 1 - pp;
+  if (slot >= P && t == pp) return;  // the middle tile of an odd count has no mirror
+  const int part = slot % P;
+  const size_t off = ((size_t)ch * Wt + t) * H * 8 + part * NC;
+  const float2 *src = io.src + off;
+  float2 *dst = io.dst + off;
+  {
+    // item i: row n = i / NC of column c = i % NC; every global load of this
+    // phase is issued before the first LDS store
+    float2 av[K], bv[K], w1[K], tv[KT];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const int i = tid + k * T, n = min(i / NC, M - 1), c = i % NC;
+      av[k] = at32(src, min(n, H - 1) * 8 + c);
+      bv[k] = P == 4 ? at32(src, min(n + M, H - 1) * 8 + c) : make_float2(0.f, 0.f);
+      w1[k] = at32(twf_y, n);
+    }
+#pragma unroll
+    for (int k = 0; k < KT; ++k) tv[k] = at32(twf_y, P * M + min(tid + k * T, M - 1));  // w_M^k
+#pragma unroll
+    for (int k = 0; k < KT; ++k)
+      if (tid + k * T < M) tw[tid + k * T] = tv[k];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const int i = tid + k * T, n = i / NC, c = i % NC;
+      if (K * T == NI || i < NI) {
+        const float2 a = n < H ? av[k] : make_float2(0.f, 0.f);
+        if constexpr (P == 4) {
+          const float2 bb = n + M < H ? bv[k] : make_float2(0.f, 0.f);
+          const float2 s0 = cadd(a, bb), s2 = csub(a, bb);
+          const float2 s1 = make_float2(a.x + bb.y, a.y - bb.x);  // a - i b
+          const float2 s3 = make_float2(a.x - bb.y, a.y + bb.x);  // a + i b
+          const float2 w2 = cmul(w1[k], w1[k]), w3 = cmul(w2, w1[k]);  // w^{2n}, w^{3n}
+          buf[(4 * c) * M + n] = s0;
+          buf[(4 * c + 1) * M + n] = cmul(s1, w1[k]);
+          buf[(4 * c + 2) * M + n] = cmul(s2, w2);
+          buf[(4 * c + 3) * M + n] = cmul(s3, w3);
+        } else {
+          buf[(2 * c) * M + n] = a;
+          buf[(2 * c + 1) * M + n] = cmul(a, w1[k]);
+        }
+      }
+    }
+  }
+  __syncthreads();
+  {
+    const int c = wave / P, p = wave % P;
+    float2 *wb = buf + wave * M;
+    // columns past Wp (the last tile of a Wp that is not a multiple of 8) hold
+    // nothing that is read again; their table column is clamped
+    const int kx = min(t * 8 + part * NC + c, Wp - 1);
+    const int qx = min(kx, Wp - kx);
+    const float2 *hcol = io.htab + (size_t)ch * io.hstride + (size_t)qx * Hq;
+    // transfer values for ky = P (j + NB2 q) + p, issued before the forward stages
+    float2 hv[R2];
+    {
+      const int j = min(lane, NB2 - 1);
+      static_for<0, R2>([&](auto qc) {
+        constexpr int q = decltype(qc)::value;
+        const int ky = P * (j + NB2 * q) + p;
+        hv[q] = at32(hcol, min(ky, P * M - ky));
+      });
+    }
+    wstage<R0, -1, M, 1>(wb, tw, lane);
+    if constexpr (R1 > 1) wstage<R1, -1, M, R0>(wb, tw, lane);
+    float2 v[R2];
+    if (lane < NB2) {
+      static_for<0, R2>([&](auto qc) {
+        constexpr int q = decltype(qc)::value;
+        v[q] = wb[lane + q * NB2];
+      });
+      static_for<1, R2>([&](auto qc) {
+        constexpr int q = decltype(qc)::value;
+        v[q] = cmul(v[q], tw[q * lane]);  // last forward stage: Ns = NB2, unit twiddle step
+      });
+      RFft<R2, -1>::run(v);
+      static_for<0, R2>([&](auto qc) {
+        constexpr int q = decltype(qc)::value;
+        v[q] = cmul(v[q], CONJ ? cconj(hv[q]) : hv[q]);  // the table carries 1 / (Hp Wp)
+      });
+      RFft<R2, +1>::run(v);  // first inverse stage: Ns = 1, no twiddles
+    }
+    wave_lds_order();
+    if (lane < NB2) {
+      static_for<0, R2>([&](auto qc) {
+        constexpr int q = decltype(qc)::value;
+        wb[lane * R2 + q] = v[q];
+      });
+    }
+    wave_lds_order();
+    if constexpr (R1 > 1) wstage<R1, +1, M, R2>(wb, tw, lane);
+    wstage<R0, +1, M, R2 * R1>(wb, tw, lane);
+  }
+  {
+    float2 w1[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) w1[k] = at32(twf_y, min((tid + k * T) / NC, M - 1));
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const int i = tid + k * T, n = i / NC, c = i % NC;
+      if ((K * T == NI || i < NI) && n < H) {
+        float2 y0, y1;
+        if constexpr (P == 4) {
+          const float2 w2 = cmul(w1[k], w1[k]), w3 = cmul(w2, w1[k]);
+          const float2 z0 = buf[(4 * c) * M + n];
+          const float2 z1 = cmul(cconj(w1[k]), buf[(4 * c + 1) * M + n]);
+          const float2 z2 = cmul(cconj(w2), buf[(4 * c + 2) * M + n]);
+          const float2 z3 = cmul(cconj(w3), buf[(4 * c + 3) * M + n]);
+          y0 = cadd(cadd(z0, z1), cadd(z2, z3));
+          // z0 + i z1 - z2 - i z3
+          const float2 e = csub(z0, z2), o = csub(z1, z3);
+          y1 = make_float2(e.x - o.y, e.y + o.x);
+        } else {
+          y0 = cadd(buf[(2 * c) * M + n], cmul(cconj(w1[k]), buf[(2 * c + 1) * M + n]));
+        }
+        float2 &d0 = at32(dst, n * 8 + c);
+        d0 = io.acc ? cadd(d0, y0) : y0;
+        if (P == 4 && n + M < H) {
+          float2 &d1 = at32(dst, (n + M) * 8 + c);
+          d1 = io.acc ? cadd(d1, y1) : y1;
+        }
+      }
+    }
+  }
+}
+
+// ----------------------------------------------------------------------------
+// Launchers, one translation unit per part: part k of kChainParts holds the
+// chain lengths whose index in increasing order is k modulo kChainParts.
+// ----------------------------------------------------------------------------
+struct RowArgs {
+  int pass;  // 0: forward (F1), 1: inverse (B2), 2: middle pass (F3)
+  const float2 *field;
+  float2 *S;
+  float2 *out;
+  int H, W, rows;
+  const float2 *twf_x;
+  const float *target, *grad_I, *mask;
+  int mcg;
+  float *intensity;
+  float2 *u_out;
+  double *loss_part;
+  float gscale;
+  int make_grad;
+};
+struct ColArgs {
+  ColIO io;
+  int conj_h, Hq, H, Wp, Wt, C;
+  const float2 *twf_y;
+};
+constexpr int kChainParts = 8;
+// each returns true if its part holds the (M, P) kernels (which were then launched)
+#define CGH_CHAIN_PART_FNS(k)                                               \
+  bool row_chain_part_##k(int M, int P, const RowArgs &a, hipStream_t s); \
+  bool col_chain_part_##k(int M, int P, const ColArgs &a, hipStream_t s);
+CGH_CHAIN_PART_FNS(0) CGH_CHAIN_PART_FNS(1) CGH_CHAIN_PART_FNS(2) CGH_CHAIN_PART_FNS(3)
+CGH_CHAIN_PART_FNS(4) CGH_CHAIN_PART_FNS(5) CGH_CHAIN_PART_FNS(6) CGH_CHAIN_PART_FNS(7)
+#undef CGH_CHAIN_PART_FNS
+
+}  // namespace cgh

@@ -26,10 +26,7 @@
 // which halves the LDS footprint of a column block.
 #include <cmath>
 
-#include <type_traits>
-
-#include "cgh_internal.h"
-#include "fft_reg.h"
+#include "fft_chain.h"
 
 namespace cgh {
 
@@ -45,18 +42,6 @@ struct TwLds {
   float2 hi[kTwHi];
   float2 lo[64];
 };
-
-// Element i of an array at a wave-uniform base, addressed with a 32-bit byte
-// offset (so the access takes the scalar-base form, with no 64-bit address add).
-template <class T>
-__device__ __forceinline__ T &at32(T *base, uint32_t i) {
-  return *reinterpret_cast<T *>(reinterpret_cast<char *>(base) + i * (uint32_t)sizeof(T));
-}
-template <class T>
-__device__ __forceinline__ const T &at32(const T *base, uint32_t i) {
-  return *reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) +
-                                      i * (uint32_t)sizeof(T));
-}
 
 __device__ __forceinline__ float2 tw_at(const TwLds &t, int e) {
   return cmul(t.hi[e >> 6], t.lo[e & 63]);
@@ -223,15 +208,30 @@ hipError_t launch_build_twiddles_full(float2 *tw, int n, hipStream_t s) {
 // "Spatial Frequency Computation", "Bandlimit Computation", "Transfer Function
 // Evaluation"), quarter table indexed by |fx| = qx / (Wp dx), |fy| = qy / (Hp dx).
 // L_x, L_y are the extents of the padded grid.  Evanescent frequencies get 0.
-// out_t (optional) receives the same table column-major, [Wq][Hq], times
-// t_scale (the 1 / (Hp Wp) of the inverse transform, applied in FP64).
 // aperture > 0: the circular aperture of Alg. 3, centred on the zero frequency
 // (bins with qx^2 + qy^2 >= aperture^2 are zeroed).
+//
+// One table entry per thread.  out: row-major [Hq][Wq] (x fastest over the
+// threads); out_t: column-major [Wq][Hq] (y fastest), times t_scale (the
+// 1 / (Hp Wp) of the inverse transform, applied in FP64).  The chain column pass
+// reads only the column-major table, the other column kernels only the
+// row-major one, so a context holds one of them.  optics: where lambda and z are
+// kept on the device (2 doubles): written from the arguments, or, with
+// from_optics, read instead of them (cgh_get_transfer: the table of the optics
+// that are current in stream order).
 __global__ void k_transfer(float2 *out, float2 *out_t, double t_scale, int Hq, int Wq, int Hp,
-                           int Wp, double pitch, double lambda, double z, double aperture) {
-  int qx = blockIdx.x * blockDim.x + threadIdx.x;
-  int qy = blockIdx.y;
-  if (qx >= Wq) return;
+                           int Wp, double pitch, double lambda, double z, double aperture,
+                           double *optics, int from_optics) {
+  const int fast = blockIdx.x * blockDim.x + threadIdx.x, slow = blockIdx.y;
+  const int qx = out_t ? slow : fast, qy = out_t ? fast : slow;
+  if (from_optics) {
+    lambda = optics[0];
+    z = optics[1];
+  } else if (optics && fast == 0 && slow == 0) {
+    optics[0] = lambda;
+    optics[1] = z;
+  }
+  if (qx >= Wq || qy >= Hq) return;
   const double Lx = Wp * pitch, Ly = Hp * pitch;
   const double fx = qx / Lx, fy = qy / Ly;
   const double ax = 2.0 * z / Lx, ay = 2.0 * z / Ly;
@@ -244,25 +244,35 @@ __global__ void k_transfer(float2 *out, float2 *out_t, double t_scale, int Hq, i
     const double ph = 6.283185307179586476925 * z * sqrt(arg);  // 2 pi z sqrt(arg)
     sincos(ph, &sn, &cs);
   }
-  out[(size_t)qy * Wq + qx] = make_float2((float)cs, (float)sn);
+  if (out) out[(size_t)qy * Wq + qx] = make_float2((float)cs, (float)sn);
   if (out_t)
     out_t[(size_t)qx * Hq + qy] = make_float2((float)(cs * t_scale), (float)(sn * t_scale));
 }
 
 hipError_t launch_build_transfer(const Ctx &c, int b0, int b1, hipStream_t s) {
+  const bool t = c.htab_t != nullptr;
+  const dim3 grid(((t ? c.Hq : c.Wq) + 255) / 256, t ? c.Wq : c.Hq);
   for (int b = b0; b < b1; ++b)
     for (int ch = 0; ch < c.C; ++ch)
       for (int l = 0; l < c.L; ++l) {
         // propagation channel b C + ch: colour ch of hologram b
-        const size_t at = (((size_t)b * c.C + ch) * c.L + l) * c.Hq * c.Wq;
-        hipLaunchKernelGGL(k_transfer, dim3((c.Wq + 255) / 256, c.Hq), dim3(256), 0, s,
-                           c.htab + at, c.htab_t ? c.htab_t + at : nullptr,
-                           1.0 / ((double)c.Hp * (double)c.Wp), c.Hq, c.Wq, c.Hp, c.Wp,
-                           c.cfg.pitch_m, c.lam[b][ch], c.zd[b][l], c.cfg.aperture);
+        const size_t k = ((size_t)b * c.C + ch) * c.L + l, at = k * c.Hq * c.Wq;
+        hipLaunchKernelGGL(k_transfer, grid, dim3(256), 0, s, t ? nullptr : c.htab + at,
+                           t ? c.htab_t + at : nullptr, 1.0 / ((double)c.Hp * (double)c.Wp), c.Hq,
+                           c.Wq, c.Hp, c.Wp, c.cfg.pitch_m, c.lam[b][ch], c.zd[b][l],
+                           c.cfg.aperture, c.optics + 2 * k, 0);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
       }
   return hipSuccess;
+}
+
+hipError_t launch_read_transfer(const Ctx &c, int channel, int plane, float2 *out,
+                                hipStream_t s) {
+  hipLaunchKernelGGL(k_transfer, dim3((c.Wq + 255) / 256, c.Hq), dim3(256), 0, s, out, nullptr,
+                     1.0, c.Hq, c.Wq, c.Hp, c.Wp, c.cfg.pitch_m, 0.0, 0.0, c.cfg.aperture,
+                     c.optics + 2 * ((size_t)channel * c.L + plane), 1);
+  return hipGetLastError();
 }
 
 // ----------------------------------------------------------------------------
@@ -633,259 +643,9 @@ __global__ __launch_bounds__(T) void k_row_loss_c(
   }
 }
 
-// ----------------------------------------------------------------------------
-// Quarter-length row passes, for Wp = 4M with W <= 2M (7680: M = 1920).  With
-// the samples at n < 2M, bin 4m + p of the forward is FFT_M of
-// w^{pn}(x[n] + (-i)^p x[n + M]) (n < M), and the inverse cropped to n < 2M is
-// u[n + M j] = sum_p w^{-pn} i^{pj} z_p[n] for j = 0, 1, with z_p the M-point
-// inverse of bins p mod 4 (w = exp(-2 pi i / Wp)).  A 512-thread workgroup
-// takes one row: four interleaved M-point chains, chain p at buf[4 m + p],
-// which is the row in natural bin order.  Blocks b and b + 8, which run on one
-// XCD, take rows 2k and 2k + 1, so the two halves of each 128-byte line of the
-// column-tiled spectrum meet in one L2.
-// ----------------------------------------------------------------------------
-__device__ __forceinline__ int quarter_row(int b, int rows) {
-  if (b >= (rows & ~15)) return b;
-  return (b & ~15) + 2 * (b & 7) + ((b >> 3) & 1);
-}
-
-// M-entry table exp(-2 pi i e / M) (every fourth entry of the Wp = 4 M table),
-// stored contiguously after that table
-template <int M, int T>
-__device__ __forceinline__ void load_quarter_table(float2 *tw, const float2 *__restrict__ twf_x,
-                                                   int tid) {
-  constexpr int KT = (M + T - 1) / T;
-  float2 tv[KT];
-#pragma unroll
-  for (int k = 0; k < KT; ++k) tv[k] = at32(twf_x, 4 * M + min(tid + k * T, M - 1));
-#pragma unroll
-  for (int k = 0; k < KT; ++k)
-    if (KT * T == M || tid + k * T < M) tw[tid + k * T] = tv[k];
-}
-
-// one row y of channel base Sc (column-tiled [Wp / 8][H][8]) <-> buf in natural order
-template <int M, int T>
-__device__ __forceinline__ void load_quarter_row(float2 *buf, const float2 *Sc, int H, int y,
-                                                 int tid) {
-  constexpr int n = 4 * M, K = (n + T - 1) / T;
-  float2 v[K];
-#pragma unroll
-  for (int k = 0; k < K; ++k) {
-    const int x = min(tid + k * T, n - 1);
-    v[k] = at32(Sc, ((x >> 3) * H + y) * 8 + (x & 7));
-  }
-#pragma unroll
-  for (int k = 0; k < K; ++k)
-    if (K * T == n || tid + k * T < n) buf[tid + k * T] = v[k];
-}
-
-template <int M, int T>
-__device__ __forceinline__ void store_quarter_row(const float2 *buf, float2 *Sc, int H, int y,
-                                                  int tid) {
-  constexpr int n = 4 * M, K = (n + T - 1) / T;
-  float2 v[K];
-#pragma unroll
-  for (int k = 0; k < K; ++k) v[k] = buf[min(tid + k * T, n - 1)];
-#pragma unroll
-  for (int k = 0; k < K; ++k) {
-    const int x = tid + k * T;
-    if (K * T == n || x < n) at32(Sc, ((x >> 3) * H + y) * 8 + (x & 7)) = v[k];
-  }
-}
-
-// the four chain inputs at m = n from the samples a = x[n], b = x[n + M]
-__device__ __forceinline__ void quarter_inputs(float2 *buf, int n, float2 a, float2 b,
-                                               float2 w1) {
-  const float2 w2 = cmul(w1, w1), w3 = cmul(w2, w1);
-  buf[4 * n] = cadd(a, b);
-  buf[4 * n + 1] = cmul(make_float2(a.x + b.y, a.y - b.x), w1);  // (a - i b) w^n
-  buf[4 * n + 2] = cmul(csub(a, b), w2);                         // (a - b) w^{2n}
-  buf[4 * n + 3] = cmul(make_float2(a.x - b.y, a.y + b.x), w3);  // (a + i b) w^{3n}
-}
-
-// u[n] and u[n + M] from the four chain outputs at m = n
-__device__ __forceinline__ void quarter_outputs(const float2 *buf, int n, float2 w1, float2 &u0,
-                                                float2 &u1) {
-  const float2 w2 = cmul(w1, w1), w3 = cmul(w2, w1);
-  const float2 z0 = buf[4 * n];
-  const float2 z1 = cmul(cconj(w1), buf[4 * n + 1]);
-  const float2 z2 = cmul(cconj(w2), buf[4 * n + 2]);
-  const float2 z3 = cmul(cconj(w3), buf[4 * n + 3]);
-  u0 = cadd(cadd(z0, z1), cadd(z2, z3));
-  const float2 e = csub(z0, z2), o = csub(z1, z3);
-  u1 = make_float2(e.x - o.y, e.y + o.x);  // z0 + i z1 - z2 - i z3
-}
-
-template <int M>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k_row_fwd_q(
-    const float2 *__restrict__ field, int H, int W, int rows, const float2 *__restrict__ twf_x,
-    float2 *__restrict__ S) {
-  constexpr int T = 512, K = (M + T - 1) / T, Wt = M / 2;
-  __shared__ float2 buf[4 * M];
-  __shared__ float2 tw[M];
-  const int tid = threadIdx.x;
-  const int R = quarter_row(blockIdx.x, rows), c = R / H, y = R - c * H;
-  load_quarter_table<M, T>(tw, twf_x, tid);
-  {
-    const float2 *f = field + ((size_t)c * H + y) * W;
-    float2 av[K], bv[K], wv[K];
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-      const int n = min(tid + k * T, M - 1);
-      av[k] = at32(f, min(n, W - 1));
-      bv[k] = at32(f, min(n + M, W - 1));
-      wv[k] = at32(twf_x, n);
-    }
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-      const int n = tid + k * T;
-      if (K * T == M || n < M) {
-        const float2 a = n < W ? av[k] : make_float2(0.f, 0.f);
-        const float2 b = n + M < W ? bv[k] : make_float2(0.f, 0.f);
-        quarter_inputs(buf, n, a, b, wv[k]);
-      }
-    }
-  }
-  __syncthreads();
-  cfft<-1, 4, T, M>(buf, tw, tid);
-  store_quarter_row<M, T>(buf, S + (size_t)c * Wt * H * 8, H, y, tid);
-}
-
-template <int M>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k_row_inv_q(
-    const float2 *__restrict__ S, int H, int W, int rows, const float2 *__restrict__ twf_x,
-    float2 *__restrict__ out) {
-  constexpr int T = 512, K = (M + T - 1) / T, Wt = M / 2;
-  __shared__ float2 buf[4 * M];
-  __shared__ float2 tw[M];
-  const int tid = threadIdx.x;
-  const int R = quarter_row(blockIdx.x, rows), c = R / H, y = R - c * H;
-  load_quarter_table<M, T>(tw, twf_x, tid);
-  load_quarter_row<M, T>(buf, S + (size_t)c * Wt * H * 8, H, y, tid);
-  float2 wv[K];
-#pragma unroll
-  for (int k = 0; k < K; ++k) wv[k] = at32(twf_x, min(tid + k * T, M - 1));
-  lds_sync();
-  cfft<+1, 4, T, M>(buf, tw, tid);
-  float2 *o = out + ((size_t)c * H + y) * W;
-#pragma unroll
-  for (int k = 0; k < K; ++k) {
-    const int n = tid + k * T;
-    if ((K * T == M || n < M) && n < W) {
-      float2 u0, u1;
-      quarter_outputs(buf, n, wv[k], u0, u1);
-      o[n] = u0;
-      if (n + M < W) o[n + M] = u1;
-    }
-  }
-}
-
-template <int M>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k_row_loss_q(
-    float2 *__restrict__ S, int H, int W, int rows, const float2 *__restrict__ twf_x,
-    const float *__restrict__ target, const float *__restrict__ grad_I,
-    const float *__restrict__ mask, int mcg, float *__restrict__ intensity, float2 *__restrict__ u_out,
-    double *__restrict__ loss_part, float gscale, int make_grad) {
-  constexpr int T = 512, K = (M + T - 1) / T, Wt = M / 2;
-  __shared__ float2 buf[4 * M];
-  __shared__ float2 tw[M];
-  __shared__ double red[T / 64];
-  const int tid = threadIdx.x;
-  const int R = quarter_row(blockIdx.x, rows), c = R / H, y = R - c * H;
-  float2 *Sc = S + (size_t)c * Wt * H * 8;
-  load_quarter_table<M, T>(tw, twf_x, tid);
-  load_quarter_row<M, T>(buf, Sc, H, y, tid);
-  if (mask) mask += (size_t)(c / mcg) * H * W;
-  // per-element inputs at n and n + M, fetched before the transform so that
-  // their latency overlaps it
-  const float *tsrc = target ? target : grad_I;
-  const size_t row = ((size_t)c * H + y) * W;
-  float tv0[K], tv1[K], mv0[K], mv1[K];
-#pragma unroll
-  for (int k = 0; k < K; ++k) {
-    const int n = min(tid + k * T, M - 1);
-    const int n0 = min(n, W - 1), n1 = min(n + M, W - 1);
-    tv0[k] = tsrc ? tsrc[row + n0] : 0.f;
-    tv1[k] = tsrc ? tsrc[row + n1] : 0.f;
-    mv0[k] = mask ? mask[(size_t)y * W + n0] : 0.f;
-    mv1[k] = mask ? mask[(size_t)y * W + n1] : 0.f;
-  }
-  lds_sync();
-  cfft<+1, 4, T, M>(buf, tw, tid);
-  double acc = 0.0;
-#pragma unroll
-  for (int k = 0; k < K; ++k) {
-    const int n = tid + k * T;
-    if (K * T == M || n < M) {
-      const float2 w1 = at32(twf_x, n);
-      float2 u[2];
-      quarter_outputs(buf, n, w1, u[0], u[1]);
-      float f[2] = {0.f, 0.f};
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int x = n + j * M;
-        if (x >= W) continue;
-        const float t = j ? tv1[k] : tv0[k], m = j ? mv1[k] : mv0[k];
-        const float I = u[j].x * u[j].x + u[j].y * u[j].y;
-        if (intensity) intensity[row + x] = I;
-        if (u_out) u_out[row + x] = u[j];
-        if (target) {
-          // L_recon weight 1 + m^2 + t^2 (plain MSE without a mask)
-          const float d = I - t, w = mask ? 1.f + m * m + t * t : 1.f;
-          acc += (double)d * (double)d * (double)w;
-          f[j] = gscale * d * w;  // 4 w (I - T) / M
-        } else if (grad_I) {
-          f[j] = 2.0f * t;
-        }
-      }
-      if (make_grad)
-        quarter_inputs(buf, n, make_float2(f[0] * u[0].x, f[0] * u[0].y),
-                       make_float2(f[1] * u[1].x, f[1] * u[1].y), w1);
-    }
-  }
-  if (target) {
-    for (int d = 32; d > 0; d >>= 1) acc += __shfl_down(acc, d, 64);
-    if ((tid & 63) == 0) red[tid >> 6] = acc;
-    __syncthreads();
-    if (tid == 0) {
-      double sum = 0.0;
-      for (int w = 0; w < T / 64; ++w) sum += red[w];
-      loss_part[R] = sum;
-    }
-  }
-  if (make_grad) {
-    __syncthreads();
-    cfft<-1, 4, T, M>(buf, tw, tid);
-    store_quarter_row<M, T>(buf, Sc, H, y, tid);
-  }
-}
-
-// rows per row-pass workgroup (specialised lengths use 4, the runtime path 2)
-static bool row_specialised(int Wp) { return Wp == 3840 || Wp == 512; }
-// the half-length row passes take Wp = 3840 (1080p) and 7680 (4K) with W <= Wp / 2
-// the quarter-length row passes take Wp = 4 M with W <= Wp / 2, one row per workgroup,
-// for the chain lengths they are built for (4K: 1920; 1080p: 960; 1024 .. 4096 pads:
-// 256, 512, 1024);
-// quarter_m returns M, or 0 where they do not apply
-static int quarter_m(const Ctx &c) {
-  if (c.Wp % 4 != 0 || 2 * c.W > c.Wp) return 0;
-  const int M = c.Wp / 4;
-  return (M == 1920 || M == 1024 || M == 960 || M == 512 || M == 256) ? M : 0;
-}
-static bool row_quarter(const Ctx &c) { return quarter_m(c) != 0; }
-// calls f(std::integral_constant<int, M>) for the quarter length of c
-template <class F>
-static void with_quarter(const Ctx &c, F &&f) {
-  switch (quarter_m(c)) {
-    case 1920: f(std::integral_constant<int, 1920>{}); break;
-    case 1024: f(std::integral_constant<int, 1024>{}); break;
-    case 960: f(std::integral_constant<int, 960>{}); break;
-    case 512: f(std::integral_constant<int, 512>{}); break;
-    default: f(std::integral_constant<int, 256>{}); break;
-  }
-}
+// rows per row-pass workgroup
 int row_group_rows(const Ctx &c) {
-  return c.Wp == 512 ? 4 : (row_quarter(c) ? 1 : 2);
+  return c.row_p ? 1 : c.Wp == 512 ? 4 : 2;
 }
 static int row_blocks(const Ctx &c) {
   const int r = row_group_rows(c);
@@ -893,13 +653,38 @@ static int row_blocks(const Ctx &c) {
 }
 static size_t row_lds(const Ctx &c) { return (size_t)2 * c.Wp * sizeof(float2); }
 
+static RowArgs row_args(const Ctx &c, int pass) {
+  RowArgs a{};
+  a.pass = pass;
+  a.H = c.H;
+  a.W = c.W;
+  a.rows = row_blocks(c);
+  a.twf_x = c.twf_x;
+  return a;
+}
+
+// the chain kernels of c.row_p chains of Wp / c.row_p points (fft_chain.h)
+static hipError_t launch_row_chain(const Ctx &c, const RowArgs &a, hipStream_t s) {
+  const int P = c.row_p, M = c.Wp / P;
+  const bool found =
+      row_chain_part_0(M, P, a, s) || row_chain_part_1(M, P, a, s) ||
+      row_chain_part_2(M, P, a, s) || row_chain_part_3(M, P, a, s) ||
+      row_chain_part_4(M, P, a, s) || row_chain_part_5(M, P, a, s) ||
+      row_chain_part_6(M, P, a, s) || row_chain_part_7(M, P, a, s);
+  return found ? hipGetLastError() : hipErrorInvalidValue;
+}
+
+int row_split(int Wp, int W) { return split_of(Wp, W, row_chain); }
+int col_split(int Hp, int H) { return split_of(Hp, H, col_chain); }
+
 hipError_t launch_row_fwd(const Ctx &c, const float2 *field, float2 *dst, hipStream_t s) {
-  if (row_quarter(c))
-    with_quarter(c, [&](auto mc) {
-      hipLaunchKernelGGL(k_row_fwd_q<decltype(mc)::value>, dim3(row_blocks(c)), dim3(512), 0, s,
-                         field, c.H, c.W, row_blocks(c), c.twf_x, dst);
-    });
-  else if (c.Wp == 3840)
+  if (c.row_p) {
+    RowArgs a = row_args(c, 0);
+    a.field = field;
+    a.S = dst;
+    return launch_row_chain(c, a, s);
+  }
+  if (c.Wp == 3840)
     hipLaunchKernelGGL((k_row_fwd_c<3840, 2, 512, false>), dim3(row_blocks(c)), dim3(512), 0, s,
                        field, c.H, c.W, c.Wt, c.twf_x, c.tw_x, dst);
   else if (c.Wp == 512)
@@ -915,12 +700,13 @@ hipError_t launch_row_fwd(const Ctx &c, const float2 *field, float2 *dst, hipStr
 }
 
 hipError_t launch_row_inv(const Ctx &c, const float2 *src, float2 *out, hipStream_t s) {
-  if (row_quarter(c))
-    with_quarter(c, [&](auto mc) {
-      hipLaunchKernelGGL(k_row_inv_q<decltype(mc)::value>, dim3(row_blocks(c)), dim3(512), 0, s,
-                         src, c.H, c.W, row_blocks(c), c.twf_x, out);
-    });
-  else if (c.Wp == 3840)
+  if (c.row_p) {
+    RowArgs a = row_args(c, 1);
+    a.S = const_cast<float2 *>(src);  // only read by this pass
+    a.out = out;
+    return launch_row_chain(c, a, s);
+  }
+  if (c.Wp == 3840)
     hipLaunchKernelGGL((k_row_inv_c<3840, 2, 512, false>), dim3(row_blocks(c)), dim3(512), 0, s,
                        src, c.H, c.W, c.Wt, c.twf_x, c.tw_x, out);
   else if (c.Wp == 512)
@@ -951,13 +737,21 @@ hipError_t launch_row_loss(const Ctx &c, int plane, float2 *buf, const float *ta
   if (mask) mask += (size_t)plane * c.B * c.H * c.W;
   const int mcg = c.C;
   double *lp = c.loss_part + (size_t)plane * row_blocks(c);
-  if (row_quarter(c))
-    with_quarter(c, [&](auto mc) {
-      hipLaunchKernelGGL(k_row_loss_q<decltype(mc)::value>, dim3(row_blocks(c)), dim3(512), 0, s,
-                         buf, c.H, c.W, row_blocks(c), c.twf_x, target, grad_intensity, mask, mcg,
-                         intensity, u_out, lp, gscale, make_grad);
-    });
-  else if (c.Wp == 3840)
+  if (c.row_p) {
+    RowArgs a = row_args(c, 2);
+    a.S = buf;
+    a.target = target;
+    a.grad_I = grad_intensity;
+    a.mask = mask;
+    a.mcg = mcg;
+    a.intensity = intensity;
+    a.u_out = u_out;
+    a.loss_part = lp;
+    a.gscale = gscale;
+    a.make_grad = make_grad;
+    return launch_row_chain(c, a, s);
+  }
+  if (c.Wp == 3840)
     hipLaunchKernelGGL((k_row_loss_c<3840, 2, 512, false>), dim3(row_blocks(c)), dim3(512), 0, s,
                        buf, c.H, c.W, c.Wt, c.twf_x, c.tw_x, target, grad_intensity, mask, mcg, intensity,
                        u_out, lp, gscale, make_grad);
@@ -980,18 +774,6 @@ hipError_t launch_row_loss(const Ctx &c, int plane, float2 *buf, const float *ta
 // Column passes over one 8-column tile of one channel (a contiguous block of
 // H x 8 complex in S), in place.
 // ----------------------------------------------------------------------------
-// Source, destination and transfer table of one column pass.  src and dst
-// may be the same buffer (in place).  acc: add the result to dst instead of
-// overwriting it (the adjoint's sum over planes).  htab points at the table
-// of the pass's plane for channel 0; channel ch is at htab + ch * hstride.
-struct ColIO {
-  const float2 *src;
-  float2 *dst;
-  const float2 *htab;
-  size_t hstride;
-  int acc;
-};
-
 __device__ __forceinline__ void col_store(const ColIO &io, size_t i, float2 v) {
   io.dst[i] = io.acc ? cadd(io.dst[i], v) : v;
 }
@@ -1216,186 +998,30 @@ __global__ __launch_bounds__(T) void k_col_half_c(ColIO io, int H, int Wp, int W
   }
 }
 
-// ----------------------------------------------------------------------------
-// Column pass for Hp = 4 M with H <= 2 M, one wave per chain, M = R0 R1 R2
-// (1080 = 9 6 20 at 4K, 540 = 12 5 9 at 1080p); CONJ: multiply by conj(H)
-// (the adjoint pass).
-// Output bin 4 m + p of the padded column is bin m of the M-point transform
-// of w^{p n} (x[n] + (-i)^p x[n + M]) (n < M; w = e^{-2 pi i / Hp}), so a
-// column is four M-point chains; the inverse gives u[n + M j] = sum_p
-// w^{-p n} i^{p j} z_p[n] for j = 0, 1.  A workgroup takes two columns of a
-// quarter tile; wave 4 c + p runs chain p of column c in its own M-element
-// LDS buffer, so the stages of a chain need no workgroup barrier: only
-// loading the columns and combining the chains are workgroup steps.  The
-// forward plan is R0, R1, R2; its last stage leaves lane j < M / R2 holding
-// spectrum entries j + (M / R2) q (q < R2), exactly the input of a first
-// inverse stage of radix R2, so the transfer multiply and that stage run in
-// registers; the inverse plan is R2, R1, R0.  The transfer table is read
-// column-major ([Wq][Hq]); the eight quarter tiles of a mirror pair of tiles
-// (t, Wt - 1 - t), whose columns need the same table columns, are blocks
-// b + 8 s (s < 8), which share an XCD.
-// ----------------------------------------------------------------------------
-template <int R0, int R1, int R2, bool CONJ>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k_col_wave4(
-    ColIO io, const float2 *__restrict__ htab_t, int Hq, int H, int Wp, int Wt, int C,
-    const float2 *__restrict__ twf_y) {
-  constexpr int M = R0 * R1 * R2;
-  constexpr int NB2 = M / R2;
-  static_assert(NB2 <= 64, "the fused stage takes one butterfly per lane");
-  constexpr int T = 512, NI = 2 * M, K = (NI + T - 1) / T, KT = (M + T - 1) / T;
-  __shared__ float2 buf[8 * M];
-  __shared__ float2 tw[M];
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: scalar addressing
-  const int b = blockIdx.x;
-  const int slot = (b >> 3) & 7, pi = (b >> 6) * 8 + (b & 7);
-  const int hp = (Wt + 1) >> 1;
-  if (pi >= C * hp) return;
-  const int ch = pi / hp, pp = pi - ch * hp;
-  const int t = slot < 4 ? pp : Wt - 1 - pp;
-  if (slot >= 4 && t == pp) return;  // the middle tile of an odd count has no mirror
-  const int part = slot & 3;
-  const size_t off = ((size_t)ch * Wt + t) * H * 8 + part * 2;
-  const float2 *src = io.src + off;
-  float2 *dst = io.dst + off;
-  {
-    // item i: row n = i / 2 of column c = i % 2; every global load of this
-    // phase is issued before the first LDS store
-    float2 av[K], bv[K], w1[K], tv[KT];
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-      const int i = tid + k * T, n = min(i >> 1, M - 1), c = i & 1;
-      av[k] = at32(src, min(n, H - 1) * 8 + c);
-      bv[k] = at32(src, min(n + M, H - 1) * 8 + c);
-      w1[k] = at32(twf_y, n);
-    }
-#pragma unroll
-    for (int k = 0; k < KT; ++k) tv[k] = at32(twf_y, 4 * M + min(tid + k * T, M - 1));  // w_M^k
-#pragma unroll
-    for (int k = 0; k < KT; ++k)
-      if (tid + k * T < M) tw[tid + k * T] = tv[k];
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-      const int i = tid + k * T, n = i >> 1, c = i & 1;
-      if (K * T == NI || i < NI) {
-        const float2 a = n < H ? av[k] : make_float2(0.f, 0.f);
-        const float2 bb = n + M < H ? bv[k] : make_float2(0.f, 0.f);
-        const float2 s0 = cadd(a, bb), s2 = csub(a, bb);
-        const float2 s1 = make_float2(a.x + bb.y, a.y - bb.x);  // a - i b
-        const float2 s3 = make_float2(a.x - bb.y, a.y + bb.x);  // a + i b
-        const float2 w2 = cmul(w1[k], w1[k]), w3 = cmul(w2, w1[k]);  // w^{2n}, w^{3n}
-        buf[(4 * c) * M + n] = s0;
-        buf[(4 * c + 1) * M + n] = cmul(s1, w1[k]);
-        buf[(4 * c + 2) * M + n] = cmul(s2, w2);
-        buf[(4 * c + 3) * M + n] = cmul(s3, w3);
-      }
-    }
-  }
-  __syncthreads();
-  {
-    const int c = wave >> 2, p = wave & 3;
-    float2 *wb = buf + wave * M;
-    const int kx = t * 8 + part * 2 + c;
-    const int qx = min(kx, Wp - kx);
-    const float2 *hcol = htab_t + (size_t)ch * io.hstride + (size_t)qx * Hq;
-    // transfer values for ky = 4 (j + NB2 q) + p, issued before the forward stages
-    float2 hv[R2];
-    {
-      const int j = min(lane, NB2 - 1);
-      static_for<0, R2>([&](auto qc) {
-        constexpr int q = decltype(qc)::value;
-        const int ky = 4 * (j + NB2 * q) + p;
-        hv[q] = at32(hcol, min(ky, 4 * M - ky));
-      });
-    }
-    wstage<R0, -1, M, 1>(wb, tw, lane);
-    wstage<R1, -1, M, R0>(wb, tw, lane);
-    float2 v[R2];
-    if (lane < NB2) {
-      static_for<0, R2>([&](auto qc) {
-        constexpr int q = decltype(qc)::value;
-        v[q] = wb[lane + q * NB2];
-      });
-      static_for<1, R2>([&](auto qc) {
-        constexpr int q = decltype(qc)::value;
-        v[q] = cmul(v[q], tw[q * lane]);  // last forward stage: Ns = NB2, unit twiddle step
-      });
-      RFft<R2, -1>::run(v);
-      static_for<0, R2>([&](auto qc) {
-        constexpr int q = decltype(qc)::value;
-        v[q] = cmul(v[q], CONJ ? cconj(hv[q]) : hv[q]);  // the table carries 1 / (Hp Wp)
-      });
-      RFft<R2, +1>::run(v);  // first inverse stage: Ns = 1, no twiddles
-    }
-    wave_lds_order();
-    if (lane < NB2) {
-      static_for<0, R2>([&](auto qc) {
-        constexpr int q = decltype(qc)::value;
-        wb[lane * R2 + q] = v[q];
-      });
-    }
-    wave_lds_order();
-    wstage<R1, +1, M, R2>(wb, tw, lane);
-    wstage<R0, +1, M, R2 * R1>(wb, tw, lane);
-  }
-  {
-    float2 w1[K];
-#pragma unroll
-    for (int k = 0; k < K; ++k) w1[k] = at32(twf_y, min((tid + k * T) >> 1, M - 1));
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-      const int i = tid + k * T, n = i >> 1, c = i & 1;
-      if ((K * T == NI || i < NI) && n < H) {
-        const float2 w2 = cmul(w1[k], w1[k]), w3 = cmul(w2, w1[k]);
-        const float2 z0 = buf[(4 * c) * M + n];
-        const float2 z1 = cmul(cconj(w1[k]), buf[(4 * c + 1) * M + n]);
-        const float2 z2 = cmul(cconj(w2), buf[(4 * c + 2) * M + n]);
-        const float2 z3 = cmul(cconj(w3), buf[(4 * c + 3) * M + n]);
-        const float2 y0 = cadd(cadd(z0, z1), cadd(z2, z3));
-        float2 &d0 = at32(dst, n * 8 + c);
-        d0 = io.acc ? cadd(d0, y0) : y0;
-        if (n + M < H) {
-          // z0 + i z1 - z2 - i z3
-          const float2 e = csub(z0, z2), o = csub(z1, z3);
-          const float2 y1 = make_float2(e.x - o.y, e.y + o.x);
-          float2 &d1 = at32(dst, (n + M) * 8 + c);
-          d1 = io.acc ? cadd(d1, y1) : y1;
-        }
-      }
-    }
-  }
-}
-
 hipError_t launch_col_pass(const Ctx &c, int conj_h, int plane, const float2 *src, float2 *dst,
                            int acc, hipStream_t s) {
   const float scale = (float)(1.0 / ((double)c.Hp * (double)c.Wp));
   const size_t tab = (size_t)c.Hq * c.Wq;
   const ColIO io{src, dst, c.htab + (size_t)plane * tab, (size_t)c.L * tab, acc};
   dim3 grid(c.Wt, c.CF);
-  if (col_wave4(c)) {
-    const int pairs = c.CF * ((c.Wt + 1) / 2);
-    const float2 *ht = c.htab_t + (size_t)plane * tab;
-    const dim3 grid4((pairs + 7) / 8 * 64);
-    // M = R0 R1 R2 with M / R2 <= 64 (one fused butterfly per lane)
-    auto go = [&](auto r0, auto r1, auto r2) {
-      constexpr int R0 = decltype(r0)::value, R1 = decltype(r1)::value, R2 = decltype(r2)::value;
-      if (conj_h)
-        hipLaunchKernelGGL((k_col_wave4<R0, R1, R2, true>), grid4, dim3(512), 0, s, io, ht, c.Hq,
-                           c.H, c.Wp, c.Wt, c.CF, c.twf_y);
-      else
-        hipLaunchKernelGGL((k_col_wave4<R0, R1, R2, false>), grid4, dim3(512), 0, s, io, ht,
-                           c.Hq, c.H, c.Wp, c.Wt, c.CF, c.twf_y);
-    };
-    using std::integral_constant;
-    switch (col_wave4_m(c)) {
-      case 1080: go(integral_constant<int, 9>{}, integral_constant<int, 6>{}, integral_constant<int, 20>{}); break;
-      case 1024: go(integral_constant<int, 8>{}, integral_constant<int, 8>{}, integral_constant<int, 16>{}); break;
-      case 540: go(integral_constant<int, 12>{}, integral_constant<int, 5>{}, integral_constant<int, 9>{}); break;
-      case 512: go(integral_constant<int, 8>{}, integral_constant<int, 8>{}, integral_constant<int, 8>{}); break;
-      case 384: go(integral_constant<int, 6>{}, integral_constant<int, 8>{}, integral_constant<int, 8>{}); break;
-      default: go(integral_constant<int, 4>{}, integral_constant<int, 8>{}, integral_constant<int, 8>{}); break;
-    }
+  if (c.col_p) {
+    const int P = c.col_p, M = c.Hp / P;
+    ColArgs a{};
+    a.io = io;
+    a.io.htab = c.htab_t + (size_t)plane * tab;
+    a.conj_h = conj_h;
+    a.Hq = c.Hq;
+    a.H = c.H;
+    a.Wp = c.Wp;
+    a.Wt = c.Wt;
+    a.C = c.CF;
+    a.twf_y = c.twf_y;
+    const bool found =
+        col_chain_part_0(M, P, a, s) || col_chain_part_1(M, P, a, s) ||
+        col_chain_part_2(M, P, a, s) || col_chain_part_3(M, P, a, s) ||
+        col_chain_part_4(M, P, a, s) || col_chain_part_5(M, P, a, s) ||
+        col_chain_part_6(M, P, a, s) || col_chain_part_7(M, P, a, s);
+    if (!found) return hipErrorInvalidValue;
   } else if (c.Hp == 2160) {
     hipLaunchKernelGGL((k_col_half_c<1080, 1024>), grid, dim3(1024), 0, s, io, c.H, c.Wp, c.Wt,
                        c.twf_m, c.tw_y, c.Wq, conj_h, scale);

@@ -305,31 +305,13 @@ constexpr int pick_radix(int n) {
   return n;
 }
 
-// Measured plans that replace the greedy one for some lengths (n = 0: none).
-// With four chains over 512 threads a stage of radix R has 4 N / R
-// butterflies, one or more per thread.  For 960 the greedy 15 16 4 has a
-// radix-16 stage with 240 butterflies (half the threads idle) and two
-// radix-4 passes; 15 8 8 (256, 480, 480 butterflies) shortens the chain each
-// thread runs between barriers (row passes 36.7 -> 35.6 us, loss row pass
-// 65.3 -> 61.8 us at 1080p; 12 8 10, 8 12 10 and 10 12 8 were in between).
+// Measured plans that replace the greedy one for some lengths (n = 0: none):
+// greedy 16 16 2 and 16 16 leave 3/4 to 7/8 of the threads idle in their
+// radix-16 stages.
 template <int N>
 struct CPlanFixed {
   static constexpr int n = 0;
   static constexpr int r[1] = {1};
-};
-template <>
-struct CPlanFixed<960> {
-  static constexpr int n = 3;
-  static constexpr int r[3] = {15, 8, 8};
-};
-// The serving pads' quarter rows (1024, 512, 256) likewise: greedy 16 16 4,
-// 16 16 2 and 16 16 leave 3/4 to 7/8 of the threads idle in their radix-16
-// stages; 8 8 16, 8 8 8 and 4 8 8 cut the batched solves of the 512^2,
-// 768x1024 and 1024^2 classes by 8, 7 and 3 %.
-template <>
-struct CPlanFixed<1024> {
-  static constexpr int n = 3;
-  static constexpr int r[3] = {8, 8, 16};
 };
 template <>
 struct CPlanFixed<512> {

@@ -1,0 +1,102 @@
+"""The chain FFT passes at the lengths where they can go wrong, against the FP64
+oracle: the smallest and longest chains of each split, chains that leave lanes
+idle or need several butterflies per lane, canvases smaller than half the
+padded grid, and grids whose last column tile is partly empty.
+
+Tolerance.  A propagation is four transforms of at most 13 radix-2 levels; each
+level rounds its values about three times to a relative 2^-24 (the rms of a
+rounding is 0.3 of that), the errors are independent, and twiddles and transfer
+values carry one rounding each: sqrt(4 (13 * 3 + 2)) * 0.3 * 2^-24 = 2.3e-7
+relative L2.  The bar is four times that, 1e-6; for gradients, which add the
+loss's own arithmetic on two propagations, 4e-6."""
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2511_15022_amd import binding
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-6
+GRAD_TOL = 4e-6
+
+
+def say(*a):
+    print("[gpu-case]", *a, flush=True)
+    sys.stdout.flush()
+
+
+def rel(a, b):
+    return float(np.linalg.norm((np.asarray(a) - b).ravel()) / np.linalg.norm(np.asarray(b).ravel()))
+
+
+CASES = [
+    # (H, W, Hp, Wp, C): chains of four, 16 x 16 (the shortest) and with idle samples
+    (32, 32, 64, 64, 1),
+    (21, 19, 64, 72, 2),
+    # chains of two (padded lengths 2 M, M odd), partly empty last tile
+    (25, 27, 50, 54, 1),
+    (220, 131, 450, 270, 1),
+    # several butterflies per lane, odd canvases
+    (333, 517, 720, 1080, 1),
+    (128, 128, 256, 512, 1),
+    # one stage of radix 25 or 27 in the fused butterfly; the longest columns
+    (600, 9, 1250, 64, 2),
+    (1215, 11, 2430, 64, 1),
+    (2400, 8, 4800, 64, 1),
+    # the longest rows of each split
+    (7, 4096, 64, 8192, 1),
+    (5, 3645, 64, 7290, 1),
+    (6, 3000, 64, 6250, 1),
+    # two planes: the adjoint column pass adds into its destination
+    (45, 80, 90, 160, 3),
+]
+
+
+@pytest.mark.parametrize("H,W,Hp,Wp,C", CASES)
+def test_chain_passes_match_oracle(O, H, W, Hp, Wp, C):
+    zs = [2e-3, -1e-3] if C == 3 else [2e-3]
+    L = len(zs)
+    lambdas = [639e-9, 515e-9, 473e-9][:C]
+    say("chain", H, W, Hp, Wp, C, L)
+    opt = O.Optics(H, W, C, Hp, Wp, 8e-6, lambdas, zs)
+    ctx = binding.Context(H, W, C, 8e-6, lambdas, zs, pad=(Hp, Wp), max_gaussians=1)
+    rng = np.random.default_rng(5)
+    f = (rng.standard_normal((C, H, W)) + 1j * rng.standard_normal((C, H, W))).astype(np.complex64)
+    F = torch.from_numpy(f).cuda()
+    I, u = ctx.propagate(F, intensity=True, field_out=True)
+    ref = O.propagate(f.astype(np.complex128), opt)
+    assert rel(u.cpu().numpy(), ref) <= TOL
+    assert rel(I.cpu().numpy(), np.abs(ref) ** 2) <= TOL
+    gu = (rng.standard_normal((L, C, H, W)) + 1j * rng.standard_normal((L, C, H, W))).astype(
+        np.complex64)
+    g = ctx.propagate_field_adjoint(torch.from_numpy(gu).cuda())
+    assert rel(g.cpu().numpy(), O.propagate_adjoint(gu.astype(np.complex128), opt)) <= TOL
+    # the middle pass with the loss weights and its partial sums
+    T = rng.random((L, C, H, W)).astype(np.float32)
+    mask = (rng.random((L, H, W)) < 0.5).astype(np.float32)
+    P = torch.zeros(6 + 2 * C, device="cuda")
+    ctx.rasterize(P, 1)
+    loss = torch.zeros(2, dtype=torch.float64, device="cuda")
+    gf = torch.empty_like(F)
+    ctx.backward(P, 1, F, torch.from_numpy(T).cuda(), loss=loss, grad_field=gf,
+                 mask=torch.from_numpy(mask).cuda())
+    w = 1.0 + mask[:, None].astype(np.float64) ** 2 + T.astype(np.float64) ** 2
+    d = np.abs(ref) ** 2 - T
+    assert abs(loss[0].item() - np.mean(w * d * d)) <= GRAD_TOL * np.mean(w * d * d)
+    seed = 4.0 * w * d * ref / d.size
+    assert rel(gf.cpu().numpy(), O.propagate_adjoint(seed, opt)) <= GRAD_TOL
+
+
+def test_transfer_table_follows_the_optics():
+    """get_transfer of a chain context is the table of a context made with the
+    same optics, after set_optics too (bitwise: the same kernel)."""
+    a = binding.Context(45, 80, 2, 8e-6, [639e-9, 515e-9], [2e-3], max_gaussians=1)
+    b = binding.Context(45, 80, 2, 8e-6, [473e-9, 639e-9], [-3e-3], max_gaussians=1)
+    say("transfer table")
+    assert not torch.equal(a.get_transfer(1, 0), b.get_transfer(1, 0))
+    a.set_optics([473e-9, 639e-9], [-3e-3])
+    for ch in range(2):
+        assert torch.equal(a.get_transfer(ch, 0), b.get_transfer(ch, 0))
