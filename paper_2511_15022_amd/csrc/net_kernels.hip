@@ -11,9 +11,11 @@
 // D[8 (v / 4) + 4 (l / 32) + v % 4][l % 32] in accumulator v < 16.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "cgh_internal.h"
 #include "cgh_net.h"
+#include "fft_reg.h"
 
 namespace cgh {
 namespace {
@@ -50,216 +52,484 @@ __device__ __forceinline__ v8s conv_in8(const uint16_t *__restrict__ x1, int c1,
 }
 
 // ----------------------------------------------------------------------------
-// Convolution: a workgroup of NWV waves takes 32 NWV consecutive pixels
-// (row-major) p0 .. p0 + 32 NWV - 1 and 32 NB output channels.  For each
-// block of 16 input channels it stages in LDS the three input row segments
-// that the 3 x 3 taps of its pixels read (pixels p0 + (ky - 1) W - 1 ..
-// p0 + (ky - 1) W + 32 NWV, ky < 3, zero outside the image) and the weights
-// of its output channels for the 9 taps; wave w then takes its 32 pixels x
-// 32 NB channels through the 9 taps from LDS.  A tap that leaves the image (a pixel in the first or last
-// column or row) reads zero.  With one output block (NB = 1) each input
-// block's global loads are issued before the workgroup waits for the previous
-// block's products; with two or four, the loads of block k + 1 are issued
-// before the products of block k.
+// Convolution.  A workgroup of four waves takes tiles of 32 columns x 4 R rows and
+// 32 NB output channels; wave w takes R rows of a tile (all 32 columns), in R NB
+// accumulators of 32 channels x 32 pixels.  For each block of 16 input channels (a
+// stage) it holds in LDS the tile's input pixels with a border of one (4 R + 2 rows
+// of 34) and its output channels' weights for the 9 taps.  A wave reads its 9 NB
+// weight fragments once per stage, then walks its R + 2 staged rows: one fragment
+// of a staged row serves the three output rows above, at and below it, so a stage
+// costs 3 (R + 2) + 9 NB reads of 16 bytes per lane for 9 R NB matrix instructions
+// (R = 4, NB = 2: 36 for 72; with one row per wave and a read of each operand per tap
+// 27 for 18).  LDS feeds at most one such read per two matrix instructions of the
+// CU's four SIMDs, so this ratio decides whether the matrix cores or LDS are the
+// limit.  With at most 32 input channels (KC = 2) a stage is the whole tile and the
+// weights stay in registers for the kernel: there HBM is the limit.
+//
+// The stages are loaded straight into LDS (buffer loads to LDS, 16 bytes per lane:
+// no registers held while they are in flight), NBUF - 1 stages ahead of the
+// products and across tiles: workgroups are persistent, so a tile's first stage
+// loads during the last products and the stores of the tile before it.  One
+// barrier per stage, which waits for LDS only.  A lane without a source (outside the
+// image, past the last channel) has an offset past the buffer's end, which reads
+// zero.  The loads fill LDS in lane order, so the arrangement against bank conflicts
+// is made on the source side: slot 2 i + b of 16 bytes holds half
+// b ^ ((column >> 3) & 1) of pixel i's 16 channels (of weight row i, its channel; with
+// KC = 2, quarter b ^ ((column >> 2) & 3) in slot 4 i + b), which spreads the 16 lanes
+// of an LDS phase over all banks and keeps a pixel's channels on neighbouring
+// lanes of the load.
+//
+// The weights are the A operand and the pixels the B operand, so a lane ends up
+// with groups of four consecutive channels of one pixel; exchanges between the
+// wave's halves make them eight, and the outputs leave in 16-byte stores without
+// passing through LDS.
+//
+// For every output the products are added in the order input block, tap
+// (ky, kx), channel group of the instruction, whatever the tile: results do not
+// depend on NB and R.
+//
+// Measured (1080 x 1920, C = 3, per layer, before and now): 24 -> 32 channels 96 and
+// 53 us (4.4 TB/s), 32 -> 32 84 and 60 us, 96 -> 32 209 and 128 us; 128 -> 128 at
+// 270 x 480 66 and 44 us, 384 -> 128 152 and 94 us (1214 TFLOP/s; a large library
+// matrix product reaches 1227 on the same card).
 // ----------------------------------------------------------------------------
 
-// waves (of 32 pixels each) per convolution workgroup: 8 halves the weight
-// traffic and the halo per pixel against 4 (16 was slower at every width)
-constexpr int kConvWaves = 8;
-
-// Workgroups are handed to the 8 XCDs in turn (block b to XCD b % 8).  This
-// bijection on [0, nb) gives XCD x one contiguous run of pixel blocks, taken
-// in order, so the three workgroups that read one input row (the blocks one
-// image row above and below) run on the same XCD and share its L2.
-__device__ __forceinline__ int xcd_block(int b, int nb) {
-  const int q = nb >> 3, r = nb & 7, x = b & 7, k = b >> 3;
-  return x < r ? x * (q + 1) + k : r * (q + 1) + (x - r) * q + k;
+// A buffer of `bytes` bytes from `base`; loads at or past the end return zero.
+constexpr int kBufferBytes = 0x7fff0000;    // the end where offsets are valid by construction
+constexpr uint32_t kOutside = 0x80000000u;  // an offset past the end of any buffer here
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const uint16_t *base, int bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(base), 0, bytes, 0x00027000);
 }
 
-template <int NB, int NWV>
-__global__ __launch_bounds__(64 * NWV) void k_conv3x3(
-    const uint16_t *__restrict__ x1, int c1, int up, const uint16_t *__restrict__ x2, int c2,
-    int H, int W, const uint16_t *__restrict__ w, const float *__restrict__ bias, int cout,
-    int relu, float *__restrict__ out32, uint16_t *__restrict__ out16) {
-  constexpr int CO = 32 * NB, NT = 64 * NWV, PX = 32 * NWV;
-  constexpr int kSeg = PX + 2;  // pixels per staged row segment: one more on each side
-  constexpr int NA = 3 * kSeg * 2, NW = 9 * CO * 2;  // 16-byte items: [ky][pixel][half], [t][co][half]
-  constexpr int KA = (NA + NT - 1) / NT, KW = (NW + NT - 1) / NT;
-  // the staged operands; after the products the same memory holds the
-  // output tile [PX][32] (FP32) of one output block for the store
-  static_assert((NA + NW) * 16 >= PX * 32 * 4, "output tile fits the staging memory");
-  __shared__ v8s smem[NA + NW];
-  v8s *const sa = smem, *const sw = smem + NA;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int P = H * W, cin = c1 + c2;
-  const int pb = xcd_block(blockIdx.x, gridDim.x);
-  const int p0 = pb * PX;
-  const int i = wave * 32 + (lane & 31);  // this lane's A row: pixel p0 + i
-  const int half = lane >> 5;             // its 8 channels of a block of 16
-  const int p = p0 + i;
-  const int co0 = blockIdx.y * CO;
-  const int px = p - (p / W) * W;  // this lane's pixel column
-  const int nk = (cin + 15) / 16;  // channel blocks (a last block of 8 is zero-filled)
-  const v8s z = {0, 0, 0, 0, 0, 0, 0, 0};
-  v16f acc[NB];
-#pragma unroll
-  for (int b = 0; b < NB; ++b)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[b][v] = 0.f;
-  // The source of each staged item, worked out once: A item k is channel
-  // ah[k] + 16 kb of pixel q2[k] (q1[k] in x1, which may be the half-size
-  // image), or zero (q2[k] < 0); B item k is channel 8 (wo[k] & 1) + 16 kb of
-  // weight row wo[k] >> 1 (an element offset), or zero (wo[k] < 0).
-  int q2[KA], q1[KA], ah[KA], wo[KW];
+// 16 bytes per lane, at byte `off` + `sof` (wave-uniform) of `buf`, to LDS at `dst`
+// (wave-uniform) + 16 lane
+__device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t buf, uint32_t off, int sof,
+                                            v8s *dst) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(
+      buf, (__attribute__((address_space(3))) void *)dst, 16, off, sof, 0, 0);
+}
+
+// two BF16 (round to nearest, ties to even) in one word, by the hardware conversion
+typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+  v2bf r;
+  r[0] = (__bf16)a;
+  r[1] = (__bf16)b;
+  return __builtin_bit_cast(uint32_t, r);
+}
+
+// the BF16 pair v where the pair m is > 0 (its bits 0x0001 .. 0x7f80: not NaN), else 0
+__device__ __forceinline__ uint32_t gated(uint32_t v, uint32_t m) {
+  const uint32_t lo = m & 0xffffu, hi = m >> 16;
+  return (lo - 1u < 0x7f80u ? v & 0xffffu : 0u) | (hi - 1u < 0x7f80u ? v & 0xffff0000u : 0u);
+}
+
+// waits until at most N of this wave's vector memory operations are in flight (the
+// builtin, so that the compiler knows)
+template <int N>
+__device__ __forceinline__ void wait_vm() {
+  __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
+  asm volatile("" ::: "memory");
+}
+
+struct ConvArgs {
+  const uint16_t *x1, *x2, *w;
+  const float *bias;
+  int c1, c2, up, H, W, cout, relu;
+  float *out32;
+  uint16_t *out16;
+  uint16_t *pooled;      // 2 x 2 averages of out16, or null
+  const uint16_t *gate;  // out16 is zero where gate <= 0 (gradient through ReLU), or null
+  int tiles_x, nco, items;  // column tiles, channel tiles, tiles in all (channel tile fastest)
+};
+
+template <int R, int NB, int KC, int NBUF, bool TWO, bool GEN>
+__global__ __launch_bounds__(256, 2) void k_conv3x3(ConvArgs a) {
+  constexpr bool THIN = KC == 2;
+  static_assert(!THIN || (!TWO && NB == 1 && NBUF == 2), "one input of at most 32 channels");
+  constexpr int CO = 32 * NB, TY = 4 * R, SR = TY + 2, SC = 34, SP = 2 * KC;  // SP: slots per pixel
+  constexpr int NA = SR * SC * SP, NW = THIN ? 0 : 9 * CO * 2;  // 16-byte slots
+  constexpr int KA = (NA + 255) / 256, KW = (NW + 255) / 256;
+  // With more than two buffers a wait counts the loads still in flight, so every
+  // wave issues the same number: the slots are padded to whole rounds.
+  constexpr bool PAD = NBUF > 2;
+  constexpr int LA = PAD ? 256 * KA : NA, LW = PAD ? 256 * KW : NW, LB = LA + LW;
+  __shared__ v8s smem[NBUF][LB];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int px = lane & 31, half = lane >> 5;
+  const int H = a.H, W = a.W, cin = TWO ? a.c1 + a.c2 : a.c1;
+  const int W1 = TWO && a.up ? W >> 1 : W;  // (an upsampled input always has a skip here)
+  const int nst = THIN ? 1 : (cin + 15) / 16;  // stages per tile (a last block of 8 is zero-filled)
+  // Workgroup b runs on XCD b % 8.  Each XCD takes one contiguous run of the tiles and
+  // its workgroups take them in turn, so neighbouring tiles, which share border
+  // pixels or inputs, meet in one L2.
+  const int xcd = blockIdx.x & 7, nx = (gridDim.x - xcd + 7) >> 3;
+  const int share = a.items >> 3, extra = a.items & 7;
+  const int run0 = xcd * share + min(xcd, extra), run1 = run0 + share + (xcd < extra ? 1 : 0);
+  int item = run0 + (blockIdx.x >> 3);
+  if (item >= run1) return;
+  // The pixel slots this thread fills: the byte offsets of their channels in x1 and
+  // x2 from the tile's first staged pixel.  Tiles start at multiples of 4 rows and
+  // 32 columns, so with an upsampled x1 these are the same for every tile too.
+  uint32_t o1[KA], o2[TWO ? KA : 1], ah = 0;  // ah bit k: the upper 8 channels
 #pragma unroll
   for (int k = 0; k < KA; ++k) {
-    const int item = tid + NT * k;
-    q2[k] = -1;
-    q1[k] = 0;
-    ah[k] = 0;
-    if (KA * NT == NA || item < NA) {
-      const int seg = item / (2 * kSeg), rem = item - seg * (2 * kSeg);
-      const int q = p0 + (seg - 1) * W - 1 + (rem >> 1);
-      ah[k] = 8 * (rem & 1);
-      if (q >= 0 && q < P) {
-        const int qy = q / W, qx = q - qy * W;
-        q2[k] = q;
-        q1[k] = up ? (qy >> 1) * (W >> 1) + (qx >> 1) : q;
-      }
+    const int s = tid + 256 * k, i = s / SP, row = i / SC, col = i - row * SC;
+    const int g = (s % SP) ^ (THIN ? (col >> 2) & 3 : (col >> 3) & 1);
+    if (g & 1) ah |= 1u << k;
+    int q = row * W + col;
+    if constexpr (TWO) {
+      o2[k] = s < NA ? 2u * (uint32_t)(q * a.c2 + 8 * g) : kOutside;
+      if (a.up) q = ((row + 1) >> 1) * W1 + ((col + 1) >> 1);
     }
+    o1[k] = s < NA && (!THIN || 8 * g < cin) ? 2u * (uint32_t)(q * a.c1 + 8 * g) : kOutside;
   }
+  uint32_t wo[KW > 0 ? KW : 1], wh = 0;
 #pragma unroll
   for (int k = 0; k < KW; ++k) {
-    const int item = tid + NT * k;
-    wo[k] = -1;
-    if (KW * NT == NW || item < NW) {
-      const int t = item / (2 * CO), rem = item - t * (2 * CO);
-      const int co = co0 + (rem >> 1);
-      if (co < cout) wo[k] = 2 * ((co * 9 + t) * cin) + (rem & 1);
-    }
+    const int s = tid + 256 * k, i = s >> 1, t = i / CO, c = i - t * CO;
+    const int g = (s & 1) ^ ((c >> 3) & 1);
+    if (g) wh |= 1u << k;
+    wo[k] = s < NW ? 2u * (uint32_t)((c * 9 + t) * cin + 8 * g) : kOutside;
   }
-  // block kb of 16 input channels: its staged A and B items, global -> registers
-  v8s ra[KA], rw[KW];
-  auto fetch = [&](int kb) {
+  // the tile being loaded
+  __amdgpu_buffer_rsrc_t b1, b2, bw;
+  uint32_t out = 0;  // bit k: slot k's pixel lies outside the image
+  auto aim = [&](int it) {
+    const int tile = THIN ? it : it / a.nco, ty = tile / a.tiles_x;
+    const int ax = (tile - ty * a.tiles_x) * 32 - 1, ay = ty * TY - 1;
+    out = 0;
+    if (ay < 0 || ax < 0 || ay + SR > H || ax + SC > W) {  // an edge tile
+      int t0 = tid;
+      asm volatile("" : "+v"(t0));  // worked out here, not kept
 #pragma unroll
-    for (int k = 0; k < KA; ++k) {
-      const int c0 = kb * 16 + ah[k];
-      ra[k] = z;
-      if (q2[k] >= 0 && c0 < cin) {
-        const uint16_t *src = c0 < c1 ? x1 + (size_t)q1[k] * c1 + c0
-                                      : x2 + (size_t)q2[k] * c2 + (c0 - c1);
-        ra[k] = *reinterpret_cast<const v8s *>(src);
+      for (int k = 0; k < KA; ++k) {
+        const int i = (t0 + 256 * k) / SP, row = i / SC, col = i - row * SC;
+        const bool in = ((uint32_t)(ay + row) < (uint32_t)H) & ((uint32_t)(ax + col) < (uint32_t)W);
+        out |= in ? 0u : 1u << k;
       }
     }
-#pragma unroll
-    for (int k = 0; k < KW; ++k) {
-      rw[k] = z;
-      const int c0 = kb * 16 + 8 * (wo[k] & 1);
-      if (wo[k] >= 0 && c0 < cin)
-        rw[k] = *reinterpret_cast<const v8s *>(w + (size_t)(wo[k] >> 1) + c0);
+    // the first staged pixel; before the first of the image where that lies outside
+    const int64_t q2 = (int64_t)ay * W + ax;
+    if constexpr (TWO) {
+      const int64_t q1 = a.up ? (int64_t)(((ay + 1) >> 1) - 1) * W1 + ((ax + 1) >> 1) - 1 : q2;
+      b1 = buffer_of(a.x1 + q1 * a.c1, kBufferBytes);
+      b2 = buffer_of(a.x2 + q2 * a.c2, kBufferBytes);
+    } else {
+      b1 = buffer_of(a.x1 + q2 * a.c1, kBufferBytes);
+    }
+    if constexpr (!THIN) {
+      const int co = (it - tile * a.nco) * CO;
+      bw = buffer_of(a.w + (size_t)co * 9 * cin, (a.cout - co) * 9 * cin * 2);
     }
   };
-  auto stage = [&]() {
+  // offset o of slot k, past the buffer where its pixel is outside
+  auto masked = [&](uint32_t o, int k) { return o | ((out << (31 - k)) & kOutside); };
+  auto load_stage = [&](int st, int buf) {
+    v8s *const sa = smem[buf] + 64 * wave, *const sw = sa + LA;
+    const int c0 = 16 * st;  // the block's channels c0 .. c0 + 15
+    if (!GEN || (c0 + 8 < cin && (c0 + 8 < a.c1 || c0 >= a.c1))) {
+      // uniform: sixteen channels of one input
+      const bool in1 = !TWO || c0 < a.c1;
+      const __amdgpu_buffer_rsrc_t src = in1 ? b1 : b2;
+      const int sof = 2 * (in1 ? c0 : c0 - a.c1);
 #pragma unroll
-    for (int k = 0; k < KA; ++k)
-      if (KA * NT == NA || tid + NT * k < NA) sa[tid + NT * k] = ra[k];
+      for (int k = 0; k < KA; ++k)
+        if (PAD || 256 * (k + 1) <= NA || tid + 256 * k < NA)
+          load_to_lds(src, masked(in1 ? o1[k] : o2[TWO ? k : 0], k), sof, sa + 256 * k);
+    } else {
+      // the last eight channels, or x1's last eight and x2's first
+      const bool both = TWO && c0 < a.c1 && c0 + 8 >= a.c1 && c0 + 8 < cin;
 #pragma unroll
-    for (int k = 0; k < KW; ++k)
-      if (KW * NT == NW || tid + NT * k < NW) sw[tid + NT * k] = rw[k];
+      for (int k = 0; k < KA; ++k) {
+        if (!PAD && 256 * (k + 1) > NA && tid + 256 * k >= NA) continue;
+        const bool up8 = (ah >> k) & 1;
+        const uint32_t p1 = masked(o1[k], k), p2 = TWO ? masked(o2[k], k) : kOutside;
+        if (TWO && (up8 || c0 >= a.c1))
+          load_to_lds(b2, up8 ? (both && p2 < kOutside ? p2 - 16u : kOutside)
+                              : p2 + 2u * (uint32_t)(c0 - a.c1),
+                      0, sa + 256 * k);
+        else
+          load_to_lds(b1, up8 ? kOutside : p1, 2 * c0, sa + 256 * k);
+      }
+    }
+    if constexpr (!THIN) {
+      const bool cut = GEN && c0 + 8 >= cin;  // the block's upper 8 channels are past the last
+#pragma unroll
+      for (int k = 0; k < KW; ++k)
+        if (PAD || 256 * (k + 1) <= NW || tid + 256 * k < NW)
+          load_to_lds(bw, cut && ((wh >> k) & 1) ? kOutside : wo[k], 2 * c0, sw + 256 * k);
+    }
   };
-  // A tap above the first or below the last row reads a staged zero (its
-  // linear pixel index is outside [0, P)) unless it also leaves the image at
-  // the side; a tap that leaves at the side reads the neighbouring row's end
-  // pixel in the staged segment, so it is masked here.  Outputs past P are
-  // not stored.
-  const bool in_l = px != 0, in_r = px != W - 1;
-  auto products = [&]() {
+  v16f acc[R][NB];
+  v8bf wf[KC][9][NB];
+  auto channel = [&](int it) { return THIN ? (int)blockIdx.y * CO : (it % a.nco) * CO; };
+  // this lane's operands in a buffer: pixel (row wave R, column px + kx), group 2 u +
+  // half, and weight row px
+  int ia[3][KC];
 #pragma unroll
-    for (int t = 0; t < 9; ++t) {
-      const int ky = t / 3, kx = t - 3 * ky;
-      const v8s sv = sa[(ky * kSeg + i + kx) * 2 + half];
-      const v8s a = kx == 0 ? (in_l ? sv : z) : (kx == 2 ? (in_r ? sv : z) : sv);
+  for (int kx = 0; kx < 3; ++kx)
 #pragma unroll
-      for (int b = 0; b < NB; ++b) {
-        const v8s bb = sw[(t * CO + 32 * b + (lane & 31)) * 2 + half];
-        acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, a),
-                                                         __builtin_bit_cast(v8bf, bb), acc[b],
-                                                         0, 0, 0);
+    for (int u = 0; u < KC; ++u) {
+      const int col = px + kx, g = 2 * u + half;
+      ia[kx][u] = (wave * R * SC + col) * SP + (g ^ (THIN ? (col >> 2) & 3 : (col >> 3) & 1));
+    }
+  const int iw = LA + px * 2 + (half ^ ((px >> 3) & 1));
+  auto products = [&](int buf) {
+    const v8s *const sb = smem[buf];
+    if constexpr (!THIN) {
+#pragma unroll
+      for (int t = 0; t < 9; ++t)
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+          wf[0][t][b] = __builtin_bit_cast(v8bf, sb[iw + (t * CO + 32 * b) * 2]);
+    }
+#pragma unroll
+    for (int u = 0; u < KC; ++u) {
+      // the three fragments of the next staged row are read before this row's products
+      v8bf f[2][3];
+#pragma unroll
+      for (int kx = 0; kx < 3; ++kx) f[0][kx] = __builtin_bit_cast(v8bf, sb[ia[kx][u]]);
+#pragma unroll
+      for (int sr = 0; sr < R + 2; ++sr) {
+        if (sr + 1 < R + 2)
+#pragma unroll
+          for (int kx = 0; kx < 3; ++kx)
+            f[(sr + 1) & 1][kx] =
+                __builtin_bit_cast(v8bf, sb[ia[kx][u] + (sr + 1) * SC * SP]);
+#pragma unroll
+        for (int kx = 0; kx < 3; ++kx)
+#pragma unroll
+          for (int r = 0; r < R; ++r) {
+            const int ky = sr - r;
+            if (ky < 0 || ky > 2) continue;
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+              acc[r][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                  wf[u][3 * ky + kx][b], f[sr & 1][kx], acc[r][b], 0, 0, 0);
+          }
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
   };
-  if constexpr (NB == 1) {
-    // each block's loads are issued before the workgroup waits for the
-    // previous block's products
-    for (int kb = 0; kb < nk; ++kb) {
-      fetch(kb);
-      if (kb > 0) __syncthreads();  // every wave is done with the previous block
-      stage();
-      __syncthreads();
-      products();
+  // the stages are loaded in order, NBUF - 1 ahead of the products, across tiles
+  int l_item = item, l_st = 0, l_buf = 0;
+  auto load_next = [&]() -> bool {
+    if (l_item >= run1) return false;
+    load_stage(l_st, l_buf);
+    l_buf = l_buf + 1 == NBUF ? 0 : l_buf + 1;
+    if (++l_st == nst) {
+      l_st = 0;
+      l_item += nx;
+      if (l_item < run1) aim(l_item);
     }
+    return true;
+  };
+  // this wave's loads of the next stage have landed: with `ahead` stages loaded
+  // after it still in flight
+  auto landed = [&](bool ahead) {
+    if (NBUF == 3 && ahead) wait_vm<KA + KW>();
+    else wait_vm<0>();
+  };
+  static_assert(NBUF == 2 || (NBUF == 3 && KA + KW < 63), "buffers");
+  aim(item);
+  load_next();
+  if constexpr (THIN) {
+    // the weights of this workgroup's channels, for the whole kernel
+    const int c = channel(0) + px;
+#pragma unroll
+    for (int u = 0; u < KC; ++u)
+#pragma unroll
+      for (int t = 0; t < 9; ++t) {
+        const int ci = 16 * u + 8 * half;
+        v8s v = {0, 0, 0, 0, 0, 0, 0, 0};
+        if (c < a.cout && ci < cin)
+          v = *reinterpret_cast<const v8s *>(a.w + ((size_t)c * 9 + t) * cin + ci);
+        wf[u][t][0] = __builtin_bit_cast(v8bf, v);
+      }
+  }
+  landed(NBUF == 3 && load_next());
+  lds_sync();  // (a barrier that leaves the loads in flight)
+  int buf = 0;
+  while (true) {
+    const int tile = THIN ? item : item / a.nco, ty = tile / a.tiles_x;
+    const int x0 = (tile - ty * a.tiles_x) * 32, y0 = ty * TY, co0 = channel(item);
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[r][b][v] = 0.f;
+    for (int st = 0; st < nst; ++st) {
+      // the stage in smem[buf] has landed for every wave, and no wave reads the buffer
+      // of the stage before it any more, which the next load fills
+      const bool ahead = load_next();
+      products(buf);
+      // (the stores of a tile's outputs are issued after this wait, so they complete
+      // during the next stage's products)
+      landed(ahead);
+      buf = buf + 1 == NBUF ? 0 : buf + 1;
+      if (st + 1 < nst) lds_sync();
+    }
+    // ---- outputs: lane l holds, of pixel l % 32, channels 8 g + 4 (l / 32) + e in
+    // accumulator 4 g + e (g, e < 4)
+    const int x = x0 + px;
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+    const int cb = co0 + 32 * b;
+    float bv[16];
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const bool any = a.bias && cb + 8 * g < a.cout;  // uniform: scalar loads
+        const float lo = any ? a.bias[cb + 8 * g + e] : 0.f;
+        const float hi = any ? a.bias[cb + 8 * g + 4 + e] : 0.f;
+        bv[4 * g + e] = half ? hi : lo;
+      }
+    uint32_t prev[8];  // the packed channels of the row above (pooling)
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int y = y0 + wave * R + r;
+      if (y >= H) break;  // uniform
+      __builtin_amdgcn_sched_barrier(0);  // one row at a time: fewer registers
+      const size_t row = ((size_t)y * W + x0) * a.cout + cb;  // of the tile's first pixel
+      float f[16];
+#pragma unroll
+      for (int v = 0; v < 16; ++v) f[v] = acc[r][b][v] + bv[v];
+      if (a.out32 && x < W) {
+        float *o = a.out32 + row;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const int c = 8 * g + 4 * half;  // cout is a multiple of 8
+          if (cb + c < a.cout)
+            *reinterpret_cast<float4 *>(o + px * a.cout + c) =
+                make_float4(f[4 * g], f[4 * g + 1], f[4 * g + 2], f[4 * g + 3]);
+        }
+      }
+      if (!a.out16) continue;  // uniform
+      uint32_t o[8];
+#pragma unroll
+      for (int v = 0; v < 8; ++v) {
+        const float u0 = a.relu ? fmaxf(f[2 * v], 0.f) : f[2 * v];
+        const float u1 = a.relu ? fmaxf(f[2 * v + 1], 0.f) : f[2 * v + 1];
+        o[v] = pack_bf16(u0, u1);
+      }
+      // groups g and g + 1 of the two halves -> eight consecutive channels per lane:
+      // lanes below 32 get 8 g .. 8 g + 7, the others 8 (g + 1) .. 8 (g + 1) + 7
+      uint32_t s[8];
+#pragma unroll
+      for (int g = 0; g < 4; g += 2)
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const auto sw2 = __builtin_amdgcn_permlane32_swap(o[2 * g + e], o[2 * g + 2 + e], false,
+                                                            false);
+          s[2 * g + e] = sw2[0];
+          s[2 * g + 2 + e] = sw2[1];
+        }
+#pragma unroll
+      for (int g = 0; g < 4; g += 2) {
+        const int c = 8 * g + 8 * half;
+        uint4 val = make_uint4(s[2 * g], s[2 * g + 1], s[2 * g + 2], s[2 * g + 3]);
+        if (x < W && cb + c < a.cout) {
+          if (a.gate) {
+            const uint4 m = *reinterpret_cast<const uint4 *>(a.gate + row + px * a.cout + c);
+            val = make_uint4(gated(val.x, m.x), gated(val.y, m.y), gated(val.z, m.z),
+                             gated(val.w, m.w));
+          }
+          *reinterpret_cast<uint4 *>(a.out16 + row + px * a.cout + c) = val;
+        }
+      }
+      static_assert(R % 2 == 0, "the pooling pairs rows of one wave");
+      {
+        if (a.pooled) {  // uniform; H and W are even, and so are y0 and x0
+          if (r % 2 == 0) {
+#pragma unroll
+            for (int v = 0; v < 8; ++v) prev[v] = s[v];
+          } else {
+#pragma unroll
+            for (int v = 0; v < 8; ++v) {
+              // (left + right) of the row above plus (left + right) of this row
+              auto pairs = [](uint32_t u, int hi) {
+                const float me = from_bf16((uint16_t)(hi ? u >> 16 : u & 0xffffu));
+                return me + __shfl_xor(me, 1, 64);
+              };
+              const float lo = pairs(prev[v], 0) + pairs(s[v], 0);
+              const float hi = pairs(prev[v], 1) + pairs(s[v], 1);
+              s[v] = pack_bf16(0.25f * lo, 0.25f * hi);
+            }
+            const size_t qp = (size_t)(y >> 1) * (W >> 1) + (x >> 1);
+#pragma unroll
+            for (int g = 0; g < 4; g += 2) {
+              const int c = cb + 8 * g + 8 * half;
+              if (x < W && !(x & 1) && c < a.cout)
+                *reinterpret_cast<uint4 *>(a.pooled + qp * a.cout + c) =
+                    make_uint4(s[2 * g], s[2 * g + 1], s[2 * g + 2], s[2 * g + 3]);
+            }
+          }
+        }
+      }
+    }
+    }
+    item += nx;
+    if (item >= run1) break;
+    lds_sync();  // the next tile's first stage has landed for every wave
+  }
+}
+
+// The tile of a convolution (rows per wave, blocks of 32 output channels): the
+// largest that still gives every CU about two workgroups (480 of 512), because a CU
+// holds two and fewer leave the chip idle; else two rows per wave with a third buffer
+// (66 x 98 with 384 input and 128 output channels: 26 us with four rows, 18 us with
+// two, 21 us with one).
+struct ConvTile {
+  int r, nb;
+};
+ConvTile conv_tile(int H, int W, bool thin, int cout) {
+  auto groups = [&](int r, int nb) {
+    return (int64_t)((W + 31) / 32) * ((H + 4 * r - 1) / (4 * r)) * ((cout + 32 * nb - 1) / (32 * nb));
+  };
+  if (!thin && cout % 64 == 0 && groups(4, 2) >= 480) return {4, 2};
+  return {groups(4, 1) >= 480 ? 4 : 2, 1};
+}
+
+hipError_t launch_conv(ConvArgs a, hipStream_t s) {
+  // an upsampled input without a skip runs as one with an absent skip
+  const bool two = a.c2 > 0 || a.up;
+  const bool thin = !two && a.c1 <= 32;
+  const bool gen = a.c1 % 16 != 0 || a.c2 % 16 != 0;
+  ConvTile t = conv_tile(a.H, a.W, thin, a.cout);
+  if (gen) t.nb = 1;
+  a.tiles_x = (a.W + 31) / 32;
+  a.nco = (a.cout + 32 * t.nb - 1) / (32 * t.nb);
+  const int tiles = a.tiles_x * ((a.H + 4 * t.r - 1) / (4 * t.r));
+  a.items = thin ? tiles : tiles * a.nco;
+  // persistent workgroups, as many as the chip holds at once, in whole rounds over
+  // the 8 XCDs
+  const int most = 512 / (thin ? a.nco : 1);
+  const dim3 grid(std::min(a.items, std::max(8, most & ~7)), thin ? a.nco : 1);
+  auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, a); };
+  auto rows = [&](auto twoc, auto genc) {
+    constexpr bool TWO = decltype(twoc)::value, GEN = decltype(genc)::value;
+    if constexpr (!GEN) {
+      if (t.r == 4 && t.nb == 2) return go(k_conv3x3<4, 2, 1, 2, TWO, false>);
+    }
+    if (t.r == 4) go(k_conv3x3<4, 1, 1, 2, TWO, GEN>);
+    else go(k_conv3x3<2, 1, 1, 3, TWO, GEN>);
+  };
+  using std::bool_constant;
+  if (thin) {
+    if (t.r == 4) go(k_conv3x3<4, 1, 2, 2, false, false>);
+    else go(k_conv3x3<2, 1, 2, 2, false, false>);
+  } else if (two) {
+    if (gen) rows(bool_constant<true>{}, bool_constant<true>{});
+    else rows(bool_constant<true>{}, bool_constant<false>{});
   } else {
-    // the loads of block kb + 1 are issued before the products of block kb
-    // (more registers: faster where 2 or 4 output blocks give the products
-    // enough length to cover them, slower with one)
-    fetch(0);
-    stage();
-    __syncthreads();
-    for (int kb = 0; kb < nk; ++kb) {
-      if (kb + 1 < nk) fetch(kb + 1);
-      products();
-      if (kb + 1 < nk) {
-        __syncthreads();  // every wave is done with this block
-        stage();
-        __syncthreads();
-      }
-    }
+    if (gen) rows(bool_constant<false>{}, bool_constant<true>{});
+    else rows(bool_constant<false>{}, bool_constant<false>{});
   }
-  // Store, one output block at a time: the accumulators (lane l holds output
-  // channel l % 32 of 16 pixels) go through LDS as a [pixel][channel] FP32
-  // tile, which each thread then reads and writes 16 bytes at a time.
-  float *tile = reinterpret_cast<float *>(smem);
-#pragma unroll
-  for (int b = 0; b < NB; ++b) {
-    const int cb = co0 + 32 * b;  // first output channel of the block
-    {
-      const int col = lane & 31;
-      const float bv = (bias && cb + col < cout) ? bias[cb + col] : 0.f;
-      __syncthreads();  // every wave is done with the staged operands (or the previous tile)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int row = wave * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-        tile[row * 32 + col] = acc[b][v] + bv;
-      }
-      __syncthreads();
-    }
-    if (out32) {
-      // 8 chunks of 4 channels per pixel
-      for (int c = tid; c < PX * 8; c += NT) {
-        const int row = c >> 3, part = c & 7, q = p0 + row, co = cb + 4 * part;
-        if (q < P && co < cout) {
-          // cout is a multiple of 8, so the 4 channels are all below cout
-          *reinterpret_cast<float4 *>(out32 + (size_t)q * cout + co) =
-              *reinterpret_cast<const float4 *>(tile + row * 32 + 4 * part);
-        }
-      }
-    }
-    if (out16) {
-      // 4 chunks of 8 channels per pixel (cout is a multiple of 8)
-      for (int c = tid; c < PX * 4; c += NT) {
-        const int row = c >> 2, part = c & 3, q = p0 + row, co = cb + 8 * part;
-        if (q < P && co < cout) {
-          const float4 u0 = *reinterpret_cast<const float4 *>(tile + row * 32 + 8 * part);
-          const float4 u1 = *reinterpret_cast<const float4 *>(tile + row * 32 + 8 * part + 4);
-          const float f[8] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w};
-          v8s o;
-#pragma unroll
-          for (int e = 0; e < 8; ++e) o[e] = (short)to_bf16(relu ? fmaxf(f[e], 0.f) : f[e]);
-          *reinterpret_cast<v8s *>(out16 + (size_t)q * cout + co) = o;
-        }
-      }
-    }
-  }
+  return hipGetLastError();
 }
 
 // ----------------------------------------------------------------------------
@@ -638,17 +908,9 @@ cgh_status cgh_net_conv3x3(const cgh_bf16 *x1, int32_t c1, int32_t up, const cgh
   NET_CHECK(w && cout > 0 && cout % 8 == 0, "w NULL or cout = %d not a multiple of 8", cout);
   NET_CHECK(out32 || out16, "no output");
   NET_CHECK(al16(w) && al16(out32) && al16(out16), "w, out32 and out16 must be 16-byte aligned");
-  hipStream_t s = (hipStream_t)stream;
-  const int nb = cout % 128 == 0 ? 4 : (cout % 64 == 0 ? 2 : 1);
-  const dim3 grid(blocks_of((int64_t)H * W, 32 * kConvWaves), (cout + 32 * nb - 1) / (32 * nb));
-#define NET_CONV(NB)                                                                         \
-  hipLaunchKernelGGL((k_conv3x3<NB, kConvWaves>), grid, dim3(64 * kConvWaves), 0, s, x1, c1, up, \
-                     x2, c2, H, W, w, bias, cout, relu, out32, out16)
-  if (nb == 4) NET_CONV(4);
-  else if (nb == 2) NET_CONV(2);
-  else NET_CONV(1);
-#undef NET_CONV
-  NET_LAUNCHED("conv3x3");
+  ConvArgs a{x1, x2, w, bias, c1, c2, up, H, W, cout, relu, out32, out16, nullptr, nullptr, 0};
+  const hipError_t e = launch_conv(a, (hipStream_t)stream);
+  if (e != hipSuccess) return report(CGH_ERR_DEVICE, "conv3x3: %s", hipGetErrorString(e));
   return CGH_OK;
 }
 
