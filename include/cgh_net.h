@@ -7,7 +7,7 @@
  * ReLU, 2x2 average pooling and nearest 2x upsampling with skip
  * concatenation.  Precision: weights and the activations a convolution reads
  * are BF16 (round to nearest, ties to even), sums are FP32 on the matrix
- * cores (v_mfma_f32_32x32x8 bf16).
+ * cores (v_mfma_f32_32x32x16 bf16).
  *
  * Layouts: activations NHWC with batch 1, [H][W][C] contiguous; convolution
  * weights [Co][3][3][Ci] with out[y][x][co] = b[co] + sum_{ky,kx,ci}
@@ -45,20 +45,35 @@ cgh_status cgh_net_conv3x3(const cgh_bf16 *x1, int32_t c1, int32_t up, const cgh
                            const float *bias, int32_t cout, int32_t relu, float *out32,
                            cgh_bf16 *out16, void *stream);
 
+/* cgh_net_conv3x3 to out16 (required) followed by cgh_net_pool2 of out16 into
+ * `pooled`, in one pass (the same values; H, W even). */
+cgh_status cgh_net_conv3x3_pool2(const cgh_bf16 *x1, int32_t c1, int32_t up, const cgh_bf16 *x2,
+                                 int32_t c2, int32_t H, int32_t W, const cgh_bf16 *w,
+                                 const float *bias, int32_t cout, int32_t relu, cgh_bf16 *out16,
+                                 cgh_bf16 *pooled, void *stream);
+
+/* The adjoint of a convolution with respect to its input followed by the gradient
+ * through the ReLU that made that input, in one pass: cgh_net_conv3x3 of gy (cout
+ * channels) with w_t (cgh_net_flip_weights: [cin][3][3][cout], no bias), then
+ * cgh_net_relu_grad with the stored activation `gate` ([H][W][cin]) into out16
+ * (the same values; the FP32 gradient is not stored). */
+cgh_status cgh_net_conv3x3_gated(const cgh_bf16 *gy, int32_t cout, int32_t H, int32_t W,
+                                 const cgh_bf16 *w_t, int32_t cin, const cgh_bf16 *gate,
+                                 cgh_bf16 *out16, void *stream);
+
 /* w_t[ci][ky][kx][co] = w[co][2 - ky][2 - kx][ci]: the weights of the adjoint
  * (input gradient) of the convolution with w ([cout][3][3][cin], BF16). */
 cgh_status cgh_net_flip_weights(const cgh_bf16 *w, int32_t cout, int32_t cin, cgh_bf16 *w_t,
                                 void *stream);
 
-/* Bytes of scratch cgh_net_conv3x3_wgrad needs for this shape: FP32 partial
- * sums over pixel ranges, and channel-major BF16 copies of dL/dout and of the
- * input (three column-shifted, zero-padded copies). */
+/* Bytes of scratch cgh_net_conv3x3_wgrad needs for this shape (it holds FP32 partial
+ * sums over shares of the image; the size is generous). */
 size_t cgh_net_wgrad_workspace(int32_t H, int32_t W, int32_t cin, int32_t cout);
 
 /* Weight and bias gradients of the convolution above for dL/dout = gy
  * (BF16 [H][W][cout]): gw[co][ky][kx][ci] = sum_p gy[p][co] in[p + k - 1][ci]
  * and gb[co] = sum_p gy[p][co] (FP32; gb may be NULL), in = [up(x1), x2] as in
- * cgh_net_conv3x3 (same restrictions).  Partial sums over pixel ranges go to
+ * cgh_net_conv3x3 (same restrictions).  Partial sums over shares of the image go to
  * `workspace` (>= cgh_net_wgrad_workspace bytes, else CGH_ERR_WORKSPACE;
  * 16-byte aligned, as gy must be) and are added in a fixed order, so the
  * result is deterministic. */
@@ -86,11 +101,24 @@ cgh_status cgh_net_pool2(const cgh_bf16 *x, int32_t H, int32_t W, int32_t C, cgh
 cgh_status cgh_net_up_adjoint(const float *g, int32_t H, int32_t W, int32_t stride, int32_t C,
                               float *out, void *stream);
 
+/* cgh_net_up_adjoint followed by cgh_net_relu_grad with `gate` ([H/2][W/2][C]) in one
+ * pass (the same values): out BF16 [H/2][W/2][C].  C and stride multiples of 8. */
+cgh_status cgh_net_up_adjoint_gated(const float *g, int32_t H, int32_t W, int32_t stride,
+                                    int32_t C, const cgh_bf16 *gate, cgh_bf16 *out,
+                                    void *stream);
+
 /* Gradient of an encoder output that feeds both the pooling and a skip:
  * out[y][x][c] = gp[y/2][x/2][c] / 4 + gs[y][x][off + c] (gs rows of `stride`
  * channels); FP32, out [H][W][C]. */
 cgh_status cgh_net_grad_combine(const float *gp, const float *gs, int32_t stride, int32_t off,
                                 int32_t H, int32_t W, int32_t C, float *out, void *stream);
+
+/* cgh_net_grad_combine (both inputs present) followed by cgh_net_relu_grad with
+ * `gate` ([H][W][C]) in one pass (the same values): out BF16 [H][W][C].  C, stride and
+ * off multiples of 8. */
+cgh_status cgh_net_grad_combine_gated(const float *gp, const float *gs, int32_t stride,
+                                      int32_t off, int32_t H, int32_t W, int32_t C,
+                                      const cgh_bf16 *gate, cgh_bf16 *out, void *stream);
 
 /* Lattice of gy x gx Gaussians on an H x W canvas with C colour channels:
  * Gaussian k = i gx + j sits at ((j + 1/2) W / gx, (i + 1/2) H / gy) and reads

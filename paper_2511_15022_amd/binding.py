@@ -102,6 +102,10 @@ _I32, _I64, _SZ = ctypes.c_int32, ctypes.c_int64, ctypes.c_size_t
 _NET_SIGS = [
     ("cgh_net_conv3x3", ctypes.c_int,
      [_VP, _I32, _I32, _VP, _I32, _I32, _I32, _VP, _VP, _I32, _I32, _VP, _VP, _VP]),
+    ("cgh_net_conv3x3_pool2", ctypes.c_int,
+     [_VP, _I32, _I32, _VP, _I32, _I32, _I32, _VP, _VP, _I32, _I32, _VP, _VP, _VP]),
+    ("cgh_net_conv3x3_gated", ctypes.c_int,
+     [_VP, _I32, _I32, _I32, _VP, _I32, _VP, _VP, _VP]),
     ("cgh_net_flip_weights", ctypes.c_int, [_VP, _I32, _I32, _VP, _VP]),
     ("cgh_net_wgrad_workspace", ctypes.c_size_t, [_I32, _I32, _I32, _I32]),
     ("cgh_net_conv3x3_wgrad", ctypes.c_int,
@@ -111,6 +115,10 @@ _NET_SIGS = [
     ("cgh_net_pool2", ctypes.c_int, [_VP, _I32, _I32, _I32, _VP, _VP]),
     ("cgh_net_up_adjoint", ctypes.c_int, [_VP, _I32, _I32, _I32, _I32, _VP, _VP]),
     ("cgh_net_grad_combine", ctypes.c_int, [_VP, _VP, _I32, _I32, _I32, _I32, _I32, _VP, _VP]),
+    ("cgh_net_up_adjoint_gated", ctypes.c_int,
+     [_VP, _I32, _I32, _I32, _I32, _VP, _VP, _VP]),
+    ("cgh_net_grad_combine_gated", ctypes.c_int,
+     [_VP, _VP, _I32, _I32, _I32, _I32, _I32, _VP, _VP, _VP]),
     ("cgh_net_lattice_gather", ctypes.c_int, [_VP, _I32, _I32, _I32, _I32, _I32, _VP, _VP]),
     ("cgh_net_lattice_scatter", ctypes.c_int,
      [_VP, _VP, _I32, _I32, _I32, _I32, _I32, _VP, _VP]),

@@ -33,24 +33,6 @@ __device__ __forceinline__ float from_bf16(uint16_t h) { return __uint_as_float(
 
 bool al16(const void *p) { return ((uintptr_t)p & 15u) == 0; }
 
-// eight consecutive channels (16 bytes) of the convolution input at (y, x),
-// channel c0 (a multiple of 8) of [up(x1), x2]; zero outside the image and at
-// c0 >= c1 + c2 (the upper half of a last, half-filled block of 16)
-__device__ __forceinline__ v8s conv_in8(const uint16_t *__restrict__ x1, int c1, int up,
-                                        const uint16_t *__restrict__ x2, int c2, int H, int W,
-                                        int y, int x, int c0) {
-  v8s r = {0, 0, 0, 0, 0, 0, 0, 0};
-  if (y < 0 || y >= H || x < 0 || x >= W || c0 >= c1 + c2) return r;
-  const uint16_t *src;
-  if (c0 < c1) {
-    src = up ? x1 + ((size_t)(y >> 1) * (W >> 1) + (x >> 1)) * c1 + c0
-             : x1 + ((size_t)y * W + x) * c1 + c0;
-  } else {
-    src = x2 + ((size_t)y * W + x) * c2 + (c0 - c1);
-  }
-  return *reinterpret_cast<const v8s *>(src);
-}
-
 // ----------------------------------------------------------------------------
 // Convolution.  A workgroup of four waves takes tiles of 32 columns x 4 R rows and
 // 32 NB output channels; wave w takes R rows of a tile (all 32 columns), in R NB
@@ -534,133 +516,216 @@ hipError_t launch_conv(ConvArgs a, hipStream_t s) {
 
 // ----------------------------------------------------------------------------
 // Weight gradient: gw[co][t][ci] (tap t = 3 ky + kx) = sum_p gy[p][co]
-// in[p + k(t) - 1][ci], a GEMM whose reduction runs over pixels.  Both operands
-// are first copied channel-major, so that a lane's eight consecutive pixels of
-// one channel are one aligned 16-byte load (Wr = W rounded up to 16):
-//   gyT[co][y][x]      = gy[y][x][co]                (x < Wr; zero for x >= W)
-//   ink[kx][ci][yy][x] = in[yy - 1][x + kx - 1][ci]  (yy < H + 2; zero outside)
-// Tap (ky, kx) of output pixel (y, x) then reads ink[kx][ci][y + ky][x] with no
-// border test.  One wave takes 32 output channels x 32 input channels, all nine
-// taps, over a range of 16-pixel row chunks (v_mfma_f32_32x32x16 bf16, K = the
-// chunk's pixels), and writes FP32 partials for its range; the bias gradient
-// rides along in the waves of the first input-channel block.
+// in[p + k(t) - 1][ci], a GEMM whose reduction runs over pixels (K = 16 pixels of a
+// row per v_mfma_f32_32x32x16 bf16).  A workgroup of four waves takes 32 output x
+// 32 input channels, all nine taps, over a share of the tiles of 16 rows x 32
+// columns: the tile's dL/dout and its input with a border of one are loaded
+// straight into LDS as [row][pixel][32 channels] and read transposed
+// (ds_read_b64_tr_b16: a lane gets four consecutive pixels of one channel), so no
+// channel-major copy of either exists in memory.  A tap's column shift is an address
+// offset; one fragment of an input row serves the three taps ky with three rows of
+// dL/dout held in registers.  Wave w takes rows 4 w .. 4 w + 3 of the tile; the four
+// waves' sums are added in LDS, the shares' by k_wgrad_reduce, in fixed orders.  The
+// bias gradient rides along in the workgroups of the first input channels.
+//
+// LDS reads bound the products (44 transposed reads for 36 matrix instructions); two
+// workgroups per CU cover each other's loads.  Measured at 512 x 512 RGB, all 15
+// layers: staging copies, products and reduction 1222 us before (one wave per range
+// of pixels, operands from global memory), now 298 us of products and 112 us of
+// reduction.
 // ----------------------------------------------------------------------------
+struct WgradArgs {
+  const uint16_t *x1, *x2, *gy;
+  int c1, c2, up, H, W, cout;
+  int tiles_x, tiles, splits;
+  float *part, *part_b;
+};
 
-// gyT: a workgroup transposes one row y, 64 columns and 32 channels through LDS
-__global__ __launch_bounds__(256) void k_wg_gyT(const uint16_t *__restrict__ gy, int H, int W,
-                                                int Wr, int cout, uint16_t *__restrict__ gyT) {
-  __shared__ uint16_t tile[64][33];
-  const int tid = threadIdx.x;
-  const int y = blockIdx.y, x0 = blockIdx.x * 64, co0 = blockIdx.z * 32;
-  {
-    const int px = tid >> 2, g = tid & 3, x = x0 + px, co = co0 + 8 * g;
-    v8s v = {0, 0, 0, 0, 0, 0, 0, 0};
-    if (x < W && co < cout) v = *reinterpret_cast<const v8s *>(gy + ((size_t)y * W + x) * cout + co);
+constexpr int kWgRows = 16, kWgCols = 32;  // pixels of a tile
+
+__global__ __launch_bounds__(256, 2) void k_conv3x3_wgrad(WgradArgs a) {
+  constexpr int SC = kWgCols + 2, NI = (kWgRows + 2) * SC * 4, NG = kWgRows * kWgCols * 4;
+  constexpr int KI = (NI + 255) / 256, KG = NG / 256;
+  static_assert(NG % 256 == 0, "whole rounds of dL/dout slots");
+  __shared__ v8s smem[NI + NG];  // input slots, then dL/dout slots; at the end FP32 sums
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ci0 = blockIdx.x * 32, co0 = blockIdx.y * 32, share = blockIdx.z;
+  const int H = a.H, W = a.W, cin = a.c1 + a.c2, W1 = a.up ? W >> 1 : W;
+  // byte offsets of this thread's slots from the tile's first staged pixel (tiles
+  // start at even rows and columns, so they hold for every tile with up too); bit k
+  // of from2: slot k's channels are x2's
+  uint32_t oi[KI], og[KG], from2 = 0;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) tile[px][8 * g + i] = (uint16_t)v[i];
-  }
-  __syncthreads();
-  {
-    const int co = tid >> 3, seg = tid & 7, x = x0 + 8 * seg;
-    if (co0 + co < cout && x < Wr) {
-      v8s v;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) v[i] = (short)tile[8 * seg + i][co];
-      *reinterpret_cast<v8s *>(gyT + ((size_t)(co0 + co) * H + y) * Wr + x) = v;
+  for (int k = 0; k < KI; ++k) {
+    const int s = tid + 256 * k, i = s >> 2, row = i / SC, col = i - row * SC;
+    const int c = ci0 + 8 * (s & 3);
+    if (s >= NI || c >= cin) {
+      oi[k] = kOutside;
+    } else if (c < a.c1) {
+      const int q = a.up ? ((row + 1) >> 1) * W1 + ((col + 1) >> 1) : row * W + col;
+      oi[k] = 2u * (uint32_t)(q * a.c1 + c);
+    } else {
+      oi[k] = 2u * (uint32_t)((row * W + col) * a.c2 + c - a.c1);
+      from2 |= 1u << k;
     }
   }
-}
-
-// ink: a workgroup builds row yy (< H + 2) of the three shifted copies for 64
-// columns and 32 channels from source columns x0 - 1 .. x0 + 64 staged in LDS
-__global__ __launch_bounds__(256) void k_wg_ink(const uint16_t *__restrict__ x1, int c1, int up,
-                                                const uint16_t *__restrict__ x2, int c2, int H,
-                                                int W, int Wr, uint16_t *__restrict__ ink) {
-  __shared__ uint16_t tile[66][33];
-  const int tid = threadIdx.x;
-  const int yy = blockIdx.y, x0 = blockIdx.x * 64, ci0 = blockIdx.z * 32;
-  const int cin = c1 + c2;
-  for (int item = tid; item < 66 * 4; item += 256) {
-    const int col = item >> 2, g = item & 3;
-    // conv_in8 is zero outside the image and past the last channel
-    const v8s v = conv_in8(x1, c1, up, x2, c2, H, W, yy - 1, x0 - 1 + col, ci0 + 8 * g);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) tile[col][8 * g + i] = (uint16_t)v[i];
+  for (int k = 0; k < KG; ++k) {
+    const int s = tid + 256 * k, i = s >> 2, row = i / kWgCols, col = i % kWgCols;
+    const int c = co0 + 8 * (s & 3);
+    og[k] = c < a.cout ? 2u * (uint32_t)((row * W + col) * a.cout + c) : kOutside;
   }
-  __syncthreads();
-  for (int item = tid; item < 3 * 256; item += 256) {
-    const int kx = item >> 8, r = item & 255, ci = r >> 3, seg = r & 7, x = x0 + 8 * seg;
-    if (ci0 + ci < cin && x < Wr) {
-      v8s v;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) v[i] = (short)tile[8 * seg + i + kx][ci];  // column x + i + kx - 1
-      *reinterpret_cast<v8s *>(ink + (((size_t)kx * cin + ci0 + ci) * (H + 2) + yy) * Wr + x) = v;
-    }
-  }
-}
-
-__global__ __launch_bounds__(64) void k_conv3x3_wgrad(const uint16_t *__restrict__ gyT,
-                                                      const uint16_t *__restrict__ ink, int H,
-                                                      int Wr, int cin, int cout, int cps,
-                                                      int nchunks, float *__restrict__ part,
-                                                      float *__restrict__ part_b) {
-  const int lane = threadIdx.x, half = lane >> 5;
-  const int cib = blockIdx.x, cob = blockIdx.y, s = blockIdx.z;
-  const int N = 9 * cin, cw = Wr / 16;
-  const int co = cob * 32 + (lane & 31), ci = cib * 32 + (lane & 31);
-  const bool cov = co < cout, civ = ci < cin;
-  const uint16_t *arow = gyT + (size_t)(cov ? co : 0) * H * Wr;
-  const uint16_t *brow = ink + (size_t)(civ ? ci : 0) * (H + 2) * Wr;
-  const size_t kstride = (size_t)cin * (H + 2) * Wr;  // between the kx copies
-  const v8s z = {0, 0, 0, 0, 0, 0, 0, 0};
+  // this lane's part of a transposed read's address: pixel 8 (lane / 32) + (lane % 16) / 4,
+  // channels 16 (lane / 16 % 2) + 4 (lane % 4)
+  const int at = (8 * (lane >> 5) + ((lane & 15) >> 2)) * 32 + 16 * ((lane >> 4) & 1) +
+                 4 * (lane & 3);
+  uint16_t *const si = reinterpret_cast<uint16_t *>(smem) + at;
+  uint16_t *const sg = reinterpret_cast<uint16_t *>(smem + NI) + at;
+  // eight consecutive pixels of one channel per lane, from pixel index p of a staged array
+  auto frag = [](uint16_t *s, int p) {
+    typedef __attribute__((address_space(3))) v4s *lds4;
+    const v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4)(s + 32 * p));
+    const v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4)(s + 32 * (p + 4)));
+    return __builtin_bit_cast(v8bf, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+  };
   v16f acc[9];
 #pragma unroll
   for (int t = 0; t < 9; ++t)
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
   float bsum = 0.f;
-  const int cbeg = s * cps, cend = min(nchunks, cbeg + cps);
-  for (int c = cbeg; c < cend; ++c) {
-    const int y = c / cw, x = (c - y * cw) * 16 + 8 * half;
-    const v8s a = cov ? *reinterpret_cast<const v8s *>(arow + (size_t)y * Wr + x) : z;
-    v8s b[9];
+  const int t0 = (int)((int64_t)a.tiles * share / a.splits);
+  const int t1 = (int)((int64_t)a.tiles * (share + 1) / a.splits);
+  for (int tile = t0; tile < t1; ++tile) {
+    const int ty = tile / a.tiles_x, x0 = (tile - ty * a.tiles_x) * kWgCols, y0 = ty * kWgRows;
+    const int64_t q2 = (int64_t)(y0 - 1) * W + x0 - 1;
+    const int64_t q1 = a.up ? (int64_t)((y0 >> 1) - 1) * W1 + (x0 >> 1) - 1 : q2;
+    const auto b1 = buffer_of(a.x1 + q1 * a.c1, kBufferBytes);
+    const auto b2 = buffer_of(a.x2 + q2 * a.c2, kBufferBytes);
+    const auto bg = buffer_of(a.gy + ((int64_t)y0 * W + x0) * a.cout, kBufferBytes);
+    uint32_t out_i = 0, out_g = 0;  // slots whose pixel lies outside the image
+    if (y0 == 0 || x0 == 0 || y0 + kWgRows + 1 > H || x0 + kWgCols + 1 > W) {
 #pragma unroll
-    for (int ky = 0; ky < 3; ++ky)
+      for (int k = 0; k < KI; ++k) {
+        const int i = (tid + 256 * k) >> 2, row = i / SC, col = i - row * SC;
+        const bool in = ((uint32_t)(y0 - 1 + row) < (uint32_t)H) &
+                        ((uint32_t)(x0 - 1 + col) < (uint32_t)W);
+        out_i |= in ? 0u : 1u << k;
+      }
 #pragma unroll
-      for (int kx = 0; kx < 3; ++kx)
-        b[3 * ky + kx] =
-            civ ? *reinterpret_cast<const v8s *>(brow + kx * kstride + (size_t)(y + ky) * Wr + x)
-                : z;
-    if (cib == 0) {
+      for (int k = 0; k < KG; ++k) {
+        const int i = (tid + 256 * k) >> 2;
+        out_g |= (y0 + i / kWgCols < H) & (x0 + i % kWgCols < W) ? 0u : 1u << k;
+      }
+    }
+    lds_sync();  // every wave is done with the previous tile
+    v8s *const li = smem + 64 * wave, *const lg = smem + NI + 64 * wave;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) bsum += from_bf16((uint16_t)a[i]);
+    for (int k = 0; k < KI; ++k) {
+      if (256 * (k + 1) > NI && tid + 256 * k >= NI) continue;
+      const uint32_t o = oi[k] | ((out_i << (31 - k)) & kOutside);
+      if ((from2 >> k) & 1) load_to_lds(b2, o, 0, li + 256 * k);
+      else load_to_lds(b1, o, 0, li + 256 * k);
     }
 #pragma unroll
-    for (int t = 0; t < 9; ++t)
-      acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, a),
-                                                       __builtin_bit_cast(v8bf, b[t]), acc[t], 0,
-                                                       0, 0);
+    for (int k = 0; k < KG; ++k)
+      load_to_lds(bg, og[k] | ((out_g << (31 - k)) & kOutside), 0, lg + 256 * k);
+    wait_vm<0>();
+    lds_sync();
+#pragma unroll
+    for (int xc = 0; xc < kWgCols; xc += 16) {
+      v8bf g[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) g[r] = frag(sg, (4 * wave + r) * kWgCols + xc);
+      if (blockIdx.x == 0) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int i = 0; i < 8; ++i) bsum += (float)g[r][i];
+      }
+      v8bf f[2][3];
+#pragma unroll
+      for (int kx = 0; kx < 3; ++kx) f[0][kx] = frag(si, 4 * wave * SC + xc + kx);
+#pragma unroll
+      for (int sr = 0; sr < 6; ++sr) {
+        // the next row's fragments are read before this row's products
+        if (sr + 1 < 6)
+#pragma unroll
+          for (int kx = 0; kx < 3; ++kx)
+            f[(sr + 1) & 1][kx] = frag(si, (4 * wave + sr + 1) * SC + xc + kx);
+#pragma unroll
+        for (int kx = 0; kx < 3; ++kx)
+#pragma unroll
+          for (int ky = 0; ky < 3; ++ky) {
+            const int r = sr - ky;
+            if (r < 0 || r > 3) continue;
+            acc[3 * ky + kx] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(g[r], f[sr & 1][kx],
+                                                                       acc[3 * ky + kx], 0, 0, 0);
+          }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
   }
-  // D[row = co][col = ci] of tap t
-  float *dst = part + (size_t)s * cout * N;
+  // the four waves' sums, three taps at a time: D[row = co][col = ci] of tap t has row
+  // 8 (v / 4) + 4 (l / 32) + v % 4 and column l % 32 in register v of lane l
+  const int N = 9 * cin;
+  float *const red = reinterpret_cast<float *>(smem);
+  float *dst = a.part + (size_t)share * a.cout * N;
 #pragma unroll
-  for (int t = 0; t < 9; ++t)
+  for (int tb = 0; tb < 9; tb += 3) {
+    lds_sync();
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int r = cob * 32 + 8 * (v >> 2) + 4 * half + (v & 3);
-      if (civ && r < cout) dst[(size_t)r * N + t * cin + ci] = acc[t][v];
-    }
-  if (cib == 0) {
-    // lanes l and l + 32 hold the two halves of the pixels of channel co
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) red[(wave * 3 + t) * 1024 + 64 * v + lane] = acc[tb + t][v];
+    lds_sync();
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int i = tid + 256 * j, v = i >> 6, l = i & 63;
+        const int co = co0 + 8 * (v >> 2) + 4 * (l >> 5) + (v & 3), ci = ci0 + (l & 31);
+        const float s = (red[t * 1024 + i] + red[(3 + t) * 1024 + i]) +
+                        (red[(6 + t) * 1024 + i] + red[(9 + t) * 1024 + i]);
+        if (co < a.cout && ci < cin) dst[(size_t)co * N + (tb + t) * cin + ci] = s;
+      }
+  }
+  if (blockIdx.x == 0) {
+    // lanes l and l + 32 hold the two halves of the pixels of channel co0 + l
     bsum += __shfl_down(bsum, 32, 64);
-    if (lane < 32 && cov) part_b[(size_t)s * cout + co] = bsum;
+    lds_sync();
+    if (lane < 32) red[32 * wave + lane] = bsum;
+    lds_sync();
+    if (tid < 32 && co0 + tid < a.cout)
+      a.part_b[(size_t)share * a.cout + co0 + tid] =
+          (red[tid] + red[32 + tid]) + (red[64 + tid] + red[96 + tid]);
   }
 }
 
-// fixed-order sum over the splits: a workgroup takes 16 outputs with 16 lanes
-// each; lane g of an output adds splits g, g + 16, ... in order, then one lane
-// adds the 16 lane sums in order.  Outputs i < len are the weight gradients;
-// the workgroups with i < cout also sum the bias partials the same way.
+// Fixed-order sum over many shares (more than kFewShares): a workgroup takes 16
+// outputs with 16 lanes each; lane g of an output adds shares g, g + 16, ... in order
+// (sixteen loads in flight), then one lane adds the 16 lane sums in order.  Outputs
+// i < len are the weight gradients; the workgroups with i < cout also sum the bias
+// partials the same way.
+constexpr int kFewShares = 16;
+
+__device__ __forceinline__ float shares_sum(const float *__restrict__ part, int64_t stride,
+                                            int splits, int g) {
+  float s = 0.f;
+  for (int k = g; k < splits; k += 256) {
+    float v[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      const int kk = k + 16 * j;
+      v[j] = kk < splits ? part[(size_t)kk * stride] : 0.f;
+    }
+#pragma unroll
+    for (int j = 0; j < 16; ++j) s += v[j];
+  }
+  return s;
+}
+
 __global__ __launch_bounds__(256) void k_wgrad_reduce(const float *__restrict__ part,
                                                       const float *__restrict__ part_b,
                                                       int splits, int64_t len, int cout,
@@ -669,10 +734,7 @@ __global__ __launch_bounds__(256) void k_wgrad_reduce(const float *__restrict__ 
   __shared__ float red[16][17];
   const int o = threadIdx.x & 15, g = threadIdx.x >> 4;
   const int64_t i = (int64_t)blockIdx.x * 16 + o;
-  float s = 0.f;
-  if (i < len)
-    for (int k = g; k < splits; k += 16) s += part[(size_t)k * len + i];
-  red[g][o] = s;
+  red[g][o] = i < len ? shares_sum(part + i, len, splits, g) : 0.f;
   __syncthreads();
   if (g == 0 && i < len) {
     float t = 0.f;
@@ -681,15 +743,37 @@ __global__ __launch_bounds__(256) void k_wgrad_reduce(const float *__restrict__ 
   }
   if (gb == nullptr || (int64_t)blockIdx.x * 16 >= cout) return;  // uniform per workgroup
   __syncthreads();
-  s = 0.f;
-  if (i < cout)
-    for (int k = g; k < splits; k += 16) s += part_b[(size_t)k * cout + i];
-  red[g][o] = s;
+  red[g][o] = i < cout ? shares_sum(part_b + i, cout, splits, g) : 0.f;
   __syncthreads();
   if (g == 0 && i < cout) {
     float t = 0.f;
     for (int q = 0; q < 16; ++q) t += red[q][o];
     gb[i] = t;
+  }
+}
+
+// The same for at most kFewShares shares: four consecutive outputs per thread, the
+// shares in order; the threads after the weight gradients' take the biases, one each.
+// len is a multiple of 4 (cout is one of 8).
+__global__ __launch_bounds__(256) void k_wgrad_reduce_few(const float *__restrict__ part,
+                                                          const float *__restrict__ part_b,
+                                                          int splits, int64_t len, int cout,
+                                                          float *__restrict__ gw,
+                                                          float *__restrict__ gb) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x, n4 = len / 4;
+  if (i < n4) {
+    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 8
+    for (int k = 0; k < splits; ++k) {
+      const float4 v = *reinterpret_cast<const float4 *>(part + (size_t)k * len + 4 * i);
+      s = make_float4(s.x + v.x, s.y + v.y, s.z + v.z, s.w + v.w);
+    }
+    float *d = gw + 4 * i;  // (gw need not be 16-byte aligned)
+    d[0] = s.x; d[1] = s.y; d[2] = s.z; d[3] = s.w;
+  } else if (gb && i < n4 + cout) {
+    float s = 0.f;
+    for (int k = 0; k < splits; ++k) s += part_b[(size_t)k * cout + (i - n4)];
+    gb[i - n4] = s;
   }
 }
 
@@ -710,6 +794,72 @@ __global__ void k_relu_grad(const float *__restrict__ g, const uint16_t *__restr
                             int64_t n, uint16_t *__restrict__ out) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) out[i] = to_bf16((a == nullptr || from_bf16(a[i]) > 0.f) ? g[i] : 0.f);
+}
+
+// four BF16 values of v, zero where the gate's are not > 0 (no gate: all kept)
+__device__ __forceinline__ uint2 gate4(float4 v, const uint16_t *__restrict__ gate, size_t at) {
+  uint2 o = make_uint2(pack_bf16(v.x, v.y), pack_bf16(v.z, v.w));
+  if (gate) {
+    const uint2 m = *reinterpret_cast<const uint2 *>(gate + at);
+    o = make_uint2(gated(o.x, m.x), gated(o.y, m.y));
+  }
+  return o;
+}
+
+// the same as k_relu_grad, four elements per thread (16-byte aligned g, 8-byte aligned
+// a and out, n a multiple of 4): one load and one store per thread instead of four
+// narrow ones (512 x 512 x 24: 12 -> 6 us)
+__global__ void k_relu_grad4(const float *__restrict__ g, const uint16_t *__restrict__ a,
+                             int64_t n4, uint16_t *__restrict__ out) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n4) return;
+  const float4 v = reinterpret_cast<const float4 *>(g)[i];
+  *reinterpret_cast<uint2 *>(out + 4 * i) = gate4(v, a, 4 * (size_t)i);
+}
+
+// The upsampling's adjoint and the ReLU below it in one pass, four channels per thread
+// (C, stride multiples of 4): the FP32 sum of k_up_adjoint is rounded once and never
+// stored.
+__global__ void k_up_adjoint_gated(const float *__restrict__ g, int H, int W, int stride, int C,
+                                   const uint16_t *__restrict__ gate, uint16_t *__restrict__ out) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int Ho = H / 2, Wo = W / 2, C4 = C / 4;
+  if (i >= (int64_t)Ho * Wo * C4) return;
+  const int c = 4 * (int)(i % C4);
+  const int64_t q = i / C4;
+  const int y = (int)(q / Wo), x = (int)(q - (int64_t)y * Wo);
+  const float *s = g + ((size_t)(2 * y) * W + 2 * x) * stride + c;
+  const float4 p0 = *reinterpret_cast<const float4 *>(s);
+  const float4 p1 = *reinterpret_cast<const float4 *>(s + stride);
+  const float4 p2 = *reinterpret_cast<const float4 *>(s + (size_t)W * stride);
+  const float4 p3 = *reinterpret_cast<const float4 *>(s + (size_t)W * stride + stride);
+  const float4 v = make_float4((p0.x + p1.x) + (p2.x + p3.x), (p0.y + p1.y) + (p2.y + p3.y),
+                               (p0.z + p1.z) + (p2.z + p3.z), (p0.w + p1.w) + (p2.w + p3.w));
+  const size_t at = (size_t)q * C + c;
+  *reinterpret_cast<uint2 *>(out + at) = gate4(v, gate, at);
+}
+
+// k_grad_combine and the ReLU below it in one pass, likewise
+__global__ void k_grad_combine_gated(const float *__restrict__ gp, const float *__restrict__ gs,
+                                     int stride, int off, int H, int W, int C,
+                                     const uint16_t *__restrict__ gate,
+                                     uint16_t *__restrict__ out) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int C4 = C / 4;
+  if (i >= (int64_t)H * W * C4) return;
+  const int c = 4 * (int)(i % C4);
+  const int64_t q = i / C4;
+  const int y = (int)(q / W), x = (int)(q - (int64_t)y * W);
+  const float4 p = *reinterpret_cast<const float4 *>(
+      gp + ((size_t)(y >> 1) * (W >> 1) + (x >> 1)) * C + c);
+  const float4 k = *reinterpret_cast<const float4 *>(gs + (size_t)q * stride + off + c);
+  // (the product is rounded before the sum, as in k_grad_combine)
+  const float4 v = make_float4(__fadd_rn(__fmul_rn(0.25f, p.x), k.x),
+                               __fadd_rn(__fmul_rn(0.25f, p.y), k.y),
+                               __fadd_rn(__fmul_rn(0.25f, p.z), k.z),
+                               __fadd_rn(__fmul_rn(0.25f, p.w), k.w));
+  const size_t at = (size_t)q * C + c;
+  *reinterpret_cast<uint2 *>(out + at) = gate4(v, gate, at);
 }
 
 __global__ void k_pool2(const uint16_t *__restrict__ x, int H, int W, int C,
@@ -847,27 +997,33 @@ __global__ void k_features(const float *__restrict__ t, const float2 *__restrict
 unsigned blocks_of(int64_t n, int t) { return (unsigned)((n + t - 1) / t); }
 
 
-// the split of the weight-gradient GEMM: about 512 waves over the 16-pixel
-// row chunks of a Wr-wide image, and the byte offsets of its workspace parts
+// the split of the weight-gradient GEMM: about two workgroups per CU over the tiles
+// of an image, and the byte offsets of its workspace parts
 struct WgPlan {
-  int Wr, nchunks, cps, splits;
-  size_t part, part_b, gyT, ink, bytes;
+  int tiles_x, tiles, splits;
+  size_t part, part_b, bytes;
 };
 size_t round256(size_t b) { return (b + 255) & ~(size_t)255; }
 WgPlan wgrad_plan(int H, int W, int cin, int cout) {
   WgPlan p;
-  p.Wr = (W + 15) & ~15;
-  p.nchunks = H * (p.Wr / 16);
+  p.tiles_x = (W + kWgCols - 1) / kWgCols;
+  p.tiles = p.tiles_x * ((H + kWgRows - 1) / kWgRows);
   const int pairs = ((cin + 31) / 32) * ((cout + 31) / 32);
-  const int want = std::max(1, std::min(p.nchunks, (512 + pairs - 1) / pairs));
-  p.cps = (p.nchunks + want - 1) / want;
-  p.splits = (p.nchunks + p.cps - 1) / p.cps;
+  // The workspace's size is an interface callers allocate by: room for the partials
+  // of up to 512 / pairs shares of whole 16-pixel row chunks and for channel-major
+  // copies of both operands.  The copies are no longer made and the shares are of
+  // tiles, never more of them than that room holds.
+  const size_t Wr = (W + 15) & ~15;
+  const int chunks = (int)(H * (Wr / 16));
+  const int want = std::max(1, std::min(chunks, (512 + pairs - 1) / pairs));
+  const int cps = (chunks + want - 1) / want, room = (chunks + cps - 1) / cps;
+  p.splits = std::max(1, std::min(p.tiles, room));
   const size_t len = (size_t)cout * 9 * cin;
   p.part = 0;
-  p.part_b = round256(p.splits * len * sizeof(float));
-  p.gyT = p.part_b + round256((size_t)p.splits * cout * sizeof(float));
-  p.ink = p.gyT + round256((size_t)cout * H * p.Wr * sizeof(uint16_t));
-  p.bytes = p.ink + round256((size_t)3 * cin * (H + 2) * p.Wr * sizeof(uint16_t));
+  p.part_b = round256(room * len * sizeof(float));
+  p.bytes = p.part_b + round256((size_t)room * cout * sizeof(float)) +
+            round256((size_t)cout * H * Wr * sizeof(uint16_t)) +
+            round256((size_t)3 * cin * (H + 2) * Wr * sizeof(uint16_t));
   return p;
 }
 
@@ -914,6 +1070,36 @@ cgh_status cgh_net_conv3x3(const cgh_bf16 *x1, int32_t c1, int32_t up, const cgh
   return CGH_OK;
 }
 
+cgh_status cgh_net_conv3x3_pool2(const cgh_bf16 *x1, int32_t c1, int32_t up, const cgh_bf16 *x2,
+                                 int32_t c2, int32_t H, int32_t W, const cgh_bf16 *w,
+                                 const float *bias, int32_t cout, int32_t relu, cgh_bf16 *out16,
+                                 cgh_bf16 *pooled, void *stream) {
+  const cgh_status st = check_conv_shape(x1, c1, up, x2, c2, H, W);
+  if (st != CGH_OK) return st;
+  NET_CHECK(w && cout > 0 && cout % 8 == 0, "w NULL or cout = %d not a multiple of 8", cout);
+  NET_CHECK(out16 && pooled, "no output");
+  NET_CHECK(H % 2 == 0 && W % 2 == 0, "pooling needs even H, W");
+  NET_CHECK(al16(w) && al16(out16) && al16(pooled), "w, out16 and pooled must be 16-byte aligned");
+  ConvArgs a{x1, x2, w, bias, c1, c2, up, H, W, cout, relu, nullptr, out16, pooled, nullptr};
+  const hipError_t e = launch_conv(a, (hipStream_t)stream);
+  if (e != hipSuccess) return report(CGH_ERR_DEVICE, "conv3x3: %s", hipGetErrorString(e));
+  return CGH_OK;
+}
+
+cgh_status cgh_net_conv3x3_gated(const cgh_bf16 *gy, int32_t cout, int32_t H, int32_t W,
+                                 const cgh_bf16 *w_t, int32_t cin, const cgh_bf16 *gate,
+                                 cgh_bf16 *out16, void *stream) {
+  const cgh_status st = check_conv_shape(gy, cout, 0, nullptr, 0, H, W);
+  if (st != CGH_OK) return st;
+  NET_CHECK(w_t && cin > 0 && cin % 8 == 0, "w_t NULL or cin = %d not a multiple of 8", cin);
+  NET_CHECK(gate && out16, "gate/out16 is NULL");
+  NET_CHECK(al16(w_t) && al16(gate) && al16(out16), "w_t, gate and out16 must be 16-byte aligned");
+  ConvArgs a{gy, nullptr, w_t, nullptr, cout, 0, 0, H, W, cin, 0, nullptr, out16, nullptr, gate};
+  const hipError_t e = launch_conv(a, (hipStream_t)stream);
+  if (e != hipSuccess) return report(CGH_ERR_DEVICE, "conv3x3: %s", hipGetErrorString(e));
+  return CGH_OK;
+}
+
 cgh_status cgh_net_flip_weights(const cgh_bf16 *w, int32_t cout, int32_t cin, cgh_bf16 *w_t,
                                 void *stream) {
   NET_CHECK(w && w_t && cout > 0 && cin > 0, "bad arguments");
@@ -944,20 +1130,19 @@ cgh_status cgh_net_conv3x3_wgrad(const cgh_bf16 *x1, int32_t c1, int32_t up, con
   NET_CHECK(al16(workspace) && al16(gy), "workspace and gy must be 16-byte aligned");
   const int64_t len = (int64_t)cout * 9 * cin;
   char *base = (char *)workspace;
-  float *part = (float *)(base + pl.part), *part_b = (float *)(base + pl.part_b);
-  uint16_t *gyT = (uint16_t *)(base + pl.gyT), *ink = (uint16_t *)(base + pl.ink);
+  const WgradArgs wa{x1,  x2,   gy,        c1,        c2,        up,
+                     H,   W,    cout,      pl.tiles_x, pl.tiles, pl.splits,
+                     (float *)(base + pl.part), (float *)(base + pl.part_b)};
   hipStream_t s = (hipStream_t)stream;
-  hipLaunchKernelGGL(k_wg_gyT, dim3((pl.Wr + 63) / 64, H, (cout + 31) / 32), dim3(256), 0, s,
-                     reinterpret_cast<const uint16_t *>(gy), H, W, pl.Wr, cout, gyT);
-  hipLaunchKernelGGL(k_wg_ink, dim3((pl.Wr + 63) / 64, H + 2, (cin + 31) / 32), dim3(256), 0, s,
-                     reinterpret_cast<const uint16_t *>(x1), c1, up,
-                     reinterpret_cast<const uint16_t *>(x2), c2, H, W, pl.Wr, ink);
-  NET_LAUNCHED("conv3x3_wgrad staging");
-  hipLaunchKernelGGL(k_conv3x3_wgrad, dim3((cin + 31) / 32, (cout + 31) / 32, pl.splits), dim3(64),
-                     0, s, gyT, ink, H, pl.Wr, cin, cout, pl.cps, pl.nchunks, part, part_b);
+  hipLaunchKernelGGL(k_conv3x3_wgrad, dim3((cin + 31) / 32, (cout + 31) / 32, pl.splits),
+                     dim3(256), 0, s, wa);
   NET_LAUNCHED("conv3x3_wgrad");
-  hipLaunchKernelGGL(k_wgrad_reduce, dim3(blocks_of(std::max<int64_t>(len, cout), 16)),
-                     dim3(256), 0, s, part, part_b, pl.splits, len, cout, gw, gb);
+  if (pl.splits <= kFewShares)
+    hipLaunchKernelGGL(k_wgrad_reduce_few, dim3(blocks_of(len / 4 + cout, 256)), dim3(256), 0, s,
+                       wa.part, wa.part_b, pl.splits, len, cout, gw, gb);
+  else
+    hipLaunchKernelGGL(k_wgrad_reduce, dim3(blocks_of(std::max<int64_t>(len, cout), 16)),
+                       dim3(256), 0, s, wa.part, wa.part_b, pl.splits, len, cout, gw, gb);
   NET_LAUNCHED("wgrad_reduce");
   return CGH_OK;
 }
@@ -975,6 +1160,12 @@ cgh_status cgh_net_relu_grad(const float *g, const cgh_bf16 *a, int64_t count, c
                              void *stream) {
   NET_CHECK(count >= 0 && (count == 0 || (g && out)), "bad arguments");
   if (count == 0) return CGH_OK;
+  if (al16(g) && al16(a) && al16(out) && count % 4 == 0) {
+    hipLaunchKernelGGL(k_relu_grad4, dim3(blocks_of(count / 4, 256)), dim3(256), 0,
+                       (hipStream_t)stream, g, a, count / 4, out);
+    NET_LAUNCHED("relu_grad");
+    return CGH_OK;
+  }
   hipLaunchKernelGGL(k_relu_grad, dim3(blocks_of(count, 256)), dim3(256), 0,
                      (hipStream_t)stream, g, a, count, out);
   NET_LAUNCHED("relu_grad");
@@ -1008,6 +1199,33 @@ cgh_status cgh_net_grad_combine(const float *gp, const float *gs, int32_t stride
   hipLaunchKernelGGL(k_grad_combine, dim3(blocks_of((int64_t)H * W * C, 256)), dim3(256), 0,
                      (hipStream_t)stream, gp, gs, stride, off, H, W, C, out);
   NET_LAUNCHED("grad_combine");
+  return CGH_OK;
+}
+
+cgh_status cgh_net_up_adjoint_gated(const float *g, int32_t H, int32_t W, int32_t stride,
+                                    int32_t C, const cgh_bf16 *gate, cgh_bf16 *out,
+                                    void *stream) {
+  NET_CHECK(g && gate && out && H % 2 == 0 && W % 2 == 0 && H >= 2 && W >= 2 && C > 0 &&
+                stride >= C && C % 8 == 0 && stride % 8 == 0, "bad arguments");
+  NET_CHECK(al16(g) && al16(gate) && al16(out), "buffers must be 16-byte aligned");
+  hipLaunchKernelGGL(k_up_adjoint_gated,
+                     dim3(blocks_of((int64_t)(H / 2) * (W / 2) * (C / 4), 256)), dim3(256), 0,
+                     (hipStream_t)stream, g, H, W, stride, C, gate, out);
+  NET_LAUNCHED("up_adjoint_gated");
+  return CGH_OK;
+}
+
+cgh_status cgh_net_grad_combine_gated(const float *gp, const float *gs, int32_t stride,
+                                      int32_t off, int32_t H, int32_t W, int32_t C,
+                                      const cgh_bf16 *gate, cgh_bf16 *out, void *stream) {
+  NET_CHECK(gp && gs && gate && out && H >= 2 && W >= 2 && H % 2 == 0 && W % 2 == 0 && C > 0 &&
+                C % 8 == 0, "bad arguments");
+  NET_CHECK(off >= 0 && off + C <= stride && off % 8 == 0 && stride % 8 == 0,
+            "skip slice outside its rows");
+  NET_CHECK(al16(gp) && al16(gs) && al16(gate) && al16(out), "buffers must be 16-byte aligned");
+  hipLaunchKernelGGL(k_grad_combine_gated, dim3(blocks_of((int64_t)H * W * (C / 4), 256)),
+                     dim3(256), 0, (hipStream_t)stream, gp, gs, stride, off, H, W, C, gate, out);
+  NET_LAUNCHED("grad_combine_gated");
   return CGH_OK;
 }
 

@@ -66,6 +66,7 @@ class UNet:
         self.H, self.W, self.dev = H, W, torch.device(device)
         self.widths = tuple(widths)
         self.layers = architecture(c_in, widths, c_out)
+        self.by_name = {layer[0]: layer for layer in self.layers}
         self.L = binding.lib()
         # flat FP32 master weights: per layer [co][3][3][ci] then [co] bias
         self.off = {}
@@ -144,14 +145,16 @@ class UNet:
                                                   _p(self.wt16[name]), s))
 
     # -- passes ---------------------------------------------------------------
-    def _conv(self, name, x1, up, x2, out32=None, out16=None):
-        _, cu, cs, co, relu = next(l for l in self.layers if l[0] == name)
+    def _conv(self, name, x1, up, x2, out32=None, out16=None, pooled=None):
+        _, cu, cs, co, relu = self.by_name[name]
         lev = self._lev(name)
         h, w = self.H >> lev, self.W >> lev
-        self._chk(self.L.cgh_net_conv3x3(_p(x1), cu, int(up), _p(x2), cs, h, w,
-                                         _p(self._view(self.w16, name)),
-                                         _p(self._view(self.master, name + ".b")), co, int(relu),
-                                         _p(out32), _p(out16), self._stream()))
+        args = (_p(x1), cu, int(up), _p(x2), cs, h, w, _p(self._view(self.w16, name)),
+                _p(self._view(self.master, name + ".b")), co, int(relu))
+        if pooled is None:
+            self._chk(self.L.cgh_net_conv3x3(*args, _p(out32), _p(out16), self._stream()))
+        else:
+            self._chk(self.L.cgh_net_conv3x3_pool2(*args, _p(out16), _p(pooled), self._stream()))
 
     def forward(self, x16):
         """x16: BF16 [H][W][c_in] -> FP32 [H][W][c_out] (self.out)."""
@@ -159,12 +162,11 @@ class UNet:
         h = x16
         for l in range(nl):
             self._conv(f"enc{l}a", h, False, None, out16=self.act[f"enc{l}a"])
-            self._conv(f"enc{l}b", self.act[f"enc{l}a"], False, None, out16=self.act[f"enc{l}b"])
-            h = self.act[f"enc{l}b"]
-            if l < nl - 1:
-                self._chk(self.L.cgh_net_pool2(_p(h), self.H >> l, self.W >> l, self.widths[l],
-                                               _p(self.pooled[l]), self._stream()))
-                h = self.pooled[l]
+            # the encoder's second convolution also pools its output
+            pooled = self.pooled[l] if l < nl - 1 else None
+            self._conv(f"enc{l}b", self.act[f"enc{l}a"], False, None, out16=self.act[f"enc{l}b"],
+                       pooled=pooled)
+            h = self.act[f"enc{l}b"] if pooled is None else pooled
         for l in range(nl - 2, -1, -1):
             self._conv(f"dec{l}a", h, True, self.act[f"enc{l}b"], out16=self.act[f"dec{l}a"])
             self._conv(f"dec{l}b", self.act[f"dec{l}a"], False, None, out16=self.act[f"dec{l}b"])
@@ -176,16 +178,12 @@ class UNet:
         """Weight gradients (self.grad) for dL/d(out) = g_out (FP32 [H][W][c_out])."""
         nl = len(self.widths)
         s = self._stream()
-        dz = {}
 
-        def zbuf(name):
-            _, cu, cs, co, _ = next(l for l in self.layers if l[0] == name)
-            lev = self._lev(name)
-            return torch.empty(((self.H >> lev) * (self.W >> lev) * co,), dtype=torch.bfloat16,
-                               device=self.dev)
+        def zbuf(h, w, c):
+            return torch.empty((h, w, c), dtype=torch.bfloat16, device=self.dev)
 
         def wgrad(name, x1, up, x2, gy):
-            _, cu, cs, co, _ = next(l for l in self.layers if l[0] == name)
+            _, cu, cs, co, _ = self.by_name[name]
             lev = self._lev(name)
             self._chk(self.L.cgh_net_conv3x3_wgrad(
                 _p(x1), cu, int(up), _p(x2), cs, self.H >> lev, self.W >> lev, _p(gy), co,
@@ -193,7 +191,8 @@ class UNet:
                 _p(self.scratch), self.ws_bytes, s))
 
         def dgrad(name, gy):
-            _, cu, cs, co, _ = next(l for l in self.layers if l[0] == name)
+            """dL/d(input) of layer `name` in FP32"""
+            _, cu, cs, co, _ = self.by_name[name]
             lev = self._lev(name)
             h, w = self.H >> lev, self.W >> lev
             gx = torch.empty((h, w, cu + cs), dtype=torch.float32, device=self.dev)
@@ -201,46 +200,50 @@ class UNet:
                                              None, cu + cs, 0, _p(gx), None, s))
             return gx
 
-        def relu_in(name, g, act):
-            z = zbuf(name)
-            self._chk(self.L.cgh_net_relu_grad(_p(g), _p(act), g.numel(), _p(z), s))
+        def dgrad_relu(name, gy, act):
+            """the same through the ReLU that made the input `act`, in BF16"""
+            _, cu, cs, co, _ = self.by_name[name]
+            lev = self._lev(name)
+            h, w = self.H >> lev, self.W >> lev
+            z = zbuf(h, w, cu)
+            self._chk(self.L.cgh_net_conv3x3_gated(_p(gy), co, h, w, _p(self.wt16[name]), cu,
+                                                   _p(act), _p(z), s))
             return z
 
         # head (no ReLU on its output)
-        z = relu_in("head", g_out, None)
-        h_in = self.act["dec0b"] if nl > 1 else self.act["enc0b"]
-        wgrad("head", h_in, False, None, z)
-        g = dgrad("head", z)
+        z = zbuf(self.H, self.W, self.by_name["head"][3])
+        self._chk(self.L.cgh_net_relu_grad(_p(g_out), None, g_out.numel(), _p(z), s))
+        last = "dec0b" if nl > 1 else "enc0b"
+        wgrad("head", self.act[last], False, None, z)
+        z = dgrad_relu("head", z, self.act[last])
         skip_g = {}
         for l in range(0, nl - 1):
             name = f"dec{l}b"
-            z = relu_in(name, g, self.act[name])
             wgrad(name, self.act[f"dec{l}a"], False, None, z)
-            g = dgrad(name, z)
+            z = dgrad_relu(name, z, self.act[f"dec{l}a"])
             name = f"dec{l}a"
-            z = relu_in(name, g, self.act[name])
             below = self.act[f"dec{l + 1}b"] if l + 1 < nl - 1 else self.act[f"enc{nl - 1}b"]
             wgrad(name, below, True, self.act[f"enc{l}b"], z)
             gx = dgrad(name, z)
             cu = self.widths[l + 1]
             h, w = self.H >> l, self.W >> l
-            g = torch.empty((h // 2, w // 2, cu), dtype=torch.float32, device=self.dev)
-            self._chk(self.L.cgh_net_up_adjoint(_p(gx), h, w, cu + self.widths[l], cu, _p(g), s))
+            # the upsampled input's gradient, through the ReLU of the layer it came from
+            z = zbuf(h // 2, w // 2, cu)
+            self._chk(self.L.cgh_net_up_adjoint_gated(_p(gx), h, w, cu + self.widths[l], cu,
+                                                      _p(below), _p(z), s))
             skip_g[l] = (gx, cu + self.widths[l], cu)
         for l in range(nl - 1, -1, -1):
+            name = f"enc{l}b"
             if l < nl - 1:
+                # the pooled and the skipped gradient of the encoder's output
                 gx, stride, off = skip_g[l]
                 h, w = self.H >> l, self.W >> l
-                g2 = torch.empty((h, w, self.widths[l]), dtype=torch.float32, device=self.dev)
-                self._chk(self.L.cgh_net_grad_combine(_p(g), _p(gx), stride, off, h, w,
-                                                      self.widths[l], _p(g2), s))
-                g = g2
-            name = f"enc{l}b"
-            z = relu_in(name, g, self.act[name])
+                z = zbuf(h, w, self.widths[l])
+                self._chk(self.L.cgh_net_grad_combine_gated(
+                    _p(g), _p(gx), stride, off, h, w, self.widths[l], _p(self.act[name]), _p(z), s))
             wgrad(name, self.act[f"enc{l}a"], False, None, z)
-            g = dgrad(name, z)
+            z = dgrad_relu(name, z, self.act[f"enc{l}a"])
             name = f"enc{l}a"
-            z = relu_in(name, g, self.act[name])
             x_in = x16 if l == 0 else self.pooled[l - 1]
             wgrad(name, x_in, False, None, z)
             if l > 0:

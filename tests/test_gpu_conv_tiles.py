@@ -84,3 +84,83 @@ def test_conv_tiles_match_float64(H, W, c1, up, c2, cout):
     ref = reference(x1, x2, w, b, up, H, W)
     assert float((o32.double() - ref).norm() / ref.norm()) <= 2e-6
     assert torch.equal(o16, o32.clamp(min=0).bfloat16())
+
+
+WGRAD = [
+    # one tile and parts of one; shares of one and of several tiles; an upsampled first
+    # input; blocks of 32 channels that straddle the two inputs or end early
+    (5, 7, 8, 0, 0, 8), (16, 32, 32, 0, 0, 32), (33, 65, 24, 0, 0, 40), (18, 34, 40, 1, 24, 16),
+    (70, 130, 64, 1, 32, 64), (250, 500, 32, 0, 0, 24), (40, 40, 256, 0, 0, 256),
+]
+
+
+@pytest.mark.parametrize("H,W,c1,up,c2,cout", WGRAD)
+def test_weight_gradients_match_float64(H, W, c1, up, c2, cout):
+    """Bar: sums of at most 125,000 exact products: sqrt(125000) * 0.3 * 2^-24 = 6e-6
+    relative to the sum's scale if added one by one; the partial sums are shorter."""
+    say("wgrad", H, W, c1, up, c2, cout)
+    x1, x2, _, _ = inputs(H, W, c1, up, c2, cout)
+    cin = c1 + c2
+    g = torch.Generator(device="cuda")
+    g.manual_seed(9)
+    gy = torch.randn(H, W, cout, generator=g, device="cuda").bfloat16()
+    L = binding.lib()
+    nb = L.cgh_net_wgrad_workspace(H, W, cin, cout)
+    ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+    gw = torch.empty(cout, 9, cin, device="cuda")
+    gb = torch.empty(cout, device="cuda")
+    for k in range(2):
+        binding._check(L.cgh_net_conv3x3_wgrad(ptr(x1), c1, up, ptr(x2), c2, H, W, ptr(gy), cout,
+                                               ptr(gw), ptr(gb), ptr(ws), nb, stream()))
+        if k == 0:
+            first = gw.clone()
+    assert torch.equal(first, gw)
+    x = x1.double()
+    if up:
+        x = x.repeat_interleave(2, 0).repeat_interleave(2, 1)
+    if x2 is not None:
+        x = torch.cat([x, x2.double()], -1)
+    xp = torch.nn.functional.pad(x, (0, 0, 1, 1, 1, 1))
+    g64 = gy.double().reshape(H * W, cout)
+    ref = torch.stack([g64.T @ xp[t // 3:t // 3 + H, t % 3:t % 3 + W].reshape(H * W, cin)
+                       for t in range(9)], 1)
+    assert float((gw.double() - ref).norm() / ref.norm()) <= 6e-6
+    assert float((gb.double() - g64.sum(0)).norm() / g64.sum(0).norm()) <= 6e-6
+
+
+def test_fused_passes_equal_their_parts():
+    """The pooled convolution, the gated input adjoint, the gated upsampling adjoint
+    and the gated combination give the values of the separate calls."""
+    say("fused passes")
+    L = binding.lib()
+    H, W, c, co = 38, 70, 48, 64
+    x1, _, w, b = inputs(H, W, c, 0, 0, co)
+    bf = lambda *s: torch.zeros(*s, dtype=torch.bfloat16, device="cuda")
+    o, o2, p, p2 = bf(H, W, co), bf(H, W, co), bf(H // 2, W // 2, co), bf(H // 2, W // 2, co)
+    chk = binding._check
+    chk(L.cgh_net_conv3x3(ptr(x1), c, 0, None, 0, H, W, ptr(w), ptr(b), co, 1, None, ptr(o), stream()))
+    chk(L.cgh_net_pool2(ptr(o), H, W, co, ptr(p), stream()))
+    chk(L.cgh_net_conv3x3_pool2(ptr(x1), c, 0, None, 0, H, W, ptr(w), ptr(b), co, 1, ptr(o2), ptr(p2),
+                                stream()))
+    assert torch.equal(o, o2) and torch.equal(p, p2)
+    gate = torch.randn(H, W, co, device="cuda").clamp(min=0).bfloat16()
+    gate[0, 0, :3] = torch.tensor([float("inf"), float("nan"), -0.0])
+    g32, z, z2 = torch.empty(H, W, co, device="cuda"), bf(H, W, co), bf(H, W, co)
+    chk(L.cgh_net_conv3x3(ptr(x1), c, 0, None, 0, H, W, ptr(w), None, co, 0, ptr(g32), None, stream()))
+    chk(L.cgh_net_relu_grad(ptr(g32), ptr(gate), g32.numel(), ptr(z), stream()))
+    chk(L.cgh_net_conv3x3_gated(ptr(x1), c, H, W, ptr(w), co, ptr(gate), ptr(z2), stream()))
+    assert torch.equal(z, z2)
+    # the first 40 of 64 channels through the upsampling, the other 24 through the skip
+    up, small = torch.empty(H // 2, W // 2, 40, device="cuda"), gate[:H // 2, :W // 2, :40].contiguous()
+    y, y2 = bf(H // 2, W // 2, 40), bf(H // 2, W // 2, 40)
+    chk(L.cgh_net_up_adjoint(ptr(g32), H, W, co, 40, ptr(up), stream()))
+    chk(L.cgh_net_relu_grad(ptr(up), ptr(small), up.numel(), ptr(y), stream()))
+    chk(L.cgh_net_up_adjoint_gated(ptr(g32), H, W, co, 40, ptr(small), ptr(y2), stream()))
+    assert torch.equal(y, y2)
+    gp = torch.randn(H // 2, W // 2, 24, device="cuda")
+    act = gate[:, :, :24].contiguous()
+    cmb, q, q2 = torch.empty(H, W, 24, device="cuda"), bf(H, W, 24), bf(H, W, 24)
+    chk(L.cgh_net_grad_combine(ptr(gp), ptr(g32), co, 40, H, W, 24, ptr(cmb), stream()))
+    chk(L.cgh_net_relu_grad(ptr(cmb), ptr(act), cmb.numel(), ptr(q), stream()))
+    chk(L.cgh_net_grad_combine_gated(ptr(gp), ptr(g32), co, 40, H, W, 24, ptr(act), ptr(q2), stream()))
+    assert torch.equal(q, q2)
