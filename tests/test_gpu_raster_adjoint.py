@@ -1,0 +1,50 @@
+"""The rasterizer adjoint's walk over two pixels of a row at a time, for every tile
+shape and channel count, where its boxes are odd: Gaussians one to three pixels wide,
+some beside tile and canvas edges (the box grows by a column on the side that has
+room), and some that fill whole tiles.
+
+Tolerance: the pair sums are FP32 sums of at most 256 products per tile, 3e-7 of the
+sum of the terms' sizes; more comes from the FP32 geometry, whose inverse covariance
+of a Gaussian with axes 12 : 1 (condition 144) is off by about 3 * 144 * 2^-24 = 3e-5,
+times the exponent, up to 6.5 at the rim of the support: 2e-4 there.  The bar for a
+whole parameter group is 3e-4."""
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2511_15022_amd import binding, synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("tile", binding.TILE_SHAPES)
+@pytest.mark.parametrize("C", [1, 2, 3, 4])
+def test_odd_boxes_match_oracle(O, tile, C):
+    print("[gpu-case] adjoint boxes", tile, C, flush=True)
+    sys.stdout.flush()
+    H, W, n = 43, 71, 240
+    lam = [639e-9, 515e-9, 473e-9, 450e-9][:C]
+    p = synth.params(5, n, H, W, C)
+    rng = np.random.default_rng(6)
+    # means on a grid of tile corners, up to 1.5 pixels off; two scales in 0.15 .. 12
+    x = np.clip(rng.integers(0, 10, n) * 8 + rng.uniform(-1.5, 1.5, n), 0.2, W - 0.2)
+    y = np.clip(rng.integers(0, 6, n) * 8 + rng.uniform(-1.5, 1.5, n), 0.2, H - 0.2)
+    dt = p["mean_pre"].dtype
+    p["mean_pre"] = np.arctanh(np.stack([2 * x / W - 1, 2 * y / H - 1], -1)).astype(dt)
+    p["log_scale"] = np.where(rng.random((n, 1)) < 0.7, rng.uniform(-3.0, -0.5, (n, 2)),
+                              rng.uniform(0.0, 2.5, (n, 2))).astype(dt)
+    opt = O.Optics(H, W, C, 2 * H + 4, 2 * W + 2, 8e-6, lam, [2e-3])
+    ctx = binding.Context(H, W, C, 8e-6, lam, [2e-3], pad=(2 * H + 4, 2 * W + 2),
+                          max_gaussians=n, max_pairs=64 * n, tile=tile)
+    ref = O.forward_backward(p, synth.target(7, C, H, W), opt)
+    P = binding.pack(p, device="cuda")
+    ctx.rasterize(P, n)
+    gf = torch.from_numpy(ref["grad_field"].astype(np.complex64)).cuda()
+    g = binding.unpack(ctx.rasterize_adjoint(P, n, gf).cpu(), n, C)
+    for k in binding.PARAM_KEYS:
+        a, b = g[k].numpy(), ref["grads"][k]
+        err = np.linalg.norm((a - b).ravel()) / np.linalg.norm(b.ravel())
+        print("[gpu-case]", k, err, flush=True)
+        assert err <= 3e-4, (k, err)
