@@ -22,6 +22,8 @@
 // chains longer than the tables below.
 #pragma once
 
+#include <algorithm>
+
 #include "cgh_internal.h"
 #include "fft_reg.h"
 
@@ -133,14 +135,12 @@ constexpr int row_plan_cost(int M, int P, int T, const RowPlan &p) {
 
 constexpr RowPlan row_plan(int M, int P, int T) {
   if (P == 4 && T == 512) {
-    // measured: 960 (1080p) against 15 16 4, 12 8 10, 8 12 10 and 10 12 8; 1024, 512
-    // and 256 (serving pads) against 16 16 4, 16 16 2 and 16 16; 1920 (4K) is the
-    // plan of fewest stages, odd radix first
+    // measured: 960 (1080p) against 8 8 15, 8 15 8, 10 8 12, 12 8 10 and 16 4 15; 1920
+    // (4K) against 8 16 15, 16 8 15, 16 15 8, 12 16 10 and 15 8 16; 1024 (serving pads)
+    // against 16 16 4
     if (M == 960) return {3, {15, 8, 8, 1}};
     if (M == 1920) return {3, {15, 16, 8, 1}};
     if (M == 1024) return {3, {8, 8, 16, 1}};
-    if (M == 512) return {3, {8, 8, 8, 1}};
-    if (M == 256) return {3, {4, 8, 8, 1}};
   }
   RowPlan best{0, {1, 1, 1, 1}};
   int cost = 1 << 29;
@@ -174,10 +174,13 @@ constexpr RowPlan row_plan(int M, int P, int T) {
   return best;
 }
 
-// threads per row workgroup: about eight values per thread, 512 at most
+// Threads per row workgroup: 8 to 16 values per thread, 512 threads at most.  Measured
+// (row_loss, row_inv): padded 2048 with 512 threads 31.5 / 2 and 12.0 us, with 256
+// 30.0 / 2 and 11.2 us (640 x 1024 RGB); 2560 17.5 and 17.2 us; 3840 60.7 and 28.5
+// against 60.5 and 30.8 us (1080p RGB).
 constexpr int row_threads(int M, int P) {
   const int n = P * M;
-  return n >= 2000 ? 512 : n >= 900 ? 256 : n >= 400 ? 128 : 64;
+  return n >= 3200 ? 512 : n >= 900 ? 256 : n >= 400 ? 128 : 64;
 }
 
 constexpr bool smooth_c(int n) {
@@ -207,6 +210,16 @@ inline int split_of(int n, int used, bool (*built)(int, int)) {
 
 // waves per SIMD that the LDS of a workgroup of 512 threads leaves room for
 constexpr int lds_waves(int values) { return values * 8 + 1024 > 80 * 1024 ? 2 : 4; }
+// Row workgroups that a CU's LDS holds, and the lengths whose forward rows are
+// pipelined: where only one or two workgroups fit, they do not cover each other's
+// loads, so a workgroup takes several rows and loads the next one's samples while it
+// transforms this one's (4K RGB rows of 7680: 144 us without, 127 us with; with four
+// workgroups of 3840 per CU it costs, 36 against 38 us).  The passes that read the
+// spectrum do not gain from it (row_inv 172 us without, 185 us with; row_loss 247 and
+// 284 us: their next row costs 30 registers per thread).
+constexpr int row_groups(int M, int P) { return 160 * 1024 / (((P + 1) * M) * 8 + 128); }
+constexpr bool row_pipe(int M, int P) { return row_groups(M, P) <= 2; }
+constexpr int row_waves(int M, int P) { return lds_waves((P + 1) * M); }
 
 // ----------------------------------------------------------------------------
 // row passes: one row per workgroup, chain p at buf[P m + p], which is the row in
@@ -219,15 +232,111 @@ __device__ __forceinline__ int paired_row(int b, int rows) {
   return (b & ~15) + 2 * (b & 7) + ((b >> 3) & 1);
 }
 
-template <int M, int P, int T, int DIR, int S = 0>
+// stages S .. END - 1 of a row's chains, LDS to LDS
+template <int M, int P, int T, int DIR, int S, int END>
 __device__ __forceinline__ void row_stages(float2 *__restrict__ buf,
                                            const float2 *__restrict__ tw, int tid) {
   constexpr RowPlan p = row_plan(M, P, T);
-  if constexpr (S < p.n) {
+  if constexpr (S < END) {
     constexpr int ns = (S > 0 ? p.r[0] : 1) * (S > 1 ? p.r[1] : 1) * (S > 2 ? p.r[2] : 1);
     cstage<p.r[S], DIR, P, T, M, ns>(buf, tw, tid);
-    row_stages<M, P, T, DIR, S + 1>(buf, tw, tid);
+    row_stages<M, P, T, DIR, S + 1, END>(buf, tw, tid);
   }
+}
+
+// Butterfly i of a radix-R stage over P interleaved chains (i = P j + p) reads, in the
+// first stage, and writes, in the last, the row's elements i + q (P M / R): neighbouring
+// threads have neighbouring elements, so the first stage of a transform loads its
+// butterflies from memory and the last one stores them there, with no pass through LDS
+// for the exchange with memory.  Before (rows staged in LDS on both sides) and now: 4K
+// RGB row_loss 311 -> 246 us, row_inv 184 -> 172 us, row_fwd 147 -> 127 us (144 us
+// without the pipeline); 1080p RGB 63.5 -> 60.6, 31.0 -> 28.4 and 36.5 -> 36.1 us.  The
+// passes move 896, 597 and 597 MB at 4K: 3.6, 3.5 and 4.7 TB/s, against 5.2 TB/s of a
+// large copy; the reads of 64-byte pieces of the spectrum bind the first two.
+template <int M, int P, int T, int R>
+struct EdgeStage {
+  static constexpr int NB = M / R, ITEMS = NB * P, IT = (ITEMS + T - 1) / T;
+  // element i + q ITEMS of row y of a channel's column-tiled spectrum
+  // [ceil(P M / 8)][H][8]; where ITEMS is a multiple of 8, q moves the (uniform) base only
+  template <class F2>
+  static __device__ __forceinline__ F2 &at(F2 *Sc, int H, int y, int i, int q) {
+    if constexpr (ITEMS % 8 == 0)
+      return at32(Sc + (size_t)q * (ITEMS / 8) * H * 8, ((i >> 3) * H + y) * 8 + (i & 7));
+    const int x = i + q * ITEMS;
+    return at32(Sc, ((x >> 3) * H + y) * 8 + (x & 7));
+  }
+  static __device__ __forceinline__ void load(float2 (&v)[IT][R], const float2 *Sc, int H, int y,
+                                              int tid) {
+#pragma unroll
+    for (int it = 0; it < IT; ++it)
+#pragma unroll
+      for (int q = 0; q < R; ++q) v[it][q] = at(Sc, H, y, min(tid + it * T, ITEMS - 1), q);
+  }
+  // the first stage: registers to LDS
+  template <int DIR>
+  static __device__ __forceinline__ void first(float2 (&v)[IT][R], float2 *buf, int tid) {
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      const int i = tid + it * T;
+      if (ITEMS % T == 0 || i < ITEMS) {
+        RFft<R, DIR>::run(v[it]);
+        const int b = i % P, j = i / P;
+        static_for<0, R>([&](auto qc) {
+          constexpr int q = decltype(qc)::value;
+          buf[(j * R + q) * P + b] = v[it][q];
+        });
+      }
+    }
+  }
+  // the last stage: LDS to memory
+  template <int DIR>
+  static __device__ __forceinline__ void last(const float2 *buf, const float2 *tw, float2 *Sc,
+                                              int H, int y, int tid) {
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      const int i = tid + it * T;
+      if (ITEMS % T == 0 || i < ITEMS) {
+        const int b = i % P, j = i / P;
+        float2 v[R];
+        static_for<0, R>([&](auto qc) {
+          constexpr int q = decltype(qc)::value;
+          v[q] = buf[(j + q * NB) * P + b];
+        });
+        if constexpr (NB > 1) {
+          static_for<1, R>([&](auto qc) {
+            constexpr int q = decltype(qc)::value;
+            float2 w = tw[q * j];
+            if constexpr (DIR > 0) w.y = -w.y;
+            v[q] = cmul(v[q], w);
+          });
+        }
+        RFft<R, DIR>::run(v);
+        static_for<0, R>([&](auto qc) {
+          constexpr int q = decltype(qc)::value;
+          at(Sc, H, y, i, q) = v[q];
+        });
+      }
+    }
+  }
+};
+template <int M, int P, int T>
+using FirstStage = EdgeStage<M, P, T, row_plan(M, P, T).r[0]>;
+template <int M, int P, int T>
+using LastStage = EdgeStage<M, P, T, row_plan(M, P, T).r[row_plan(M, P, T).n - 1]>;
+
+// Keeps what is computed from a value inside the loop over the rows: addresses that
+// the compiler would otherwise hold in registers from one row to the next.
+__device__ __forceinline__ void opaque(int &v) { asm volatile("" : "+v"(v)); }
+
+// Waits for values loaded earlier (they become values of this point).  A pipelined
+// row waits for its successor's loads here, before its own stores: loads and stores
+// complete in issue order, and a wait after the stores would wait for them too.
+template <int A, int B>
+__device__ __forceinline__ void arrived(float2 (&v)[A][B]) {
+#pragma unroll
+  for (int a = 0; a < A; ++a)
+#pragma unroll
+    for (int b = 0; b < B; ++b) asm volatile("" : "+v"(v[a][b].x), "+v"(v[a][b].y));
 }
 
 // M-entry table exp(-2 pi i e / M), stored contiguously after the P M table
@@ -241,36 +350,6 @@ __device__ __forceinline__ void load_chain_table(float2 *tw, const float2 *__res
 #pragma unroll
   for (int k = 0; k < KT; ++k)
     if (KT * T == M || tid + k * T < M) tw[tid + k * T] = tv[k];
-}
-
-// one row y of channel base Sc (column-tiled [ceil(Wp / 8)][H][8]) <-> buf in natural order
-template <int N, int T>
-__device__ __forceinline__ void load_chain_row(float2 *buf, const float2 *Sc, int H, int y,
-                                               int tid) {
-  constexpr int K = (N + T - 1) / T;
-  float2 v[K];
-#pragma unroll
-  for (int k = 0; k < K; ++k) {
-    const int x = min(tid + k * T, N - 1);
-    v[k] = at32(Sc, ((x >> 3) * H + y) * 8 + (x & 7));
-  }
-#pragma unroll
-  for (int k = 0; k < K; ++k)
-    if (K * T == N || tid + k * T < N) buf[tid + k * T] = v[k];
-}
-
-template <int N, int T>
-__device__ __forceinline__ void store_chain_row(const float2 *buf, float2 *Sc, int H, int y,
-                                                int tid) {
-  constexpr int K = (N + T - 1) / T;
-  float2 v[K];
-#pragma unroll
-  for (int k = 0; k < K; ++k) v[k] = buf[min(tid + k * T, N - 1)];
-#pragma unroll
-  for (int k = 0; k < K; ++k) {
-    const int x = tid + k * T;
-    if (K * T == N || x < N) at32(Sc, ((x >> 3) * H + y) * 8 + (x & 7)) = v[k];
-  }
 }
 
 // the chain inputs at m = n from the samples a = x[n] and (P = 4) b = x[n + M]
@@ -307,60 +386,78 @@ __device__ __forceinline__ void chain_outputs(const float2 *buf, int n, float2 w
   }
 }
 
+#define CGH_ROW_KERNEL(M, P)                    \
+  __global__ __launch_bounds__(row_threads(M, P)) \
+      __attribute__((amdgpu_waves_per_eu(row_waves(M, P)))) void
+
 // F1: field rows (zero-extended to Wp = P M) -> forward FFT -> S
 template <int M, int P>
-__global__ __launch_bounds__(row_threads(M, P))
-__attribute__((amdgpu_waves_per_eu(lds_waves((P + 1) * M)))) void k_row_fwd_q(const float2 *__restrict__ field, int H, int W, int rows,
-            const float2 *__restrict__ twf_x, float2 *__restrict__ S) {
+CGH_ROW_KERNEL(M, P) k_row_fwd_q(const float2 *__restrict__ field, int H, int W, int rows,
+                                 const float2 *__restrict__ twf_x, float2 *__restrict__ S) {
   constexpr int T = row_threads(M, P), K = (M + T - 1) / T, Wt = (P * M + 7) / 8;
+  constexpr RowPlan pl = row_plan(M, P, T);
+  constexpr bool PIPE = row_pipe(M, P);
   __shared__ float2 buf[P * M];
   __shared__ float2 tw[M];
-  const int tid = threadIdx.x;
-  const int R = paired_row(blockIdx.x, rows), c = R / H, y = R - c * H;
+  int tid = threadIdx.x;
   load_chain_table<M, P, T>(tw, twf_x, tid);
-  {
-    const float2 *f = field + ((size_t)c * H + y) * W;
-    float2 av[K], bv[K], wv[K];
+  float2 wv[K], ab[2][K];
+  auto load = [&](int blk) {
+    const float2 *f = field + (size_t)paired_row(blk, rows) * W;  // (row R = c H + y)
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       const int n = min(tid + k * T, M - 1);
-      av[k] = at32(f, min(n, W - 1));
-      bv[k] = P == 4 ? at32(f, min(n + M, W - 1)) : make_float2(0.f, 0.f);
-      wv[k] = at32(twf_x, n);
+      ab[0][k] = at32(f, min(n, W - 1));
+      ab[1][k] = P == 4 ? at32(f, min(n + M, W - 1)) : make_float2(0.f, 0.f);
     }
+  };
+#pragma unroll
+  for (int k = 0; k < K; ++k) wv[k] = at32(twf_x, min(tid + k * T, M - 1));
+  load(blockIdx.x);
+  if constexpr (PIPE) arrived(ab);
+  for (int blk = blockIdx.x; blk < rows; blk += gridDim.x) {
+    if constexpr (PIPE) opaque(tid);
+    const int R = paired_row(blk, rows), c = R / H, y = R - c * H;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       const int n = tid + k * T;
       if (K * T == M || n < M) {
-        const float2 a = n < W ? av[k] : make_float2(0.f, 0.f);
-        const float2 b = n + M < W ? bv[k] : make_float2(0.f, 0.f);
+        const float2 a = n < W ? ab[0][k] : make_float2(0.f, 0.f);
+        const float2 b = n + M < W ? ab[1][k] : make_float2(0.f, 0.f);
         chain_inputs<P>(buf, n, a, b, wv[k]);
       }
     }
+    lds_sync();
+    row_stages<M, P, T, -1, 0, pl.n - 2>(buf, tw, tid);
+    if constexpr (PIPE) load(min(blk + (int)gridDim.x, rows - 1));
+    row_stages<M, P, T, -1, std::max(pl.n - 2, 0), pl.n - 1>(buf, tw, tid);
+    if constexpr (PIPE) arrived(ab);
+    LastStage<M, P, T>::template last<-1>(buf, tw, S + (size_t)c * Wt * H * 8, H, y, tid);
+    if constexpr (!PIPE) break;
+    lds_sync();
   }
-  __syncthreads();
-  row_stages<M, P, T, -1>(buf, tw, tid);
-  store_chain_row<P * M, T>(buf, S + (size_t)c * Wt * H * 8, H, y, tid);
 }
 
 // B2: S -> inverse FFT -> first W values of each row
 template <int M, int P>
-__global__ __launch_bounds__(row_threads(M, P))
-__attribute__((amdgpu_waves_per_eu(lds_waves((P + 1) * M)))) void k_row_inv_q(const float2 *__restrict__ S, int H, int W, int rows,
-            const float2 *__restrict__ twf_x, float2 *__restrict__ out) {
+CGH_ROW_KERNEL(M, P) k_row_inv_q(const float2 *__restrict__ S, int H, int W, int rows,
+                                 const float2 *__restrict__ twf_x, float2 *__restrict__ out) {
   constexpr int T = row_threads(M, P), K = (M + T - 1) / T, Wt = (P * M + 7) / 8;
+  constexpr RowPlan pl = row_plan(M, P, T);
+  using First = FirstStage<M, P, T>;
   __shared__ float2 buf[P * M];
   __shared__ float2 tw[M];
   const int tid = threadIdx.x;
-  const int R = paired_row(blockIdx.x, rows), c = R / H, y = R - c * H;
   load_chain_table<M, P, T>(tw, twf_x, tid);
-  load_chain_row<P * M, T>(buf, S + (size_t)c * Wt * H * 8, H, y, tid);
-  float2 wv[K];
+  const int R = paired_row(blockIdx.x, rows), c = R / H, y = R - c * H;
+  float2 wv[K], v[First::IT][pl.r[0]];
+  First::load(v, S + (size_t)c * Wt * H * 8, H, y, tid);
 #pragma unroll
   for (int k = 0; k < K; ++k) wv[k] = at32(twf_x, min(tid + k * T, M - 1));
+  First::template first<+1>(v, buf, tid);
   lds_sync();
-  row_stages<M, P, T, +1>(buf, tw, tid);
-  float2 *o = out + ((size_t)c * H + y) * W;
+  row_stages<M, P, T, +1, 1, pl.n>(buf, tw, tid);
+  float2 *o = out + (size_t)R * W;
 #pragma unroll
   for (int k = 0; k < K; ++k) {
     const int n = tid + k * T;
@@ -379,27 +476,32 @@ __attribute__((amdgpu_waves_per_eu(lds_waves((P + 1) * M)))) void k_row_inv_q(co
 // zero-extended, forward FFT, back into S.  One FP64 partial sum of the loss per
 // row into loss_part.
 template <int M, int P>
-__global__ __launch_bounds__(row_threads(M, P))
-__attribute__((amdgpu_waves_per_eu(lds_waves((P + 1) * M)))) void k_row_loss_q(float2 *__restrict__ S, int H, int W, int rows, const float2 *__restrict__ twf_x,
-             const float *__restrict__ target, const float *__restrict__ grad_I,
-             const float *__restrict__ mask, int mcg, float *__restrict__ intensity,
-             float2 *__restrict__ u_out, double *__restrict__ loss_part, float gscale,
-             int make_grad) {
+CGH_ROW_KERNEL(M, P) k_row_loss_q(float2 *__restrict__ S, int H, int W, int rows,
+                                  const float2 *__restrict__ twf_x,
+                                  const float *__restrict__ target,
+                                  const float *__restrict__ grad_I,
+                                  const float *__restrict__ mask, int mcg,
+                                  float *__restrict__ intensity, float2 *__restrict__ u_out,
+                                  double *__restrict__ loss_part, float gscale, int make_grad) {
   constexpr int T = row_threads(M, P), K = (M + T - 1) / T, Wt = (P * M + 7) / 8, J = P / 2;
+  constexpr RowPlan pl = row_plan(M, P, T);
+  using First = FirstStage<M, P, T>;
   __shared__ float2 buf[P * M];
   __shared__ float2 tw[M];
   __shared__ double red[T / 64];
   const int tid = threadIdx.x;
+  load_chain_table<M, P, T>(tw, twf_x, tid);
   const int R = paired_row(blockIdx.x, rows), c = R / H, y = R - c * H;
   float2 *Sc = S + (size_t)c * Wt * H * 8;
-  load_chain_table<M, P, T>(tw, twf_x, tid);
-  load_chain_row<P * M, T>(buf, Sc, H, y, tid);
-  if (mask) mask += (size_t)(c / mcg) * H * W;
-  // per-element inputs at n and n + M, fetched before the transform so that
-  // their latency overlaps it
+  float2 v[First::IT][pl.r[0]];
+  First::load(v, Sc, H, y, tid);
+  // per-element inputs at n and n + M and the chains' twiddles, fetched before the
+  // transform so that their latency overlaps it
   const float *tsrc = target ? target : grad_I;
-  const size_t row = ((size_t)c * H + y) * W;
+  const size_t row = (size_t)R * W;
+  if (mask) mask += ((size_t)(c / mcg) * H + y) * W;
   float tv[J][K], mv[J][K];
+  float2 wv[K];
 #pragma unroll
   for (int k = 0; k < K; ++k) {
     const int n = min(tid + k * T, M - 1);
@@ -407,19 +509,20 @@ __attribute__((amdgpu_waves_per_eu(lds_waves((P + 1) * M)))) void k_row_loss_q(f
     for (int j = 0; j < J; ++j) {
       const int x = min(n + j * M, W - 1);
       tv[j][k] = tsrc ? tsrc[row + x] : 0.f;
-      mv[j][k] = mask ? mask[(size_t)y * W + x] : 0.f;
+      mv[j][k] = mask ? mask[x] : 0.f;
     }
+    wv[k] = at32(twf_x, n);
   }
+  First::template first<+1>(v, buf, tid);
   lds_sync();
-  row_stages<M, P, T, +1>(buf, tw, tid);
+  row_stages<M, P, T, +1, 1, pl.n>(buf, tw, tid);
   double acc = 0.0;
 #pragma unroll
   for (int k = 0; k < K; ++k) {
     const int n = tid + k * T;
     if (K * T == M || n < M) {
-      const float2 w1 = at32(twf_x, n);
       float2 u[2];
-      chain_outputs<P>(buf, n, w1, u[0], u[1]);
+      chain_outputs<P>(buf, n, wv[k], u[0], u[1]);
       float f[2] = {0.f, 0.f};
 #pragma unroll
       for (int j = 0; j < J; ++j) {
@@ -440,23 +543,22 @@ __attribute__((amdgpu_waves_per_eu(lds_waves((P + 1) * M)))) void k_row_loss_q(f
       }
       if (make_grad)
         chain_inputs<P>(buf, n, make_float2(f[0] * u[0].x, f[0] * u[0].y),
-                        make_float2(f[1] * u[1].x, f[1] * u[1].y), w1);
+                        make_float2(f[1] * u[1].x, f[1] * u[1].y), wv[k]);
     }
   }
   if (target) {
     for (int d = 32; d > 0; d >>= 1) acc += __shfl_down(acc, d, 64);
     if ((tid & 63) == 0) red[tid >> 6] = acc;
-    __syncthreads();
-    if (tid == 0) {
-      double sum = 0.0;
-      for (int w = 0; w < T / 64; ++w) sum += red[w];
-      loss_part[R] = sum;
-    }
+  }
+  lds_sync();
+  if (target && tid == 0) {
+    double sum = 0.0;
+    for (int w = 0; w < T / 64; ++w) sum += red[w];
+    loss_part[R] = sum;
   }
   if (make_grad) {
-    __syncthreads();
-    row_stages<M, P, T, -1>(buf, tw, tid);
-    store_chain_row<P * M, T>(buf, Sc, H, y, tid);
+    row_stages<M, P, T, -1, 0, pl.n - 1>(buf, tw, tid);
+    LastStage<M, P, T>::template last<-1>(buf, tw, Sc, H, y, tid);
   }
 }
 
@@ -642,7 +744,7 @@ struct RowArgs {
   const float2 *field;
   float2 *S;
   float2 *out;
-  int H, W, rows;
+  int H, W, rows, num_cu;
   const float2 *twf_x;
   const float *target, *grad_I, *mask;
   int mcg;

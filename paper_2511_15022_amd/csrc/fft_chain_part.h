@@ -2,6 +2,7 @@
 // file defines CGH_CHAIN_PART, and the kernels of the chain lengths whose index
 // is that part modulo kChainParts are compiled here (they are split only so
 // that they compile in parallel).
+#include <algorithm>
 #include <array>
 #include <utility>
 
@@ -43,9 +44,12 @@ constexpr auto kColLengths = part_lengths<col_chain>();
 template <int M, int P>
 void launch_row(const RowArgs &a, hipStream_t s) {
   static_assert(row_plan(M, P, row_threads(M, P)).n > 0, "no row plan");
+  // pipelined rows: as many workgroups as run at once, each taking every grid-th row
+  // (a multiple of 16 workgroups, so that a pair of rows stays on one XCD)
+  const int most = row_pipe(M, P) ? std::max(16, a.num_cu * row_groups(M, P) / 16 * 16) : a.rows;
   const dim3 grid(a.rows), block(row_threads(M, P));
   if (a.pass == 0)
-    hipLaunchKernelGGL((k_row_fwd_q<M, P>), grid, block, 0, s, a.field, a.H, a.W, a.rows, a.twf_x,
+    hipLaunchKernelGGL((k_row_fwd_q<M, P>), dim3(std::min(a.rows, most)), block, 0, s, a.field, a.H, a.W, a.rows, a.twf_x,
                        a.S);
   else if (a.pass == 1)
     hipLaunchKernelGGL((k_row_inv_q<M, P>), grid, block, 0, s, a.S, a.H, a.W, a.rows, a.twf_x,

@@ -659,6 +659,7 @@ static RowArgs row_args(const Ctx &c, int pass) {
   a.H = c.H;
   a.W = c.W;
   a.rows = row_blocks(c);
+  a.num_cu = c.num_cu;
   a.twf_x = c.twf_x;
   return a;
 }

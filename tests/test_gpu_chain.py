@@ -100,3 +100,25 @@ def test_transfer_table_follows_the_optics():
     a.set_optics([473e-9, 639e-9], [-3e-3])
     for ch in range(2):
         assert torch.equal(a.get_transfer(ch, 0), b.get_transfer(ch, 0))
+
+
+PIPED = [
+    # (H, W, Hp, Wp, C): rows of two workgroups per CU and one, whose forward pass takes
+    # several rows per workgroup; fewer rows than workgroups, and a remainder of rows
+    (5, 2600, 64, 5400, 1),
+    (257, 2700, 540, 5400, 2),
+    (181, 4000, 384, 8000, 3),
+    (523, 3645, 1080, 7290, 1),
+]
+
+
+@pytest.mark.parametrize("H,W,Hp,Wp,C", PIPED)
+def test_long_rows_match_oracle(O, H, W, Hp, Wp, C):
+    say("long rows", H, W, Hp, Wp, C)
+    lam = [639e-9, 515e-9, 473e-9][:C]
+    rng = np.random.default_rng(3)
+    f = (rng.standard_normal((C, H, W)) + 1j * rng.standard_normal((C, H, W))).astype(np.complex64)
+    opt = O.Optics(H, W, C, Hp, Wp, 8e-6, lam, [2e-3])
+    ctx = binding.Context(H, W, C, 8e-6, lam, [2e-3], pad=(Hp, Wp), max_gaussians=16)
+    _, u = ctx.propagate(torch.from_numpy(f).cuda(), intensity=True, field_out=True)
+    assert rel(u.cpu().numpy(), O.propagate(f.astype(np.complex128), opt)) <= TOL
