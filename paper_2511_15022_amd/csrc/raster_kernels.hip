@@ -1313,10 +1313,10 @@ hipError_t launch_raster_fwd(const Ctx &c, float2 *field, hipStream_t s) {
 //   S[2C+2] += w dx^2, S[2C+3] += w dx dy, S[2C+4] += w dy^2   (-> dL/dSigma^{-1})
 // with dx, dy = pixel - mean.  The clamped exponent has zero derivative.
 //
-// Work balance.  A workgroup of three waves owns a tile: the tile's dL/dU0 is
-// staged in LDS once, the pair list is cut into three equal parts, and each
+// Work balance.  A workgroup of NW waves owns a tile: the tile's dL/dU0 is
+// staged in LDS once, the pair list is cut into NW equal parts, and each
 // wave takes its part in batches of 64 with a pair table of its own in LDS
-// (three waves per tile rather than one keep more waves resident per CU,
+// (several waves per tile rather than one keep more waves resident per CU,
 // since the staged tile is shared).  Each pair's pixel box is cut into segments of 8 pixels (the last one
 // padded), the segments of a batch are laid end to end, and the segment range
 // is cut into 64 equal contiguous pieces, one per lane, so every lane walks
@@ -1334,15 +1334,20 @@ hipError_t launch_raster_fwd(const Ctx &c, float2 *field, hipStream_t s) {
 // one, and a step's values are read from LDS while the step before it is summed.
 // What bounds it: VALU issue and, from three channels on, the LDS reads (8 C bytes
 // per pixel and lane, at addresses that spread over the banks like random ones).
-// Three waves per tile: two leave too few waves (152 us), four cut a tile's list
-// into batches too short (139 us).  Measured before (one pixel per step) and now: 1080p
+// Three waves per tile where there are many: two leave too few waves (152 us), four cut
+// a tile's list into batches too short (139 us).  Measured before (one pixel per step) and now: 1080p
 // RGB, 415k Gaussians, 137 -> 133 us; 512 x 512 gray, 52k Gaussians x 8 holograms,
 // 84 -> 74 us.
 // ----------------------------------------------------------------------------
 constexpr int kAdjBatch = 64;
 constexpr int kAdjSeg = 8;    // pixels per segment
 constexpr int kAdjRowPad = 1;  // float2 of padding after each staged tile row (bank spread)
-constexpr int kAdjWaves = 3;  // waves per tile; wave w takes part w of kAdjWaves of the list
+// Waves per tile (wave w takes part w of NW of the tile's list): 3, or 8 where there are
+// at most kAdjFewTiles tiles per CU, whose waves would be too few to cover their own
+// latencies.  Measured with 3, 6, 8 and 12 waves: one tile per CU (256 x 256 gray) 14.8,
+// 11.4, 10.6 and 11.2 us; 2.7 (333 x 517 gray) 19.1, 16.1, 16.6 and 20.6 us; 10 (640 x
+// 1024 RGB) 35, 55, 60 and 105 us.
+constexpr int kAdjWaves = 3, kAdjManyWaves = 8, kAdjFewTiles = 3;
 
 // per-pair quantities kept in LDS for the walk (floats):
 //   0-1 offx, offy (tile origin - floor(mean) - frac(mean))
@@ -1364,8 +1369,8 @@ template <int C, bool PA> struct AdjQ {
 // Pair partials: dP_c, dQ_c (2C), sum w d (2), sum w d d^T (3); with PA one more,
 // the sum of G gp over the pixels where the 0.99 clamp is active (their
 // weight does not depend on alpha), in the slot that the stride leaves spare.
-template <int C, bool CLAMP, bool PA, int TW, int TH>
-__global__ __launch_bounds__(64 * kAdjWaves) void k_raster_adj(
+template <int C, bool CLAMP, bool PA, int TW, int TH, int NW>
+__global__ __launch_bounds__(64 * NW) void k_raster_adj(
     const float *__restrict__ rec, const uint32_t *__restrict__ vals,
     const uint2 *__restrict__ ranges, const uint2 *__restrict__ rect,
     const uint32_t *__restrict__ offsets, int W, int H, int tiles_x, int tiles_per, float thr,
@@ -1386,7 +1391,7 @@ __global__ __launch_bounds__(64 * kAdjWaves) void k_raster_adj(
   // offsets as immediates.
   constexpr int RS2 = TW * C + kAdjRowPad;
   constexpr int kSg4 = ((TH + 1) * RS2 * 2 + 3) / 4, kSq4 = kAdjBatch * Q::N / 4;
-  __shared__ float4 lds4[kSg4 + kAdjWaves * kSq4];
+  __shared__ float4 lds4[kSg4 + NW * kSq4];
   float2 *sg = reinterpret_cast<float2 *>(lds4);
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1394,17 +1399,25 @@ __global__ __launch_bounds__(64 * kAdjWaves) void k_raster_adj(
   // share nothing, and a wave's LDS operations execute in issue order
   float *sq = reinterpret_cast<float *>(lds4 + kSg4 + wave * kSq4);
   auto wave_sync = [] {
-    if constexpr (kAdjWaves == 1) __syncthreads();
-    else asm volatile("" ::: "memory");
+    asm volatile("" ::: "memory");
   };
   const int tile = blockIdx.x;
   const int hb = tile / tiles_per, ltile = tile - hb * tiles_per;  // hologram, its tile
   const float2 *gfield = gfield_all + (size_t)hb * C * H * W;
   const int tx = ltile % tiles_x, ty = ltile / tiles_x;
   const int X0 = tx * TW, Y0 = ty * TH;
+  uint2 rg = ranges[tile];
+  {
+    // a tile without pairs has the range (0xffffffff, 0)
+    const uint32_t len = rg.y > rg.x ? rg.y - rg.x : 0u;
+    rg = make_uint2(rg.x + (uint32_t)(((uint64_t)len * wave) / NW),
+                    rg.x + (uint32_t)(((uint64_t)len * (wave + 1)) / NW));
+  }
+  // a batch's Gaussian ids are loaded a batch ahead, the first with the tile
+  uint32_t gid = rg.x + lane < rg.y ? vals[rg.x + lane] : 0u;
   {
     // all loads of a thread are issued before the first is stored
-    constexpr int NT = 64 * kAdjWaves, K = (C * TP + NT - 1) / NT;
+    constexpr int NT = 64 * NW, K = (C * TP + NT - 1) / NT;
     const int tid = threadIdx.x;
     float2 v[K];
 #pragma unroll
@@ -1424,15 +1437,8 @@ __global__ __launch_bounds__(64 * kAdjWaves) void k_raster_adj(
     }
     for (int i = tid; i < TW * C; i += NT) sg[TH * RS2 + i] = make_float2(0.f, 0.f);
   }
-  if constexpr (kAdjWaves > 1) __syncthreads();
+  __syncthreads();
   const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  uint2 rg = ranges[tile];
-  {
-    // a tile without pairs has the range (0xffffffff, 0)
-    const uint32_t len = rg.y > rg.x ? rg.y - rg.x : 0u;
-    rg = make_uint2(rg.x + (uint32_t)(((uint64_t)len * wave) / kAdjWaves),
-                    rg.x + (uint32_t)(((uint64_t)len * (wave + 1)) / kAdjWaves));
-  }
   for (uint32_t base = rg.x; base < rg.y; base += kAdjBatch) {
     // ---- set-up: one pair per lane --------------------------------------
     const int cnt = (int)min((uint32_t)kAdjBatch, rg.y - base);
@@ -1442,8 +1448,10 @@ __global__ __launch_bounds__(64 * kAdjWaves) void k_raster_adj(
     float r[RX];
 #pragma unroll
     for (int k = 0; k < RX; ++k) r[k] = 0.f;
+    const uint32_t g = gid;
+    if (rg.y - base > kAdjBatch)  // (uniform)
+      gid = base + kAdjBatch + lane < rg.y ? vals[base + kAdjBatch + lane] : 0u;
     if (lane < cnt) {
-      const uint32_t g = vals[base + lane];
       const float4 *src = reinterpret_cast<const float4 *>(rec + (size_t)g * RS);
 #pragma unroll
       for (int k = 0; k < RX / 4; ++k) {
@@ -1512,7 +1520,7 @@ __global__ __launch_bounds__(64 * kAdjWaves) void k_raster_adj(
       q[Q::START] = __int_as_float(start | segs << 16);
       q[Q::SLOT] = __uint_as_float(slot);
       if (PA) {
-        const float2 l = alim[vals[base + lane]];
+        const float2 l = alim[g];
         q[Q::LO] = l.x;
         q[Q::HI] = l.y;
       }
@@ -1994,14 +2002,21 @@ hipError_t launch_raster_adjoint(const Ctx &c, const float2 *grad_field, hipStre
     constexpr int TW = decltype(tw)::value, TH = decltype(th)::value;
     with_channels(c.C, [&](auto cc) {
       constexpr int CC = decltype(cc)::value;
-      auto go = [&](auto kern) {
-        hipLaunchKernelGGL(kern, dim3(c.num_tiles), dim3(64 * kAdjWaves), 0, s, c.rec, vals, c.ranges,
-                           c.rect, c.offsets, c.W, c.H, c.tiles_x, c.tiles_per, thr, c.alim,
-                           grad_field, c.pair_cap, c.partials);
+      auto waves = [&](auto nw) {
+        constexpr int NW = decltype(nw)::value;
+        auto go = [&](auto kern) {
+          hipLaunchKernelGGL(kern, dim3(c.num_tiles), dim3(64 * NW), 0, s, c.rec, vals, c.ranges,
+                             c.rect, c.offsets, c.W, c.H, c.tiles_x, c.tiles_per, thr, c.alim,
+                             grad_field, c.pair_cap, c.partials);
+        };
+        if (pa) go(k_raster_adj<CC, false, true, TW, TH, NW>);
+        else if (clamp) go(k_raster_adj<CC, true, false, TW, TH, NW>);
+        else go(k_raster_adj<CC, false, false, TW, TH, NW>);
       };
-      if (pa) go(k_raster_adj<CC, false, true, TW, TH>);
-      else if (clamp) go(k_raster_adj<CC, true, false, TW, TH>);
-      else go(k_raster_adj<CC, false, false, TW, TH>);
+      if (c.num_tiles <= kAdjFewTiles * c.num_cu)
+        waves(std::integral_constant<int, kAdjManyWaves>{});
+      else
+        waves(std::integral_constant<int, kAdjWaves>{});
     });
   });
   return hipGetLastError();
