@@ -355,7 +355,7 @@ cgh_status cgh_read_status(cgh_ctx *ctx, void *stream, int64_t *pairs);
 #define CGH_KERNEL_ROW_FFT 4            /* first forward and last adjoint row pass      */
 #define CGH_KERNEL_COL_PASS 5           /* column passes (H and conj H)                 */
 #define CGH_KERNEL_ROW_LOSS 6           /* middle row pass: |u|^2, loss, adjoint seed   */
-#define CGH_KERNEL_LOSS 7               /* loss reduction                               */
+#define CGH_KERNEL_LOSS 7               /* loss reduction (where it is its own launch)  */
 #define CGH_KERNEL_RASTER_ADJOINT 8     /* rasterizer adjoint, tile stage               */
 #define CGH_KERNEL_PREPROCESS_ADJOINT 9 /* rasterizer adjoint, per-Gaussian FP64 stage  */
 

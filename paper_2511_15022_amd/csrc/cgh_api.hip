@@ -456,10 +456,11 @@ static cgh_status raster_adjoint(Ctx &c, const float *params, int n, const float
   return CGH_OK;
 }
 
-// B2: c.spec_acc -> dL/dU0
-static cgh_status adjoint_rows(Ctx &c, float2 *grad_field, hipStream_t s) {
+// B2: c.spec_acc -> dL/dU0; with loss, the sums of the loss partials
+static cgh_status adjoint_rows(Ctx &c, float2 *grad_field, hipStream_t s,
+                               double *loss = nullptr) {
   ProfScope p(c, CGH_KERNEL_ROW_FFT, s);
-  CGH_CHECK_LAUNCH(cgh::launch_row_inv(c, c.spec_acc, grad_field, s), "adjoint row fft");
+  CGH_CHECK_LAUNCH(cgh::launch_row_inv(c, c.spec_acc, grad_field, s, loss), "adjoint row fft");
   return CGH_OK;
 }
 
@@ -516,11 +517,11 @@ static cgh_status backward_impl(cgh_ctx *ctx, const float *params, int32_t n,
     st = plane_adjoint(c, l, s);
     if (st != CGH_OK) return st;
   }
-  if (loss) {
+  if (loss && !c.row_p) {
     ProfScope p(c, CGH_KERNEL_LOSS, s);
     CGH_CHECK_LAUNCH(cgh::launch_loss_finalize(c, loss, s), "loss");
   }
-  st = adjoint_rows(c, gf, s);
+  st = adjoint_rows(c, gf, s, c.row_p ? loss : nullptr);
   if (st != CGH_OK) return st;
   return raster_adjoint(c, params, n, gf, grads, s, adam);
 }

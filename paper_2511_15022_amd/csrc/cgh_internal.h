@@ -176,7 +176,8 @@ hipError_t launch_build_transfer(const Ctx &c, int b0, int b1, hipStream_t s);
 // the row-major table of (propagation channel, plane) for its current optics -> out
 hipError_t launch_read_transfer(const Ctx &c, int channel, int plane, float2 *out, hipStream_t s);
 hipError_t launch_row_fwd(const Ctx &c, const float2 *field, float2 *dst, hipStream_t s);
-hipError_t launch_row_inv(const Ctx &c, const float2 *src, float2 *out, hipStream_t s);
+hipError_t launch_row_inv(const Ctx &c, const float2 *src, float2 *out, hipStream_t s,
+                          double *loss = nullptr);
 // column pass of plane `plane`: src -> dst (may alias); acc adds into dst
 hipError_t launch_col_pass(const Ctx &c, int conj_h, int plane, const float2 *src, float2 *dst,
                            int acc, hipStream_t s);
@@ -184,6 +185,8 @@ hipError_t launch_col_pass(const Ctx &c, int conj_h, int plane, const float2 *sr
 hipError_t launch_row_loss(const Ctx &c, int plane, float2 *buf, const float *target,
                            const float *grad_intensity, const float *mask, float *intensity,
                            float2 *u_out, int make_grad, hipStream_t s);
+// the loss sums of every hologram, to loss (2 B values); launch_row_inv takes them with
+// it where it runs the chain kernels (the partials are complete before either)
 hipError_t launch_loss_finalize(const Ctx &c, double *loss, hipStream_t s);
 
 // SSIM term of the full loss over the [L][C] images in c.ssim_I against target

@@ -52,8 +52,8 @@ void launch_row(const RowArgs &a, hipStream_t s) {
     hipLaunchKernelGGL((k_row_fwd_q<M, P>), dim3(std::min(a.rows, most)), block, 0, s, a.field, a.H, a.W, a.rows, a.twf_x,
                        a.S);
   else if (a.pass == 1)
-    hipLaunchKernelGGL((k_row_inv_q<M, P>), grid, block, 0, s, a.S, a.H, a.W, a.rows, a.twf_x,
-                       a.out);
+    hipLaunchKernelGGL((k_row_inv_q<M, P>), dim3(a.rows + a.sums.blocks), block, 0, s, a.S, a.H,
+                       a.W, a.rows, a.twf_x, a.out, a.sums);
   else
     hipLaunchKernelGGL((k_row_loss_q<M, P>), grid, block, 0, s, a.S, a.H, a.W, a.rows, a.twf_x,
                        a.target, a.grad_I, a.mask, a.mcg, a.intensity, a.u_out, a.loss_part,

@@ -675,6 +675,12 @@ static hipError_t launch_row_chain(const Ctx &c, const RowArgs &a, hipStream_t s
   return found ? hipGetLastError() : hipErrorInvalidValue;
 }
 
+static LossSums loss_sums_of(const Ctx &c, double *loss) {
+  const int rows = row_blocks(c);
+  return LossSums{c.loss_part, c.L, rows, rows / c.B, c.B,
+                  1.0 / ((double)c.L * c.C * c.H * c.W), loss, c.finite_flag};
+}
+
 int row_split(int Wp, int W) { return split_of(Wp, W, row_chain); }
 int col_split(int Hp, int H) { return split_of(Hp, H, col_chain); }
 
@@ -700,12 +706,18 @@ hipError_t launch_row_fwd(const Ctx &c, const float2 *field, float2 *dst, hipStr
   return hipGetLastError();
 }
 
-hipError_t launch_row_inv(const Ctx &c, const float2 *src, float2 *out, hipStream_t s) {
+hipError_t launch_row_inv(const Ctx &c, const float2 *src, float2 *out, hipStream_t s,
+                          double *loss) {
   if (c.row_p) {
     RowArgs a = row_args(c, 1);
     a.S = const_cast<float2 *>(src);  // only read by this pass
     a.out = out;
+    if (loss) a.sums = loss_sums_of(c, loss);
     return launch_row_chain(c, a, s);
+  }
+  if (loss) {
+    const hipError_t e = launch_loss_finalize(c, loss, s);
+    if (e != hipSuccess) return e;
   }
   if (c.Wp == 3840)
     hipLaunchKernelGGL((k_row_inv_c<3840, 2, 512, false>), dim3(row_blocks(c)), dim3(512), 0, s,
@@ -1044,39 +1056,12 @@ hipError_t launch_col_pass(const Ctx &c, int conj_h, int plane, const float2 *sr
   return hipGetLastError();
 }
 
-// Per hologram b: loss = sum of its loss partials / M, psnr = 10 log10(1 / loss);
-// one block per hologram, fixed order.  The partials of plane l are
-// part[l * rows_per_plane + r]; hologram b owns r in [b span, (b + 1) span).
-__global__ __launch_bounds__(256) void k_loss_finalize(const double *__restrict__ part,
-                                                       int planes, int rows_per_plane, int span,
-                                                       double inv_m, double *__restrict__ out,
-                                                       uint32_t *__restrict__ finite_flag) {
-  __shared__ double red[256];
-  const int b = blockIdx.x;
-  double acc = 0.0;
-  for (int l = 0; l < planes; ++l) {
-    const double *p = part + (size_t)l * rows_per_plane + (size_t)b * span;
-    for (int i = threadIdx.x; i < span; i += 256) acc += p[i];
-  }
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    const double loss = red[0] * inv_m;
-    out[2 * b] = loss;
-    out[2 * b + 1] = 10.0 * log10(1.0 / loss);
-    if (finite_flag && !isfinite(loss)) atomicOr(finite_flag, kNonFiniteLoss);
-  }
+__global__ __launch_bounds__(256) void k_loss_finalize(LossSums sums) {
+  loss_sums<256>(sums, blockIdx.x);
 }
 
 hipError_t launch_loss_finalize(const Ctx &c, double *loss, hipStream_t s) {
-  const double inv_m = 1.0 / ((double)c.L * c.C * c.H * c.W);
-  const int rows = row_blocks(c);
-  hipLaunchKernelGGL(k_loss_finalize, dim3(c.B), dim3(256), 0, s, c.loss_part, c.L, rows,
-                     rows / c.B, inv_m, loss, c.finite_flag);
+  hipLaunchKernelGGL(k_loss_finalize, dim3(c.B), dim3(256), 0, s, loss_sums_of(c, loss));
   return hipGetLastError();
 }
 
