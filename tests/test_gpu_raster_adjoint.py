@@ -36,8 +36,9 @@ def test_odd_boxes_match_oracle(O, tile, H, W, C):
     p["mean_pre"] = np.arctanh(np.stack([2 * x / W - 1, 2 * y / H - 1], -1)).astype(dt)
     p["log_scale"] = np.where(rng.random((n, 1)) < 0.7, rng.uniform(-3.0, -0.5, (n, 2)),
                               rng.uniform(0.0, 2.5, (n, 2))).astype(dt)
-    opt = O.Optics(H, W, C, 2 * H + 4, 2 * W + 2, 8e-6, lam, [2e-3])
-    ctx = binding.Context(H, W, C, 8e-6, lam, [2e-3], pad=(2 * H + 4, 2 * W + 2),
+    pad = (90, 144) if H == 43 else (900, 960)
+    opt = O.Optics(H, W, C, *pad, 8e-6, lam, [2e-3])
+    ctx = binding.Context(H, W, C, 8e-6, lam, [2e-3], pad=pad,
                           max_gaussians=n, max_pairs=64 * n, tile=tile)
     ref = O.forward_backward(p, synth.target(7, C, H, W), opt)
     P = binding.pack(p, device="cuda")
