@@ -218,10 +218,6 @@ size_t carve(Ctx *c, char *base) {
   }
   const size_t spec_len = (size_t)c->CF * c->Wt * c->H * 8;
   c->spec = (float2 *)take(sizeof(float2) * spec_len);
-  // with several planes the shared row spectrum stays in spec; each plane's
-  // column pass writes spec_plane, and the adjoint sums the planes in spec_acc
-  c->spec_plane = c->L > 1 ? (float2 *)take(sizeof(float2) * spec_len) : c->spec;
-  c->spec_acc = c->L > 1 ? (float2 *)take(sizeof(float2) * spec_len) : c->spec;
   c->gfield_tmp = (float2 *)take(sizeof(float2) * c->CF * HW);
   c->rec = (float *)take(sizeof(float) * c->rec_stride * (N + 1));
   c->alim = (c->cfg.flags & CGH_PAPER_ALPHA) ? (float2 *)take(sizeof(float2) * (N + 1)) : nullptr;
@@ -243,12 +239,31 @@ size_t carve(Ctx *c, char *base) {
   c->scan_tmp = (uint32_t *)take(sizeof(uint32_t) *
                                  std::max(scan_len / kScanItems + 2, (N + 255) / 256 + 2));
   // The loss partials (one per row-pass workgroup and plane) share the memory of
-  // the pair partials: a loss is reduced before the rasterizer adjoint of the
-  // same call writes its partials, and those are summed in that call.
+  // the pair partials, at its end: a loss is reduced before the rasterizer adjoint of the
+  // same call writes its partials, and those are summed in that call.  With several
+  // planes, two spectra stand before the pair partials, and the planes' spectra go on into
+  // their memory as far as it reaches (each is read before the pair partials are
+  // written).  Where all planes fit, they are propagated together and the adjoint's sum
+  // takes the place of the row spectrum, which every plane has used by then; otherwise
+  // the first spectrum is the sum and the others hold a group of planes at a time.
   const int rg = row_group_rows(*c);
   const size_t loss_bytes = sizeof(double) * c->L * c->CF * (size_t)((c->H + rg - 1) / rg);
-  c->partials = (float *)take(std::max(sizeof(float) * c->part_stride * cap, loss_bytes));
-  c->loss_part = (double *)c->partials;
+  const size_t part_bytes = std::max(sizeof(float) * c->part_stride * cap,
+                                     (loss_bytes + 255) & ~(size_t)255);
+  const size_t spec_bytes = sizeof(float2) * spec_len;
+  const size_t head = c->L > 1 ? (2 * spec_bytes + 255) & ~(size_t)255 : 0;
+  char *region = take(head + part_bytes);
+  c->partials = (float *)(region + head);
+  const size_t loss_at = (head + part_bytes - loss_bytes) & ~(size_t)255;
+  c->loss_part = (double *)(region + loss_at);
+  c->plane_group = 1;
+  c->spec_plane = c->spec_acc = c->spec;
+  if (c->L > 1) {
+    const int fit = (int)std::min((size_t)c->L, loss_at / spec_bytes);
+    c->plane_group = fit == c->L ? fit : fit - 1;
+    c->spec_plane = (float2 *)region + (fit == c->L ? 0 : spec_len);
+    if (fit < c->L) c->spec_acc = (float2 *)region;
+  }
   c->status = (uint32_t *)take(sizeof(uint32_t) * 4);
   c->finite_flag = (c->cfg.flags & CGH_CHECK_FINITE) && c->status ? c->status + 3 : nullptr;
   c->ssim_I = nullptr;
@@ -424,18 +439,23 @@ static cgh_status row_spectrum(Ctx &c, const cgh_c64 *field, hipStream_t s) {
   return CGH_OK;
 }
 
-// F2 of plane l: c.spec -> c.spec_plane (in place when L = 1)
-static cgh_status plane_spectrum(Ctx &c, int l, hipStream_t s) {
+// the planes of the group that starts at plane l
+static int group_at(const Ctx &c, int l) { return std::min(c.plane_group, c.L - l); }
+
+// F2 of the group of planes at l: c.spec -> c.spec_plane (in place when L = 1)
+static cgh_status plane_spectra(Ctx &c, int l, hipStream_t s) {
   ProfScope p(c, CGH_KERNEL_COL_PASS, s);
-  CGH_CHECK_LAUNCH(cgh::launch_col_pass(c, 0, l, c.spec, c.spec_plane, 0, s), "column pass");
+  CGH_CHECK_LAUNCH(cgh::launch_col_pass(c, 0, l, group_at(c, l), c.spec, c.spec_plane, 0, s),
+                   "column pass");
   return CGH_OK;
 }
 
-// B1 of plane l: the adjoint seed in c.spec_plane -> c.spec_acc (summed over
-// planes: the first plane writes, the others add)
-static cgh_status plane_adjoint(Ctx &c, int l, hipStream_t s) {
+// B1 of the group of planes at l: the adjoint seeds in c.spec_plane -> c.spec_acc (the
+// sum over planes: the first group writes, the others add)
+static cgh_status plane_adjoints(Ctx &c, int l, hipStream_t s) {
   ProfScope p(c, CGH_KERNEL_COL_PASS, s);
-  CGH_CHECK_LAUNCH(cgh::launch_col_pass(c, 1, l, c.spec_plane, c.spec_acc, l > 0, s),
+  CGH_CHECK_LAUNCH(cgh::launch_col_pass(c, 1, l, group_at(c, l), c.spec_plane, c.spec_acc, l > 0,
+                                        s),
                    "adjoint column pass");
   return CGH_OK;
 }
@@ -474,13 +494,13 @@ cgh_status cgh_propagate(cgh_ctx *ctx, const cgh_c64 *field, float *intensity,
   hipStream_t s = (hipStream_t)stream;
   cgh_status st = row_spectrum(c, field, s);
   if (st != CGH_OK) return st;
-  for (int l = 0; l < c.L; ++l) {
-    st = plane_spectrum(c, l, s);
+  for (int l = 0; l < c.L; l += c.plane_group) {
+    st = plane_spectra(c, l, s);
     if (st != CGH_OK) return st;
     ProfScope p(c, CGH_KERNEL_ROW_LOSS, s);
-    CGH_CHECK_LAUNCH(cgh::launch_row_loss(c, l, c.spec_plane, nullptr, nullptr, nullptr,
-                                          intensity, reinterpret_cast<float2 *>(field_out), 0,
-                                          s),
+    CGH_CHECK_LAUNCH(cgh::launch_row_loss(c, l, group_at(c, l), c.spec_plane, nullptr, nullptr,
+                                          nullptr, intensity,
+                                          reinterpret_cast<float2 *>(field_out), 0, s),
                      "intensity row pass");
   }
   return CGH_OK;
@@ -505,16 +525,16 @@ static cgh_status backward_impl(cgh_ctx *ctx, const float *params, int32_t n,
   float2 *gf = grad_field ? reinterpret_cast<float2 *>(grad_field) : c.gfield_tmp;
   st = row_spectrum(c, field, s);
   if (st != CGH_OK) return st;
-  for (int l = 0; l < c.L; ++l) {
-    st = plane_spectrum(c, l, s);
+  for (int l = 0; l < c.L; l += c.plane_group) {
+    st = plane_spectra(c, l, s);
     if (st != CGH_OK) return st;
     {
       ProfScope p(c, CGH_KERNEL_ROW_LOSS, s);
-      CGH_CHECK_LAUNCH(cgh::launch_row_loss(c, l, c.spec_plane, target, nullptr, mask, nullptr,
-                                            nullptr, 1, s),
+      CGH_CHECK_LAUNCH(cgh::launch_row_loss(c, l, group_at(c, l), c.spec_plane, target, nullptr,
+                                            mask, nullptr, nullptr, 1, s),
                        "loss row pass");
     }
-    st = plane_adjoint(c, l, s);
+    st = plane_adjoints(c, l, s);
     if (st != CGH_OK) return st;
   }
   if (loss && !c.row_p) {
@@ -592,12 +612,12 @@ cgh_status cgh_backward_full(cgh_ctx *ctx, const float *params, int32_t n,
   // forward: every plane's intensity, field and L_recon partials
   st = row_spectrum(c, field, s);
   if (st != CGH_OK) return st;
-  for (int l = 0; l < c.L; ++l) {
-    st = plane_spectrum(c, l, s);
+  for (int l = 0; l < c.L; l += c.plane_group) {
+    st = plane_spectra(c, l, s);
     if (st != CGH_OK) return st;
     ProfScope p(c, CGH_KERNEL_ROW_LOSS, s);
-    CGH_CHECK_LAUNCH(cgh::launch_row_loss(c, l, c.spec_plane, target, nullptr, mask, c.ssim_I,
-                                          c.ssim_u, 0, s),
+    CGH_CHECK_LAUNCH(cgh::launch_row_loss(c, l, group_at(c, l), c.spec_plane, target, nullptr,
+                                          mask, c.ssim_I, c.ssim_u, 0, s),
                      "loss row pass");
   }
   // SSIM and dL/dI over all planes; ssim_u becomes 2 (dL/dI) u
@@ -608,14 +628,14 @@ cgh_status cgh_backward_full(cgh_ctx *ctx, const float *params, int32_t n,
     if (loss) CGH_CHECK_LAUNCH(cgh::launch_full_loss_finalize(c, ssim_weight, loss, s), "loss");
   }
   // adjoint of the propagation from the intensity gradient, plane by plane
-  for (int l = 0; l < c.L; ++l) {
+  for (int l = 0; l < c.L; l += c.plane_group) {
     {
       ProfScope p(c, CGH_KERNEL_ROW_FFT, s);
       CGH_CHECK_LAUNCH(cgh::launch_row_fwd(c, c.ssim_u + (size_t)l * c.C * c.H * c.W,
-                                           c.spec_plane, s),
+                                           c.spec_plane, s, group_at(c, l)),
                        "adjoint seed row fft");
     }
-    st = plane_adjoint(c, l, s);
+    st = plane_adjoints(c, l, s);
     if (st != CGH_OK) return st;
   }
   st = adjoint_rows(c, gf, s);
@@ -632,13 +652,14 @@ cgh_status cgh_propagate_field_adjoint(cgh_ctx *ctx, const cgh_c64 *grad_u, cgh_
     return fail(CGH_ERR_INVALID_ARG, "buffers must be 16-byte aligned");
   hipStream_t s = (hipStream_t)stream;
   const float2 *g = reinterpret_cast<const float2 *>(grad_u);
-  for (int l = 0; l < c.L; ++l) {
+  for (int l = 0; l < c.L; l += c.plane_group) {
     {
       ProfScope p(c, CGH_KERNEL_ROW_FFT, s);
-      CGH_CHECK_LAUNCH(cgh::launch_row_fwd(c, g + (size_t)l * c.CF * c.H * c.W, c.spec_plane, s),
+      CGH_CHECK_LAUNCH(cgh::launch_row_fwd(c, g + (size_t)l * c.CF * c.H * c.W, c.spec_plane, s,
+                                           group_at(c, l)),
                        "adjoint seed row fft");
     }
-    cgh_status st = plane_adjoint(c, l, s);
+    cgh_status st = plane_adjoints(c, l, s);
     if (st != CGH_OK) return st;
   }
   return adjoint_rows(c, reinterpret_cast<float2 *>(grad_field), s);
@@ -656,16 +677,16 @@ cgh_status cgh_propagate_adjoint(cgh_ctx *ctx, const cgh_c64 *field,
   hipStream_t s = (hipStream_t)stream;
   cgh_status st = row_spectrum(c, field, s);
   if (st != CGH_OK) return st;
-  for (int l = 0; l < c.L; ++l) {
-    st = plane_spectrum(c, l, s);
+  for (int l = 0; l < c.L; l += c.plane_group) {
+    st = plane_spectra(c, l, s);
     if (st != CGH_OK) return st;
     {
       ProfScope p(c, CGH_KERNEL_ROW_LOSS, s);
-      CGH_CHECK_LAUNCH(cgh::launch_row_loss(c, l, c.spec_plane, nullptr, grad_intensity,
-                                            nullptr, nullptr, nullptr, 1, s),
+      CGH_CHECK_LAUNCH(cgh::launch_row_loss(c, l, group_at(c, l), c.spec_plane, nullptr,
+                                            grad_intensity, nullptr, nullptr, nullptr, 1, s),
                        "adjoint seed row pass");
     }
-    st = plane_adjoint(c, l, s);
+    st = plane_adjoints(c, l, s);
     if (st != CGH_OK) return st;
   }
   return adjoint_rows(c, reinterpret_cast<float2 *>(grad_field), s);

@@ -117,8 +117,11 @@ struct Ctx {
   float2 *htab_t;                   // [B C][L][Wq][Hq], chain column pass only, else null
   float2 *twf_y;                    // full twiddle table for Hp, chain column pass only
   float2 *spec;                     // [B C][Wt][H][8] column-tiled propagation buffer
-  float2 *spec_plane;               // per-plane column-pass output (spec itself when L = 1)
-  float2 *spec_acc;                 // adjoint sum over planes (spec itself when L = 1)
+  float2 *spec_plane;               // [plane_group][B C][Wt][H][8] spectra of a group of
+                                    // planes (spec itself when L = 1)
+  float2 *spec_acc;                 // adjoint sum over planes (spec itself when one group
+                                    // holds them all)
+  int plane_group;                  // planes propagated together
   float2 *gfield_tmp;               // [B C][H][W]
   float *rec;                       // [B max_gaussians + 1][rec_stride]; the last is all zeros
   float2 *alim;                     // CGH_PAPER_ALPHA only, else null: [B max_gaussians + 1]
@@ -136,7 +139,7 @@ struct Ctx {
   float *partials;                  // [pair_cap][part_stride] raster-adjoint partials
   double *loss_part;                // [L][row-pass workgroups] FP64 loss partials (the
                                     // workgroups of hologram b contiguous in each plane),
-                                    // in the memory of partials
+                                    // in the memory of partials, at its end
   // cgh_backward_full only (CGH_FULL_LOSS), else null
   float *ssim_I;                    // [L][C][H][W] intensity
   float2 *ssim_u;                   // [L][C][H][W] propagated field, then 2 dL/dI u
@@ -175,14 +178,23 @@ int row_group_rows(const Ctx &c);   // rows per row-pass workgroup
 hipError_t launch_build_transfer(const Ctx &c, int b0, int b1, hipStream_t s);
 // the row-major table of (propagation channel, plane) for its current optics -> out
 hipError_t launch_read_transfer(const Ctx &c, int channel, int plane, float2 *out, hipStream_t s);
-hipError_t launch_row_fwd(const Ctx &c, const float2 *field, float2 *dst, hipStream_t s);
+// `planes` fields -> their row spectra, each after the other in field and dst
+hipError_t launch_row_fwd(const Ctx &c, const float2 *field, float2 *dst, hipStream_t s,
+                          int planes = 1);
 hipError_t launch_row_inv(const Ctx &c, const float2 *src, float2 *out, hipStream_t s,
                           double *loss = nullptr);
-// column pass of plane `plane`: src -> dst (may alias); acc adds into dst
-hipError_t launch_col_pass(const Ctx &c, int conj_h, int plane, const float2 *src, float2 *dst,
-                           int acc, hipStream_t s);
+// elements of one plane's spectrum
+inline size_t spec_elems(const Ctx &c) { return (size_t)c.CF * c.Wt * c.H * 8; }
+// column passes of planes plane .. plane + planes - 1 (one plane: src and dst may alias).
+// Forward: the spectrum src -> each plane's, one after the other in dst.  Adjoint
+// (conj_h): the planes' spectra, one after the other in src -> their sum in dst; acc adds
+// it to dst.
+hipError_t launch_col_pass(const Ctx &c, int conj_h, int plane, int planes, const float2 *src,
+                           float2 *dst, int acc, hipStream_t s);
+// the middle row pass of the same planes, their spectra one after the other in buf; the
+// other arrays are those of all L planes.
 // mask (optional, [L][H][W]): the L_recon weight 1 + mask^2 + target^2
-hipError_t launch_row_loss(const Ctx &c, int plane, float2 *buf, const float *target,
+hipError_t launch_row_loss(const Ctx &c, int plane, int planes, float2 *buf, const float *target,
                            const float *grad_intensity, const float *mask, float *intensity,
                            float2 *u_out, int make_grad, hipStream_t s);
 // the loss sums of every hologram, to loss (2 B values); launch_row_inv takes them with

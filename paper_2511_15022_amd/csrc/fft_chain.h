@@ -201,6 +201,13 @@ constexpr bool row_chain(int M, int P) {
          (P == 4 || M % 2);
 }
 
+// The column lengths whose planes share a pass (k_col_wave): those whose last radix leaves
+// the registers of a lane room for the kept spectrum beside the one at work.  Above 15 the
+// two spill: three planes at 4K RGB (radix 20) 2.78 ms together, 2.38 ms one by one.
+// Below: 720p RGB in three planes 272 us one by one, 240 us together (render);
+// 640 x 1024 RGB in two planes 425 and 400 us (gradient of the full loss).
+constexpr bool planes_chain(int M, int P) { return col_chain(M, P) && col_plan(M).r2 <= 15; }
+
 // the split of a padded length n with `used` samples: P chains of n / P, or 0
 inline int split_of(int n, int used, bool (*built)(int, int)) {
   if (2 * used > n || n % 2) return 0;
@@ -615,67 +622,46 @@ CGH_ROW_KERNEL(M, P) k_row_loss_q(float2 *__restrict__ S, int H, int W, int rows
 // may be the same buffer (in place).  acc: add the result to dst instead of
 // overwriting it (the adjoint's sum over planes).  htab points at the table
 // of the pass's plane for channel 0; channel ch is at htab + ch * hstride.
+// planes > 1 (k_col_wave with PLANES): plane l's table is at htab + l * hplane, and its
+// spectrum at l * splane of dst (forward) or src (adjoint).
 struct ColIO {
   const float2 *src;
   float2 *dst;
   const float2 *htab;
   size_t hstride;
   int acc;
+  int planes;
+  size_t hplane, splane;
 };
 
-// Column pass with one wave per chain, M = R0 R1 R2 (col_plan); CONJ: multiply
-// by conj(H) (the adjoint pass).  A workgroup of eight waves takes 8 / P
-// columns of a tile of 8; wave P c + p runs chain p of column c in its own
-// M-element LDS buffer, so the stages of a chain need no workgroup barrier: only
-// loading the columns and combining the chains are workgroup steps.  The
-// forward plan is R0, R1, R2; its last stage leaves lane j < M / R2 holding
-// spectrum entries j + (M / R2) q (q < R2), exactly the input of a first
-// inverse stage of radix R2, so the transfer multiply and that stage run in
-// registers; the inverse plan is R2, R1, R0.  The transfer table is read
-// column-major ([Wq][Hq]); the workgroups of a mirror pair of tiles
-// (t, Wt - 1 - t), whose columns need about the same table columns, are blocks
-// b + 8 s (s < 2 P), which share an XCD.
-template <int M, int P, bool CONJ>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(lds_waves(9 * M)))) void
-k_col_wave(ColIO io, int Hq, int H, int Wp, int Wt, int C, const float2 *__restrict__ twf_y) {
-  constexpr ColPlan pl = col_plan(M);
-  constexpr int R0 = pl.r0, R1 = pl.r1, R2 = pl.r2;
-  constexpr int NB2 = M / R2;
+// The steps of a column workgroup (k_col_wave); item i of a step is row n = i / NC of
+// column c = i % NC of the workgroup's.
+template <int M, int P>
+struct ColSteps {
+  static constexpr ColPlan pl = col_plan(M);
+  static constexpr int R0 = pl.r0, R1 = pl.r1, R2 = pl.r2;
+  static constexpr int NB2 = M / R2;
   static_assert(R0 * R1 * R2 == M && NB2 <= 64, "the fused stage takes one butterfly per lane");
-  constexpr int NC = 8 / P;  // columns per workgroup
-  constexpr int T = 512, NI = NC * M, K = (NI + T - 1) / T, KT = (M + T - 1) / T;
-  __shared__ float2 buf[8 * M];
-  __shared__ float2 tw[M];
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: scalar addressing
-  const int b = blockIdx.x;
-  constexpr int SL = 2 * P;  // workgroups of a mirror pair
-  const int slot = (b >> 3) % SL, pi = (b / (8 * SL)) * 8 + (b & 7);
-  const int hp = (Wt + 1) >> 1;
-  if (pi >= C * hp) return;
-  const int ch = pi / hp, pp = pi - ch * hp;
-  const int t = slot < P ? pp : Wt - 1 - pp;
-  if (slot >= P && t == pp) return;  // the middle tile of an odd count has no mirror
-  const int part = slot % P;
-  const size_t off = ((size_t)ch * Wt + t) * H * 8 + part * NC;
-  const float2 *src = io.src + off;
-  float2 *dst = io.dst + off;
-  {
-    // item i: row n = i / NC of column c = i % NC; every global load of this
-    // phase is issued before the first LDS store
-    float2 av[K], bv[K], w1[K], tv[KT];
+  static constexpr int NC = 8 / P;  // columns per workgroup
+  static constexpr int T = 512, NI = NC * M, K = (NI + T - 1) / T;
+
+  // the columns' samples, to registers
+  static __device__ __forceinline__ void load(const float2 *src, int H, int tid, float2 (&av)[K],
+                                              float2 (&bv)[K]) {
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       const int i = tid + k * T, n = min(i / NC, M - 1), c = i % NC;
       av[k] = at32(src, min(n, H - 1) * 8 + c);
       bv[k] = P == 4 ? at32(src, min(n + M, H - 1) * 8 + c) : make_float2(0.f, 0.f);
-      w1[k] = at32(twf_y, n);
     }
+  }
+  static __device__ __forceinline__ void load_w(const float2 *twf_y, int tid, float2 (&w1)[K]) {
 #pragma unroll
-    for (int k = 0; k < KT; ++k) tv[k] = at32(twf_y, P * M + min(tid + k * T, M - 1));  // w_M^k
-#pragma unroll
-    for (int k = 0; k < KT; ++k)
-      if (tid + k * T < M) tw[tid + k * T] = tv[k];
+    for (int k = 0; k < K; ++k) w1[k] = at32(twf_y, min((tid + k * T) / NC, M - 1));
+  }
+  // the chains' inputs, to LDS
+  static __device__ __forceinline__ void inputs(float2 *buf, int H, int tid, float2 (&av)[K],
+                                                float2 (&bv)[K], float2 (&w1)[K]) {
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       const int i = tid + k * T, n = i / NC, c = i % NC;
@@ -698,28 +684,21 @@ k_col_wave(ColIO io, int Hq, int H, int Wp, int Wt, int C, const float2 *__restr
       }
     }
   }
-  __syncthreads();
-  {
-    const int c = wave / P, p = wave % P;
-    float2 *wb = buf + wave * M;
-    // columns past Wp (the last tile of a Wp that is not a multiple of 8) hold
-    // nothing that is read again; their table column is clamped
-    const int kx = min(t * 8 + part * NC + c, Wp - 1);
-    const int qx = min(kx, Wp - kx);
-    const float2 *hcol = io.htab + (size_t)ch * io.hstride + (size_t)qx * Hq;
-    // transfer values for ky = P (j + NB2 q) + p, issued before the forward stages
-    float2 hv[R2];
-    {
-      const int j = min(lane, NB2 - 1);
-      static_for<0, R2>([&](auto qc) {
-        constexpr int q = decltype(qc)::value;
-        const int ky = P * (j + NB2 * q) + p;
-        hv[q] = at32(hcol, min(ky, P * M - ky));
-      });
-    }
+  // a lane's transfer values: spectrum entries ky = P (j + NB2 q) + p of one column
+  static __device__ __forceinline__ void transfer(const float2 *hcol, int p, int lane,
+                                                  float2 (&hv)[R2]) {
+    const int j = min(lane, NB2 - 1);
+    static_for<0, R2>([&](auto qc) {
+      constexpr int q = decltype(qc)::value;
+      const int ky = P * (j + NB2 * q) + p;
+      hv[q] = at32(hcol, min(ky, P * M - ky));
+    });
+  }
+  // one wave's chain, LDS to the spectrum entries j + NB2 q of lane j
+  static __device__ __forceinline__ void forward(float2 *wb, const float2 *tw, int lane,
+                                                 float2 (&v)[R2]) {
     wstage<R0, -1, M, 1>(wb, tw, lane);
     if constexpr (R1 > 1) wstage<R1, -1, M, R0>(wb, tw, lane);
-    float2 v[R2];
     if (lane < NB2) {
       static_for<0, R2>([&](auto qc) {
         constexpr int q = decltype(qc)::value;
@@ -730,12 +709,12 @@ k_col_wave(ColIO io, int Hq, int H, int Wp, int Wt, int C, const float2 *__restr
         v[q] = cmul(v[q], tw[q * lane]);  // last forward stage: Ns = NB2, unit twiddle step
       });
       RFft<R2, -1>::run(v);
-      static_for<0, R2>([&](auto qc) {
-        constexpr int q = decltype(qc)::value;
-        v[q] = cmul(v[q], CONJ ? cconj(hv[q]) : hv[q]);  // the table carries 1 / (Hp Wp)
-      });
-      RFft<R2, +1>::run(v);  // first inverse stage: Ns = 1, no twiddles
     }
+  }
+  // the inverse of the spectrum entries of each lane, to LDS
+  static __device__ __forceinline__ void inverse(float2 *wb, const float2 *tw, int lane,
+                                                 float2 (&v)[R2]) {
+    if (lane < NB2) RFft<R2, +1>::run(v);  // first inverse stage: Ns = 1, no twiddles
     wave_lds_order();
     if (lane < NB2) {
       static_for<0, R2>([&](auto qc) {
@@ -747,11 +726,9 @@ k_col_wave(ColIO io, int Hq, int H, int Wp, int Wt, int C, const float2 *__restr
     if constexpr (R1 > 1) wstage<R1, +1, M, R2>(wb, tw, lane);
     wstage<R0, +1, M, R2 * R1>(wb, tw, lane);
   }
-  {
-    float2 w1[K];
-#pragma unroll
-    for (int k = 0; k < K; ++k) w1[k] = at32(twf_y, min((tid + k * T) / NC, M - 1));
-    __syncthreads();
+  // the columns from the chains' outputs
+  static __device__ __forceinline__ void outputs(const float2 *buf, float2 *dst, int H, int acc,
+                                                 int tid, float2 (&w1)[K]) {
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       const int i = tid + k * T, n = i / NC, c = i % NC;
@@ -771,13 +748,140 @@ k_col_wave(ColIO io, int Hq, int H, int Wp, int Wt, int C, const float2 *__restr
           y0 = cadd(buf[(2 * c) * M + n], cmul(cconj(w1[k]), buf[(2 * c + 1) * M + n]));
         }
         float2 &d0 = at32(dst, n * 8 + c);
-        d0 = io.acc ? cadd(d0, y0) : y0;
+        d0 = acc ? cadd(d0, y0) : y0;
         if (P == 4 && n + M < H) {
           float2 &d1 = at32(dst, (n + M) * 8 + c);
-          d1 = io.acc ? cadd(d1, y1) : y1;
+          d1 = acc ? cadd(d1, y1) : y1;
         }
       }
     }
+  }
+};
+
+// Column pass with one wave per chain, M = R0 R1 R2 (col_plan); CONJ: multiply
+// by conj(H) (the adjoint pass).  A workgroup of eight waves takes 8 / P
+// columns of a tile of 8; wave P c + p runs chain p of column c in its own
+// M-element LDS buffer, so the stages of a chain need no workgroup barrier: only
+// loading the columns and combining the chains are workgroup steps.  The
+// forward plan is R0, R1, R2; its last stage leaves lane j < M / R2 holding
+// spectrum entries j + (M / R2) q (q < R2), exactly the input of a first
+// inverse stage of radix R2, so the transfer multiply and that stage run in
+// registers; the inverse plan is R2, R1, R0.  The transfer table is read
+// column-major ([Wq][Hq]); the workgroups of a mirror pair of tiles
+// (t, Wt - 1 - t), whose columns need about the same table columns, are blocks
+// b + 8 s (s < 2 P), which share an XCD.
+//
+// PLANES: every focal plane in one pass.  The planes share the spectrum of the field, so
+// the forward pass transforms a column once, keeps its entries in registers and inverts
+// their product with each plane's table; the adjoint adds conj(H_l) times each plane's
+// spectrum in registers and inverts the sum once.  Of L planes' 2 L transforms, L + 1 are
+// left, and the shared side is read (or its sum written) once.  Bound by VALU issue and LDS
+// as with one plane; lengths by planes_chain.
+template <int M, int P, bool CONJ, bool PLANES>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(lds_waves(9 * M)))) void
+k_col_wave(ColIO io, int Hq, int H, int Wp, int Wt, int C, const float2 *__restrict__ twf_y) {
+  using S = ColSteps<M, P>;
+  constexpr int T = S::T, K = S::K, R2 = S::R2, NC = S::NC, KT = (M + T - 1) / T;
+  __shared__ float2 buf[8 * M];
+  __shared__ float2 tw[M];
+  int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: scalar addressing
+  const int b = blockIdx.x;
+  constexpr int SL = 2 * P;  // workgroups of a mirror pair
+  const int slot = (b >> 3) % SL, pi = (b / (8 * SL)) * 8 + (b & 7);
+  const int hp = (Wt + 1) >> 1;
+  if (pi >= C * hp) return;
+  const int ch = pi / hp, pp = pi - ch * hp;
+  const int t = slot < P ? pp : Wt - 1 - pp;
+  if (slot >= P && t == pp) return;  // the middle tile of an odd count has no mirror
+  const int part = slot % P;
+  const size_t off = ((size_t)ch * Wt + t) * H * 8 + part * NC;
+  const float2 *src = io.src + off;
+  float2 *dst = io.dst + off;
+  const int c = wave / P, p = wave % P;
+  float2 *wb = buf + wave * M;
+  // columns past Wp (the last tile of a Wp that is not a multiple of 8) hold
+  // nothing that is read again; their table column is clamped
+  const int kx = min(t * 8 + part * NC + c, Wp - 1);
+  const int qx = min(kx, Wp - kx);
+  const float2 *hcol = io.htab + (size_t)ch * io.hstride + (size_t)qx * Hq;
+  float2 av[K], bv[K];
+  {
+    // every global load of this phase is issued before the first LDS store
+    float2 w1[K], tv[KT];
+    S::load(src, H, tid, av, bv);
+    S::load_w(twf_y, tid, w1);
+#pragma unroll
+    for (int k = 0; k < KT; ++k) tv[k] = at32(twf_y, P * M + min(tid + k * T, M - 1));  // w_M^k
+#pragma unroll
+    for (int k = 0; k < KT; ++k)
+      if (tid + k * T < M) tw[tid + k * T] = tv[k];
+    S::inputs(buf, H, tid, av, bv, w1);
+  }
+  __syncthreads();
+  float2 hv[R2], v[R2];
+  auto times_h = [&](float2 (&o)[R2], bool add) {
+    static_for<0, R2>([&](auto qc) {
+      constexpr int q = decltype(qc)::value;
+      const float2 r = cmul(v[q], CONJ ? cconj(hv[q]) : hv[q]);  // the table carries 1 / (Hp Wp)
+      o[q] = add ? cadd(o[q], r) : r;
+    });
+  };
+  if constexpr (!PLANES) {
+    S::transfer(hcol, p, lane, hv);  // issued before the forward stages
+    S::forward(wb, tw, lane, v);
+    if (lane < S::NB2) times_h(v, false);
+    S::inverse(wb, tw, lane, v);
+    float2 w1[K];
+    S::load_w(twf_y, tid, w1);
+    __syncthreads();
+    S::outputs(buf, dst, H, io.acc, tid, w1);
+  } else if constexpr (!CONJ) {
+    S::transfer(hcol, p, lane, hv);
+    S::forward(wb, tw, lane, v);
+    float2 w1[K], o[R2];
+    for (int l = 0; l < io.planes; ++l) {
+      opaque(tid);
+      opaque(lane);
+      if (l > 0) {
+        S::transfer(hcol + (size_t)l * io.hplane, p, lane, hv);
+        __syncthreads();  // the previous plane's outputs have left LDS
+      }
+      times_h(o, false);
+      S::inverse(wb, tw, lane, o);
+      S::load_w(twf_y, tid, w1);
+      __syncthreads();
+      S::outputs(buf, dst + (size_t)l * io.splane, H, 0, tid, w1);
+    }
+  } else {
+    float2 sum[R2];
+#pragma unroll
+    for (int q = 0; q < R2; ++q) sum[q] = make_float2(0.f, 0.f);
+    // the next plane's columns are loaded ahead where the registers hold them (the sum,
+    // a spectrum and its table values are 6 R2 of the 128)
+    constexpr bool AHEAD = 4 * R2 + 4 * K <= 48;
+    float2 w1[K];
+    for (int l = 0;;) {
+      opaque(tid);
+      opaque(lane);
+      const bool more = l + 1 < io.planes;
+      if (AHEAD && more) S::load(src + (size_t)(l + 1) * io.splane, H, tid, av, bv);
+      if (AHEAD) S::transfer(hcol + (size_t)l * io.hplane, p, lane, hv);
+      S::forward(wb, tw, lane, v);
+      if (!AHEAD) S::transfer(hcol + (size_t)l * io.hplane, p, lane, hv);
+      if (lane < S::NB2) times_h(sum, true);
+      ++l;
+      if (!more) break;
+      if (!AHEAD) S::load(src + (size_t)l * io.splane, H, tid, av, bv);
+      S::load_w(twf_y, tid, w1);
+      __syncthreads();  // every chain has left LDS
+      S::inputs(buf, H, tid, av, bv, w1);
+      __syncthreads();
+    }
+    S::inverse(wb, tw, lane, sum);
+    S::load_w(twf_y, tid, w1);
+    __syncthreads();
+    S::outputs(buf, dst, H, io.acc, tid, w1);
   }
 }
 

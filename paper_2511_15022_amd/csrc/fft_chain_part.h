@@ -65,12 +65,16 @@ void launch_col(const ColArgs &a, hipStream_t s) {
   static_assert(col_plan(M).r2 > 0, "no column plan");
   const int pairs = a.C * ((a.Wt + 1) / 2);
   const dim3 grid((pairs + 7) / 8 * 16 * P), block(512);
-  if (a.conj_h)
-    hipLaunchKernelGGL((k_col_wave<M, P, true>), grid, block, 0, s, a.io, a.Hq, a.H, a.Wp, a.Wt,
-                       a.C, a.twf_y);
-  else
-    hipLaunchKernelGGL((k_col_wave<M, P, false>), grid, block, 0, s, a.io, a.Hq, a.H, a.Wp, a.Wt,
-                       a.C, a.twf_y);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, block, 0, s, a.io, a.Hq, a.H, a.Wp, a.Wt, a.C, a.twf_y);
+  };
+  if constexpr (planes_chain(M, P)) {
+    if (a.io.planes > 1) {
+      a.conj_h ? go(k_col_wave<M, P, true, true>) : go(k_col_wave<M, P, false, true>);
+      return;
+    }
+  }
+  a.conj_h ? go(k_col_wave<M, P, true, false>) : go(k_col_wave<M, P, false, false>);
 }
 
 template <size_t I>

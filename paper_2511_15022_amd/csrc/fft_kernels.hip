@@ -684,12 +684,21 @@ static LossSums loss_sums_of(const Ctx &c, double *loss) {
 int row_split(int Wp, int W) { return split_of(Wp, W, row_chain); }
 int col_split(int Hp, int H) { return split_of(Hp, H, col_chain); }
 
-hipError_t launch_row_fwd(const Ctx &c, const float2 *field, float2 *dst, hipStream_t s) {
+hipError_t launch_row_fwd(const Ctx &c, const float2 *field, float2 *dst, hipStream_t s,
+                          int planes) {
   if (c.row_p) {
+    // planes follow one another as channels do
     RowArgs a = row_args(c, 0);
+    a.rows *= planes;
     a.field = field;
     a.S = dst;
     return launch_row_chain(c, a, s);
+  }
+  if (planes > 1) {
+    const hipError_t e = launch_row_fwd(c, field, dst, s, planes - 1);
+    if (e != hipSuccess) return e;
+    field += (size_t)(planes - 1) * c.CF * c.H * c.W;
+    dst += (planes - 1) * spec_elems(c);
   }
   if (c.Wp == 3840)
     hipLaunchKernelGGL((k_row_fwd_c<3840, 2, 512, false>), dim3(row_blocks(c)), dim3(512), 0, s,
@@ -734,9 +743,16 @@ hipError_t launch_row_inv(const Ctx &c, const float2 *src, float2 *out, hipStrea
   return hipGetLastError();
 }
 
-hipError_t launch_row_loss(const Ctx &c, int plane, float2 *buf, const float *target,
+hipError_t launch_row_loss(const Ctx &c, int plane, int planes, float2 *buf, const float *target,
                            const float *grad_intensity, const float *mask, float *intensity,
                            float2 *u_out, int make_grad, hipStream_t s) {
+  if (!c.row_p && planes > 1) {
+    const hipError_t e = launch_row_loss(c, plane, planes - 1, buf, target, grad_intensity, mask,
+                                         intensity, u_out, make_grad, s);
+    if (e != hipSuccess) return e;
+    plane += planes - 1;
+    buf += (planes - 1) * spec_elems(c);
+  }
   // the loss of each hologram is its own mean over L C H W
   const double M = (double)c.L * c.C * c.H * c.W;
   const float gscale = (float)(4.0 / M);
@@ -752,6 +768,7 @@ hipError_t launch_row_loss(const Ctx &c, int plane, float2 *buf, const float *ta
   double *lp = c.loss_part + (size_t)plane * row_blocks(c);
   if (c.row_p) {
     RowArgs a = row_args(c, 2);
+    a.rows *= planes;
     a.S = buf;
     a.target = target;
     a.grad_I = grad_intensity;
@@ -1011,11 +1028,21 @@ __global__ __launch_bounds__(T) void k_col_half_c(ColIO io, int H, int Wp, int W
   }
 }
 
-hipError_t launch_col_pass(const Ctx &c, int conj_h, int plane, const float2 *src, float2 *dst,
-                           int acc, hipStream_t s) {
+hipError_t launch_col_pass(const Ctx &c, int conj_h, int plane, int planes, const float2 *src,
+                           float2 *dst, int acc, hipStream_t s) {
+  if (planes > 1 && !(c.col_p && planes_chain(c.Hp / c.col_p, c.col_p))) {
+    for (int l = 0; l < planes; ++l) {
+      const size_t o = l * spec_elems(c);
+      const hipError_t e = conj_h ? launch_col_pass(c, 1, plane + l, 1, src + o, dst, acc || l, s)
+                                  : launch_col_pass(c, 0, plane + l, 1, src, dst + o, acc, s);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
   const float scale = (float)(1.0 / ((double)c.Hp * (double)c.Wp));
   const size_t tab = (size_t)c.Hq * c.Wq;
-  const ColIO io{src, dst, c.htab + (size_t)plane * tab, (size_t)c.L * tab, acc};
+  const ColIO io{src, dst, c.htab + (size_t)plane * tab, (size_t)c.L * tab, acc,
+                 planes, tab, spec_elems(c)};
   dim3 grid(c.Wt, c.CF);
   if (c.col_p) {
     const int P = c.col_p, M = c.Hp / P;

@@ -122,3 +122,55 @@ def test_long_rows_match_oracle(O, H, W, Hp, Wp, C):
     ctx = binding.Context(H, W, C, 8e-6, lam, [2e-3], pad=(Hp, Wp), max_gaussians=16)
     _, u = ctx.propagate(torch.from_numpy(f).cuda(), intensity=True, field_out=True)
     assert rel(u.cpu().numpy(), O.propagate(f.astype(np.complex128), opt)) <= TOL
+
+
+PLANES = [
+    # (H, W, Hp, Wp, C, L, pairs): all planes in one pass, with the next plane's columns
+    # loaded ahead (short last radices) and not; chains of two
+    (45, 80, 90, 160, 3, 3, 0),
+    (180, 96, 360, 192, 1, 2, 0),
+    (333, 40, 900, 90, 2, 3, 0),
+    (75, 75, 150, 150, 1, 8, 0),
+    # little memory for the pairs: groups of 1, 1 and 1 planes, and of 2, 2, 2 and 1
+    (90, 200, 180, 400, 2, 3, 64),
+    (60, 64, 120, 128, 1, 7, 3000),
+    # a last radix too long for the shared pass, and shapes with no chain split
+    (600, 9, 1250, 64, 2, 3, 0),
+    (50, 40, 75, 90, 1, 3, 0),
+    (40, 60, 90, 90, 2, 2, 0),
+]
+
+
+@pytest.mark.parametrize("H,W,Hp,Wp,C,L,pairs", PLANES)
+def test_planes_match_oracle(O, H, W, Hp, Wp, C, L, pairs):
+    say("planes", H, W, Hp, Wp, C, L, pairs)
+    zs = [2e-3 - 7e-4 * l for l in range(L)]
+    lam = [639e-9, 515e-9, 473e-9][:C]
+    opt = O.Optics(H, W, C, Hp, Wp, 8e-6, lam, zs)
+    ctx = binding.Context(H, W, C, 8e-6, lam, zs, pad=(Hp, Wp), max_gaussians=1, max_pairs=pairs)
+    rng = np.random.default_rng(11)
+    cplx = lambda *s: (rng.standard_normal(s) + 1j * rng.standard_normal(s)).astype(np.complex64)
+    f, gu = cplx(C, H, W), cplx(L, C, H, W)
+    F = torch.from_numpy(f).cuda()
+    I, u = ctx.propagate(F, intensity=True, field_out=True)
+    ref = O.propagate(f.astype(np.complex128), opt)
+    for l in range(L):
+        assert rel(u[l].cpu().numpy(), ref[l]) <= TOL
+    assert rel(I.cpu().numpy(), np.abs(ref) ** 2) <= TOL
+    g = ctx.propagate_field_adjoint(torch.from_numpy(gu).cuda())
+    assert rel(g.cpu().numpy(), O.propagate_adjoint(gu.astype(np.complex128), opt)) <= TOL
+    gi = rng.random((L, C, H, W)).astype(np.float32)
+    g = ctx.propagate_adjoint(F, torch.from_numpy(gi).cuda())
+    assert rel(g.cpu().numpy(), O.propagate_adjoint(2.0 * gi * ref, opt)) <= GRAD_TOL
+    T = rng.random((L, C, H, W)).astype(np.float32)
+    mask = (rng.random((L, H, W)) < 0.5).astype(np.float32)
+    P = torch.zeros(6 + 2 * C, device="cuda")
+    ctx.rasterize(P, 1)
+    loss = torch.zeros(2, dtype=torch.float64, device="cuda")
+    gf = torch.empty_like(F)
+    ctx.backward(P, 1, F, torch.from_numpy(T).cuda(), loss=loss, grad_field=gf,
+                 mask=torch.from_numpy(mask).cuda())
+    w = 1.0 + mask[:, None].astype(np.float64) ** 2 + T.astype(np.float64) ** 2
+    d = np.abs(ref) ** 2 - T
+    assert abs(loss[0].item() - np.mean(w * d * d)) <= GRAD_TOL * np.mean(w * d * d)
+    assert rel(gf.cpu().numpy(), O.propagate_adjoint(4.0 * w * d * ref / d.size, opt)) <= GRAD_TOL
