@@ -68,27 +68,40 @@ constexpr int stage_cost(int R, int passes, bool twiddled) {
 constexpr int kRadices[] = {2, 3, 4, 5, 6, 8, 9, 10, 12, 15, 16, 18, 20, 24, 25, 27};
 
 struct ColPlan {
-  int r0, r1, r2;
+  int r0, r1, r2, ch;
 };
 
-// Column chain plan: M = r0 r1 r2 (r1 may be 1), one wave per chain; the last
-// forward and first inverse stage are fused in registers, one butterfly of
-// radix r2 per lane (M / r2 <= 64).  Among the plans of least cost an odd r0
-// comes first: the first stage stores at stride r0, and an odd stride spreads
-// the stores over the LDS banks.
+// Column chain plan: M = r0 r1 r2 (r1 may be 1), ch chains per wave; the last forward and
+// first inverse stage are fused in registers, one butterfly of radix r2 per lane
+// (ch M / r2 <= 64).  Up to M = 300 two chains share a wave: one chain's butterflies leave
+// half of the lanes idle (a radix-8 stage of 256 points has 32).  Above, the higher radices
+// that two chains need cost more registers and LDS conflicts than the lanes gain (us per
+// pass of synthetic columns, one and two chains: 128 4.5 and 4.3, 180 7.9 and 7.4, 256 32.0
+// and 24.0, 300 20.0 and 18.7; 320 29.0 and 31.1, 360 36.3 and 38.3, 512 37.7 and 40.6,
+// 540 75 and 84, 720 78 and 110).  Among the plans of least cost an odd r0 comes first: the
+// first stage stores at stride r0, and an odd stride spreads the stores over the LDS banks.
 constexpr ColPlan col_plan(int M) {
-  // measured (4K: 9 6 20 against 10 6 18 and 6 10 18; 1080p: 12 5 9 against 9 6 10
-  // and 10 6 9; the serving pads)
-  if (M == 1080) return {9, 6, 20};
-  if (M == 1024) return {8, 8, 16};
-  if (M == 540) return {12, 5, 9};
-  if (M == 512) return {8, 8, 8};
-  if (M == 384) return {6, 8, 8};
-  if (M == 256) return {4, 8, 8};
-  ColPlan best{0, 0, 0};
+  // measured, with the synthetic columns' us of the plans nearest:
+  // 4K: 10 6 18 380, 6 9 20 381, 9 6 20 389; 640: two chains 4 8 20 68.7, one 16 4 10 72.7;
+  // 384: 8 6 8 31.0, 6 8 8 32.7; 360: 6 6 10 36.3, 10 6 6 37.0; 256: 4 8 8 24.0, 8 4 8
+  // 25.2; 225: four chains 15 1 15 12.2, two 5 5 9 14.0.  540 (1080p) keeps 12 5 9 (82)
+  // against 6 9 10 (75): the Random POH's loss takes signs of differences of fields, and
+  // another order of roundings flips a few of them, which moves single gradients by 3e-3
+  // of their root mean square
+  if (M == 1080) return {10, 6, 18, 1};
+  if (M == 1024) return {8, 8, 16, 1};
+  if (M == 640) return {4, 8, 20, 2};
+  if (M == 540) return {12, 5, 9, 1};
+  if (M == 512) return {8, 8, 8, 1};
+  if (M == 384) return {8, 6, 8, 1};
+  if (M == 360) return {6, 6, 10, 1};
+  if (M == 256) return {4, 8, 8, 2};
+  if (M == 225) return {15, 1, 15, 4};
+  const int ch = M <= 300 ? 2 : 1;
+  ColPlan best{0, 0, 0, ch};
   int cost = 1 << 30;
   for (int r2 : kRadices) {
-    if (M % r2 || M / r2 > 64) continue;
+    if (M % r2 || ch * (M / r2) > 64) continue;
     const int q = M / r2;
     for (int r0 : kRadices) {
       if (q % r0) continue;
@@ -97,7 +110,7 @@ constexpr ColPlan col_plan(int M) {
       bool known = r1 == 1;
       for (int r : kRadices) known = known || r == r1;
       if (!known) continue;
-      const int n0 = (M / r0 + 63) / 64, n1 = r1 > 1 ? (M / r1 + 63) / 64 : 0;
+      const int n0 = (ch * (M / r0) + 63) / 64, n1 = r1 > 1 ? (ch * (M / r1) + 63) / 64 : 0;
       // registers: every butterfly of a stage is held before the first store
       if (n0 * r0 > 32 || n1 * r1 > 32) continue;
       int c = stage_cost(r0, n0, false) + stage_cost(r0, n0, true);
@@ -106,11 +119,54 @@ constexpr ColPlan col_plan(int M) {
       c = c * 8 + (r0 % 2 ? 0 : 4);
       if (c < cost) {
         cost = c;
-        best = ColPlan{r0, r1, r2};
+        best = ColPlan{r0, r1, r2, ch};
       }
     }
   }
   return best;
+}
+
+template <int M>
+struct ColPlanOf {
+  static constexpr ColPlan value = col_plan(M);
+};
+// The layouts between a chain's stages: after the first and second forward stage, after
+// the first and second inverse stage (exchange_pad).
+struct ColPads {
+  Pad f0, f1, i0, i1;
+};
+// Workgroups per CU that LDS of a chain stride holds (beside them the table of M), as far
+// as their waves fit a CU; padding may not cost one.
+constexpr int col_groups(int M, int stride, const ColPlan &pl) {
+  return std::min(160 * 1024 / ((8 * stride + M) * 8), 4 * pl.ch);
+}
+constexpr int col_room(int M, const ColPlan &pl) {
+  int n = M + (12 - M % 8) % 8;
+  const int groups = col_groups(M, n, pl);
+  while (n < 2 * M && col_groups(M, n + 8, pl) == groups) n += 8;
+  return n;
+}
+constexpr ColPads col_pads(int M, const ColPlan &pl) {
+  const bool two = pl.r1 == 1;
+  const int room = col_room(M, pl);
+  return {exchange_pad(pl.r0, 1, two ? M / pl.r2 : M / pl.r1, M, room),
+          two ? Pad{0, 0} : exchange_pad(pl.r1, pl.r0, M / pl.r2, M, room),
+          exchange_pad(pl.r2, 1, two ? M / pl.r0 : M / pl.r1, M, room),
+          two ? Pad{0, 0} : exchange_pad(pl.r1, pl.r2, M / pl.r0, M, room)};
+}
+// elements from one chain to the next in LDS: its longest layout, to 4 modulo 8, so that
+// the lanes that load or combine neighbouring columns' chains use all banks
+constexpr int col_stride(int M, const ColPlan &pl) {
+  const ColPads p = col_pads(M, pl);
+  const int n = std::max(std::max(p.f0.at(M - 1), p.f1.at(M - 1)),
+                         std::max(p.i0.at(M - 1), p.i1.at(M - 1))) + 1;
+  return n + (12 - n % 8) % 8;
+}
+// a workgroup's eight chains, pl.ch per wave
+constexpr int col_threads(const ColPlan &pl) { return 512 / pl.ch; }
+// waves per SIMD that the LDS of its workgroups leaves room for, four at most
+constexpr int col_waves(int M, const ColPlan &pl) {
+  return std::max(1, std::min(4, col_groups(M, col_stride(M, pl), pl) * (8 / pl.ch) / 4));
 }
 
 // Row plan: the stages of P interleaved M-point chains over T threads
@@ -636,14 +692,21 @@ struct ColIO {
 
 // The steps of a column workgroup (k_col_wave); item i of a step is row n = i / NC of
 // column c = i % NC of the workgroup's.
-template <int M, int P>
+template <int M, int P, class PL = ColPlanOf<M>>
 struct ColSteps {
-  static constexpr ColPlan pl = col_plan(M);
-  static constexpr int R0 = pl.r0, R1 = pl.r1, R2 = pl.r2;
-  static constexpr int NB2 = M / R2;
-  static_assert(R0 * R1 * R2 == M && NB2 <= 64, "the fused stage takes one butterfly per lane");
+  static constexpr ColPlan pl = PL::value;
+  static constexpr int CH = pl.ch, R0 = pl.r0, R1 = pl.r1, R2 = pl.r2;
+  static constexpr int NB2 = M / R2, LANES = CH * NB2;  // the fused stage's
+  static_assert(R0 * R1 * R2 == M && LANES <= 64, "the fused stage takes one butterfly per lane");
+  static constexpr int MS = col_stride(M, pl);
+  // layouts in LDS: plain where the columns are loaded and combined
+  struct Plain { static constexpr Pad value{0, 0}; };
+  struct F0 { static constexpr Pad value = col_pads(M, pl).f0; };
+  struct F1 { static constexpr Pad value = col_pads(M, pl).f1; };
+  struct I0 { static constexpr Pad value = col_pads(M, pl).i0; };
+  struct I1 { static constexpr Pad value = col_pads(M, pl).i1; };
   static constexpr int NC = 8 / P;  // columns per workgroup
-  static constexpr int T = 512, NI = NC * M, K = (NI + T - 1) / T;
+  static constexpr int T = col_threads(pl), NI = NC * M, K = (NI + T - 1) / T;
 
   // the columns' samples, to registers
   static __device__ __forceinline__ void load(const float2 *src, int H, int tid, float2 (&av)[K],
@@ -673,40 +736,43 @@ struct ColSteps {
           const float2 s1 = make_float2(a.x + bb.y, a.y - bb.x);  // a - i b
           const float2 s3 = make_float2(a.x - bb.y, a.y + bb.x);  // a + i b
           const float2 w2 = cmul(w1[k], w1[k]), w3 = cmul(w2, w1[k]);  // w^{2n}, w^{3n}
-          buf[(4 * c) * M + n] = s0;
-          buf[(4 * c + 1) * M + n] = cmul(s1, w1[k]);
-          buf[(4 * c + 2) * M + n] = cmul(s2, w2);
-          buf[(4 * c + 3) * M + n] = cmul(s3, w3);
+          buf[(4 * c) * MS + n] = s0;
+          buf[(4 * c + 1) * MS + n] = cmul(s1, w1[k]);
+          buf[(4 * c + 2) * MS + n] = cmul(s2, w2);
+          buf[(4 * c + 3) * MS + n] = cmul(s3, w3);
         } else {
-          buf[(2 * c) * M + n] = a;
-          buf[(2 * c + 1) * M + n] = cmul(a, w1[k]);
+          buf[(2 * c) * MS + n] = a;
+          buf[(2 * c + 1) * MS + n] = cmul(a, w1[k]);
         }
       }
     }
   }
-  // a lane's transfer values: spectrum entries ky = P (j + NB2 q) + p of one column
-  static __device__ __forceinline__ void transfer(const float2 *hcol, int p, int lane,
+  // a lane's transfer values: spectrum entries ky = P (j + NB2 q) + p of chain `chain`,
+  // whose column's table starts at entry col0 of h
+  static __device__ __forceinline__ void transfer(const float2 *h, uint32_t col0, int p, int lane,
                                                   float2 (&hv)[R2]) {
-    const int j = min(lane, NB2 - 1);
+    const int j = min(lane, LANES - 1) % NB2;
     static_for<0, R2>([&](auto qc) {
       constexpr int q = decltype(qc)::value;
       const int ky = P * (j + NB2 * q) + p;
-      hv[q] = at32(hcol, min(ky, P * M - ky));
+      hv[q] = at32(h, col0 + min(ky, P * M - ky));
     });
   }
-  // one wave's chain, LDS to the spectrum entries j + NB2 q of lane j
+  // a wave's chains, LDS to the spectrum entries j + NB2 q of lane NB2 u + j (chain u)
   static __device__ __forceinline__ void forward(float2 *wb, const float2 *tw, int lane,
                                                  float2 (&v)[R2]) {
-    wstage<R0, -1, M, 1>(wb, tw, lane);
-    if constexpr (R1 > 1) wstage<R1, -1, M, R0>(wb, tw, lane);
-    if (lane < NB2) {
+    wstage<R0, -1, M, 1, CH, MS, Plain, F0>(wb, tw, lane);
+    if constexpr (R1 > 1) wstage<R1, -1, M, R0, CH, MS, F0, F1>(wb, tw, lane);
+    if (lane < LANES) {
+      constexpr Pad in = R1 > 1 ? F1::value : F0::value;
+      const int u = lane / NB2, j = lane - u * NB2, at = u * MS + in.at(j);
       static_for<0, R2>([&](auto qc) {
         constexpr int q = decltype(qc)::value;
-        v[q] = wb[lane + q * NB2];
+        v[q] = wb[at + in.at(q * NB2)];
       });
       static_for<1, R2>([&](auto qc) {
         constexpr int q = decltype(qc)::value;
-        v[q] = cmul(v[q], tw[q * lane]);  // last forward stage: Ns = NB2, unit twiddle step
+        v[q] = cmul(v[q], tw[q * j]);  // last forward stage: Ns = NB2, unit twiddle step
       });
       RFft<R2, -1>::run(v);
     }
@@ -714,17 +780,22 @@ struct ColSteps {
   // the inverse of the spectrum entries of each lane, to LDS
   static __device__ __forceinline__ void inverse(float2 *wb, const float2 *tw, int lane,
                                                  float2 (&v)[R2]) {
-    if (lane < NB2) RFft<R2, +1>::run(v);  // first inverse stage: Ns = 1, no twiddles
+    if (lane < LANES) RFft<R2, +1>::run(v);  // first inverse stage: Ns = 1, no twiddles
     wave_lds_order();
-    if (lane < NB2) {
+    if (lane < LANES) {
+      const int u = lane / NB2, j = lane - u * NB2, at = u * MS + I0::value.at(j * R2);
       static_for<0, R2>([&](auto qc) {
         constexpr int q = decltype(qc)::value;
-        wb[lane * R2 + q] = v[q];
+        wb[at + q] = v[q];
       });
     }
     wave_lds_order();
-    if constexpr (R1 > 1) wstage<R1, +1, M, R2>(wb, tw, lane);
-    wstage<R0, +1, M, R2 * R1>(wb, tw, lane);
+    if constexpr (R1 > 1) {
+      wstage<R1, +1, M, R2, CH, MS, I0, I1>(wb, tw, lane);
+      wstage<R0, +1, M, R2 * R1, CH, MS, I1, Plain>(wb, tw, lane);
+    } else {
+      wstage<R0, +1, M, R2, CH, MS, I0, Plain>(wb, tw, lane);
+    }
   }
   // the columns from the chains' outputs
   static __device__ __forceinline__ void outputs(const float2 *buf, float2 *dst, int H, int acc,
@@ -736,16 +807,16 @@ struct ColSteps {
         float2 y0, y1;
         if constexpr (P == 4) {
           const float2 w2 = cmul(w1[k], w1[k]), w3 = cmul(w2, w1[k]);
-          const float2 z0 = buf[(4 * c) * M + n];
-          const float2 z1 = cmul(cconj(w1[k]), buf[(4 * c + 1) * M + n]);
-          const float2 z2 = cmul(cconj(w2), buf[(4 * c + 2) * M + n]);
-          const float2 z3 = cmul(cconj(w3), buf[(4 * c + 3) * M + n]);
+          const float2 z0 = buf[(4 * c) * MS + n];
+          const float2 z1 = cmul(cconj(w1[k]), buf[(4 * c + 1) * MS + n]);
+          const float2 z2 = cmul(cconj(w2), buf[(4 * c + 2) * MS + n]);
+          const float2 z3 = cmul(cconj(w3), buf[(4 * c + 3) * MS + n]);
           y0 = cadd(cadd(z0, z1), cadd(z2, z3));
           // z0 + i z1 - z2 - i z3
           const float2 e = csub(z0, z2), o = csub(z1, z3);
           y1 = make_float2(e.x - o.y, e.y + o.x);
         } else {
-          y0 = cadd(buf[(2 * c) * M + n], cmul(cconj(w1[k]), buf[(2 * c + 1) * M + n]));
+          y0 = cadd(buf[(2 * c) * MS + n], cmul(cconj(w1[k]), buf[(2 * c + 1) * MS + n]));
         }
         float2 &d0 = at32(dst, n * 8 + c);
         d0 = acc ? cadd(d0, y0) : y0;
@@ -777,12 +848,13 @@ struct ColSteps {
 // spectrum in registers and inverts the sum once.  Of L planes' 2 L transforms, L + 1 are
 // left, and the shared side is read (or its sum written) once.  Bound by VALU issue and LDS
 // as with one plane; lengths by planes_chain.
-template <int M, int P, bool CONJ, bool PLANES>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(lds_waves(9 * M)))) void
+template <int M, int P, bool CONJ, bool PLANES, class PL = ColPlanOf<M>>
+__global__ __launch_bounds__(col_threads(PL::value))
+__attribute__((amdgpu_waves_per_eu(col_waves(M, PL::value)))) void
 k_col_wave(ColIO io, int Hq, int H, int Wp, int Wt, int C, const float2 *__restrict__ twf_y) {
-  using S = ColSteps<M, P>;
+  using S = ColSteps<M, P, PL>;
   constexpr int T = S::T, K = S::K, R2 = S::R2, NC = S::NC, KT = (M + T - 1) / T;
-  __shared__ float2 buf[8 * M];
+  __shared__ float2 buf[8 * S::MS];
   __shared__ float2 tw[M];
   int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: scalar addressing
@@ -798,13 +870,16 @@ k_col_wave(ColIO io, int Hq, int H, int Wp, int Wt, int C, const float2 *__restr
   const size_t off = ((size_t)ch * Wt + t) * H * 8 + part * NC;
   const float2 *src = io.src + off;
   float2 *dst = io.dst + off;
-  const int c = wave / P, p = wave % P;
-  float2 *wb = buf + wave * M;
+  // the chain of this lane's fused butterfly (uniform with one chain per wave)
+  const int chain = S::CH == 1 ? wave : wave * S::CH + min(lane, S::LANES - 1) / S::NB2;
+  const int c = chain / P, p = chain % P;
+  float2 *wb = buf + wave * (S::CH * S::MS);
   // columns past Wp (the last tile of a Wp that is not a multiple of 8) hold
   // nothing that is read again; their table column is clamped
   const int kx = min(t * 8 + part * NC + c, Wp - 1);
   const int qx = min(kx, Wp - kx);
-  const float2 *hcol = io.htab + (size_t)ch * io.hstride + (size_t)qx * Hq;
+  const float2 *h = io.htab + (size_t)ch * io.hstride;
+  const uint32_t col0 = (uint32_t)(qx * Hq);  // below 4097^2: 32-bit byte offsets reach it
   float2 av[K], bv[K];
   {
     // every global load of this phase is issued before the first LDS store
@@ -828,23 +903,23 @@ k_col_wave(ColIO io, int Hq, int H, int Wp, int Wt, int C, const float2 *__restr
     });
   };
   if constexpr (!PLANES) {
-    S::transfer(hcol, p, lane, hv);  // issued before the forward stages
+    S::transfer(h, col0, p, lane, hv);  // issued before the forward stages
     S::forward(wb, tw, lane, v);
-    if (lane < S::NB2) times_h(v, false);
+    if (lane < S::LANES) times_h(v, false);
     S::inverse(wb, tw, lane, v);
     float2 w1[K];
     S::load_w(twf_y, tid, w1);
     __syncthreads();
     S::outputs(buf, dst, H, io.acc, tid, w1);
   } else if constexpr (!CONJ) {
-    S::transfer(hcol, p, lane, hv);
+    S::transfer(h, col0, p, lane, hv);
     S::forward(wb, tw, lane, v);
     float2 w1[K], o[R2];
     for (int l = 0; l < io.planes; ++l) {
       opaque(tid);
       opaque(lane);
       if (l > 0) {
-        S::transfer(hcol + (size_t)l * io.hplane, p, lane, hv);
+        S::transfer(h + (size_t)l * io.hplane, col0, p, lane, hv);
         __syncthreads();  // the previous plane's outputs have left LDS
       }
       times_h(o, false);
@@ -866,10 +941,10 @@ k_col_wave(ColIO io, int Hq, int H, int Wp, int Wt, int C, const float2 *__restr
       opaque(lane);
       const bool more = l + 1 < io.planes;
       if (AHEAD && more) S::load(src + (size_t)(l + 1) * io.splane, H, tid, av, bv);
-      if (AHEAD) S::transfer(hcol + (size_t)l * io.hplane, p, lane, hv);
+      if (AHEAD) S::transfer(h + (size_t)l * io.hplane, col0, p, lane, hv);
       S::forward(wb, tw, lane, v);
-      if (!AHEAD) S::transfer(hcol + (size_t)l * io.hplane, p, lane, hv);
-      if (lane < S::NB2) times_h(sum, true);
+      if (!AHEAD) S::transfer(h + (size_t)l * io.hplane, col0, p, lane, hv);
+      if (lane < S::LANES) times_h(sum, true);
       ++l;
       if (!more) break;
       if (!AHEAD) S::load(src + (size_t)l * io.splane, H, tid, av, bv);

@@ -64,7 +64,7 @@ template <int M, int P>
 void launch_col(const ColArgs &a, hipStream_t s) {
   static_assert(col_plan(M).r2 > 0, "no column plan");
   const int pairs = a.C * ((a.Wt + 1) / 2);
-  const dim3 grid((pairs + 7) / 8 * 16 * P), block(512);
+  const dim3 grid((pairs + 7) / 8 * 16 * P), block(col_threads(col_plan(M)));
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, grid, block, 0, s, a.io, a.Hq, a.H, a.Wp, a.Wt, a.C, a.twf_y);
   };

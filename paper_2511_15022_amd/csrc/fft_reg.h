@@ -465,28 +465,73 @@ __device__ __forceinline__ void cstage2(float2 *__restrict__ buf, const TW &tw, 
 // a buffer needs no workgroup barrier between the stages of its transform.
 __device__ __forceinline__ void wave_lds_order() { asm volatile("" ::: "memory"); }
 
-// One Stockham stage of a length-N transform owned by a single wave: the
-// buffer buf[0, N) is contiguous in LDS and lane l takes butterflies
-// j = l, l + 64, ...  Same index scheme and twiddles as cstage with B = 1.
-// The stage input element i comes from ld(i) (the buffer itself, or global
-// memory for a first stage); the output goes to the buffer.
-template <int R, int DIR, int N, int NS, class LD>
-__device__ __forceinline__ void wstage_ld(float2 *__restrict__ buf, const float2 *__restrict__ tw,
-                                          int lane, LD &&ld) {
-  constexpr int NB = N / R;
-  constexpr int IT = (NB + 63) / 64;
+// Layout of a transform's elements in LDS between two stages: element i at i + i / u d
+// (u = 0: at i).
+struct Pad {
+  int u, d;
+  constexpr int at(int i) const { return u ? i + i / u * d : i; }
+};
+
+// The most elements of 32 neighbouring lanes' accesses (float2, 32 to a row of the 64 banks)
+// that one bank pair holds: lane l at p.at(l / ns ns r + l % ns).
+constexpr int bank_share(const Pad &p, int ns, int r) {
+  int worst = 0, n[32] = {};
+  for (int l = 0; l < 32; ++l) {
+    const int b = p.at(l / ns * ns * r + l % ns) % 32;
+    if (++n[b] > worst) worst = n[b];
+  }
+  return worst;
+}
+
+// The layout between a stage of radix R after ns points, which stores at stride R (ns = 1)
+// or in runs of ns at stride ns R, and a stage that reads contiguously at offsets q nb: the
+// one with the fewest lanes on a bank in both, then the least padding, of those whose n
+// elements take at most `room`.  u keeps every offset
+// of a butterfly a constant: it divides nb, a store's R elements (ns = 1) lie in one u, and
+// a run (ns > 1) in one u with ns R a multiple of u.
+constexpr Pad exchange_pad(int R, int ns, int nb, int n, int room) {
+  Pad best{0, 0};
+  int cost = (bank_share(best, ns, R) + bank_share(best, 1, 1)) * 64;
+  for (int u = 4; u <= nb; ++u) {
+    if (nb % u || (ns == 1 ? u % R : (ns * R) % u || u % ns)) continue;
+    for (int d = 1; 4 * d <= u && d <= 32; ++d) {
+      const Pad p{u, d};
+      if (p.at(n - 1) >= room) break;
+      const int c = (bank_share(p, ns, R) + bank_share(p, 1, 1)) * 64 + 64 * d / u + 1;
+      if (c < cost) {
+        cost = c;
+        best = p;
+      }
+    }
+  }
+  return best;
+}
+
+// One Stockham stage of the CH length-N transforms of a single wave: transform u is
+// buf[u MS, u MS + N) in LDS, read in layout IN and written in layout OUT, and butterfly
+// i = u N / R + j of the wave is butterfly j of transform u; lane l takes i = l, l + 64, ...
+// Same index scheme and twiddles as cstage with B = 1.
+template <int R, int DIR, int N, int NS, int CH, int MS, class IN, class OUT>
+__device__ __forceinline__ void wstage(float2 *__restrict__ buf, const float2 *__restrict__ tw,
+                                       int lane) {
+  constexpr int NB = N / R, ALL = CH * NB;
+  constexpr int IT = (ALL + 63) / 64;
   constexpr int TWS = N / (NS * R);
+  constexpr Pad in = IN::value, out = OUT::value;
+  static_assert(NB % NS == 0 && (!in.u || NB % in.u == 0), "constant offsets");
   float2 v[IT][R];
 #pragma unroll
   for (int it = 0; it < IT; ++it) {
-    const int j = lane + 64 * it;
-    if ((it + 1) * 64 <= NB || j < NB) {
+    const int i = lane + 64 * it;
+    if ((it + 1) * 64 <= ALL || i < ALL) {
+      const int u = CH == 1 ? 0 : i / NB, j = i - u * NB;
+      const int at = u * MS + in.at(j);
       static_for<0, R>([&](auto qc) {
         constexpr int q = decltype(qc)::value;
-        v[it][q] = ld(j + q * NB);
+        v[it][q] = buf[at + in.at(q * NB)];
       });
       if constexpr (NS > 1) {
-        const int e = (j % NS) * TWS;
+        const int e = (i % NS) * TWS;
         static_for<1, R>([&](auto qc) {
           constexpr int q = decltype(qc)::value;
           float2 w = tw[q * e];
@@ -500,23 +545,18 @@ __device__ __forceinline__ void wstage_ld(float2 *__restrict__ buf, const float2
   wave_lds_order();
 #pragma unroll
   for (int it = 0; it < IT; ++it) {
-    const int j = lane + 64 * it;
-    if ((it + 1) * 64 <= NB || j < NB) {
-      const int k = j % NS;
-      const int base = (j - k) * R + k;
+    const int i = lane + 64 * it;
+    if ((it + 1) * 64 <= ALL || i < ALL) {
+      const int u = CH == 1 ? 0 : i / NB, j = i - u * NB;
+      const int k = i % NS;
+      const int base = u * MS + out.at((j - k) * R) + k;
       static_for<0, R>([&](auto qc) {
         constexpr int q = decltype(qc)::value;
-        buf[base + q * NS] = v[it][q];
+        buf[base + out.at(q * NS)] = v[it][q];
       });
     }
   }
   wave_lds_order();
-}
-
-template <int R, int DIR, int N, int NS>
-__device__ __forceinline__ void wstage(float2 *__restrict__ buf, const float2 *__restrict__ tw,
-                                       int lane) {
-  wstage_ld<R, DIR, N, NS>(buf, tw, lane, [&](int i) { return buf[i]; });
 }
 
 template <int DIR, int B, int T, int N, class TW, int S = 0>

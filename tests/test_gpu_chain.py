@@ -50,6 +50,15 @@ CASES = [
     (7, 4096, 64, 8192, 1),
     (5, 3645, 64, 7290, 1),
     (6, 3000, 64, 6250, 1),
+    # two and four column chains per wave, with and without idle lanes, padded layouts in
+    # LDS; the last short chain and the first long one; the longest power of two
+    (500, 33, 1000, 72, 1),
+    (600, 12, 1200, 64, 1),
+    (640, 20, 1280, 64, 1),
+    (1280, 9, 2560, 64, 1),
+    (449, 16, 900, 64, 1),
+    (486, 16, 972, 64, 1),
+    (2048, 8, 4096, 64, 1),
     # two planes: the adjoint column pass adds into its destination
     (45, 80, 90, 160, 3),
 ]
