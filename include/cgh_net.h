@@ -82,6 +82,23 @@ cgh_status cgh_net_conv3x3_wgrad(const cgh_bf16 *x1, int32_t c1, int32_t up, con
                                  int32_t cout, float *gw, float *gb, void *workspace,
                                  size_t workspace_bytes, void *stream);
 
+/* The same in two parts, so that the sums of several layers take one launch:
+ * cgh_net_wgrad_shares writes the partial sums to `shares`
+ * (>= cgh_net_wgrad_shares_bytes bytes, else CGH_ERR_WORKSPACE; 16-byte aligned, as gy
+ * must be), and cgh_net_wgrad_sums adds those of `count` layers, each to its gw and gb
+ * (gb may be NULL).  Values as cgh_net_conv3x3_wgrad's.  The shares must stay as they
+ * are until the sums have run. */
+typedef struct {
+  int32_t H, W, cin, cout;
+  const void *shares;
+  float *gw, *gb;
+} cgh_net_wgrad_job;
+size_t cgh_net_wgrad_shares_bytes(int32_t H, int32_t W, int32_t cin, int32_t cout);
+cgh_status cgh_net_wgrad_shares(const cgh_bf16 *x1, int32_t c1, int32_t up, const cgh_bf16 *x2,
+                                int32_t c2, int32_t H, int32_t W, const cgh_bf16 *gy,
+                                int32_t cout, void *shares, size_t shares_bytes, void *stream);
+cgh_status cgh_net_wgrad_sums(const cgh_net_wgrad_job *jobs, int32_t count, void *stream);
+
 /* out[i] = BF16(x[i]) (round to nearest, ties to even), i < count. */
 cgh_status cgh_net_cast_bf16(const float *x, int64_t count, cgh_bf16 *out, void *stream);
 

@@ -99,6 +99,13 @@ _SIGS = [
 ]
 # entry points of include/cgh_net.h (the learned initialiser's network)
 _I32, _I64, _SZ = ctypes.c_int32, ctypes.c_int64, ctypes.c_size_t
+
+
+class cgh_net_wgrad_job(ctypes.Structure):
+    _fields_ = [("H", _I32), ("W", _I32), ("cin", _I32), ("cout", _I32),
+                ("shares", _VP), ("gw", _VP), ("gb", _VP)]
+
+
 _NET_SIGS = [
     ("cgh_net_conv3x3", ctypes.c_int,
      [_VP, _I32, _I32, _VP, _I32, _I32, _I32, _VP, _VP, _I32, _I32, _VP, _VP, _VP]),
@@ -110,6 +117,10 @@ _NET_SIGS = [
     ("cgh_net_wgrad_workspace", ctypes.c_size_t, [_I32, _I32, _I32, _I32]),
     ("cgh_net_conv3x3_wgrad", ctypes.c_int,
      [_VP, _I32, _I32, _VP, _I32, _I32, _I32, _VP, _I32, _VP, _VP, _VP, _SZ, _VP]),
+    ("cgh_net_wgrad_shares_bytes", ctypes.c_size_t, [_I32, _I32, _I32, _I32]),
+    ("cgh_net_wgrad_shares", ctypes.c_int,
+     [_VP, _I32, _I32, _VP, _I32, _I32, _I32, _VP, _I32, _VP, _SZ, _VP]),
+    ("cgh_net_wgrad_sums", ctypes.c_int, [ctypes.POINTER(cgh_net_wgrad_job), _I32, _VP]),
     ("cgh_net_cast_bf16", ctypes.c_int, [_VP, _I64, _VP, _VP]),
     ("cgh_net_relu_grad", ctypes.c_int, [_VP, _VP, _I64, _VP, _VP]),
     ("cgh_net_pool2", ctypes.c_int, [_VP, _I32, _I32, _I32, _VP, _VP]),

@@ -531,8 +531,8 @@ hipError_t launch_conv(ConvArgs a, hipStream_t s) {
 // LDS reads bound the products (44 transposed reads for 36 matrix instructions); two
 // workgroups per CU cover each other's loads.  Measured at 512 x 512 RGB, all 15
 // layers: staging copies, products and reduction 1222 us before (one wave per range
-// of pixels, operands from global memory), now 298 us of products and 112 us of
-// reduction.
+// of pixels, operands from global memory), now 298 us of products and 59 us of
+// reduction (k_wgrad_reduce).
 // ----------------------------------------------------------------------------
 struct WgradArgs {
   const uint16_t *x1, *x2, *gy;
@@ -703,78 +703,102 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3_wgrad(WgradArgs a) {
   }
 }
 
-// Fixed-order sum over many shares (more than kFewShares): a workgroup takes 16
-// outputs with 16 lanes each; lane g of an output adds shares g, g + 16, ... in order
-// (sixteen loads in flight), then one lane adds the 16 lane sums in order.  Outputs
-// i < len are the weight gradients; the workgroups with i < cout also sum the bias
-// partials the same way.
+// Fixed-order sum over many shares (more than kFewShares): a workgroup takes 64 outputs,
+// four consecutive ones per lane, with 16 lanes each; lane g of an output adds shares g,
+// g + 16, ... in order (sixteen loads in flight), then one lane adds the 16 lane sums in
+// order.  Outputs i < len are the weight gradients; the workgroups with i < cout also sum
+// the bias partials the same way.  Bound by the reads of the shares.
 constexpr int kFewShares = 16;
 
-__device__ __forceinline__ float shares_sum(const float *__restrict__ part, int64_t stride,
-                                            int splits, int g) {
-  float s = 0.f;
+__device__ __forceinline__ float4 shares_sum(const float *__restrict__ part, int64_t stride,
+                                             int splits, int g) {
+  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
   for (int k = g; k < splits; k += 256) {
-    float v[16];
+    float4 v[16];
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
       const int kk = k + 16 * j;
-      v[j] = kk < splits ? part[(size_t)kk * stride] : 0.f;
+      v[j] = kk < splits ? *reinterpret_cast<const float4 *>(part + (size_t)kk * stride)
+                         : make_float4(0.f, 0.f, 0.f, 0.f);
     }
 #pragma unroll
-    for (int j = 0; j < 16; ++j) s += v[j];
+    for (int j = 0; j < 16; ++j)
+      s = make_float4(s.x + v[j].x, s.y + v[j].y, s.z + v[j].z, s.w + v[j].w);
   }
   return s;
 }
 
-__global__ __launch_bounds__(256) void k_wgrad_reduce(const float *__restrict__ part,
-                                                      const float *__restrict__ part_b,
-                                                      int splits, int64_t len, int cout,
-                                                      float *__restrict__ gw,
-                                                      float *__restrict__ gb) {
-  __shared__ float red[16][17];
+// One layer's shares and where their sums go; its workgroups are blocks
+// [first, next job's first).
+struct SumJob {
+  const float *part, *part_b;
+  float *gw, *gb;
+  int64_t len;
+  int splits, cout;
+  unsigned first;
+};
+constexpr int kSumJobs = 16;
+struct SumJobs {
+  SumJob job[kSumJobs];
+  int count;
+};
+
+__device__ __forceinline__ void sum_many(const SumJob &a, unsigned block) {
+  __shared__ float4 red[16][17];
   const int o = threadIdx.x & 15, g = threadIdx.x >> 4;
-  const int64_t i = (int64_t)blockIdx.x * 16 + o;
-  red[g][o] = i < len ? shares_sum(part + i, len, splits, g) : 0.f;
+  const int64_t i = (int64_t)block * 64 + 4 * o;  // len and cout are multiples of 4
+  const auto total = [&](float *out) {
+    float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int q = 0; q < 16; ++q) {
+      const float4 v = red[q][o];
+      t = make_float4(t.x + v.x, t.y + v.y, t.z + v.z, t.w + v.w);
+    }
+    out[0] = t.x; out[1] = t.y; out[2] = t.z; out[3] = t.w;  // (need not be 16-byte aligned)
+  };
+  if (i < a.len) red[g][o] = shares_sum(a.part + i, a.len, a.splits, g);
   __syncthreads();
-  if (g == 0 && i < len) {
-    float t = 0.f;
-    for (int q = 0; q < 16; ++q) t += red[q][o];
-    gw[i] = t;
-  }
-  if (gb == nullptr || (int64_t)blockIdx.x * 16 >= cout) return;  // uniform per workgroup
+  if (g == 0 && i < a.len) total(a.gw + i);
+  if (a.gb == nullptr || (int64_t)block * 64 >= a.cout) return;  // uniform per workgroup
   __syncthreads();
-  red[g][o] = i < cout ? shares_sum(part_b + i, cout, splits, g) : 0.f;
+  if (i < a.cout) red[g][o] = shares_sum(a.part_b + i, a.cout, a.splits, g);
   __syncthreads();
-  if (g == 0 && i < cout) {
-    float t = 0.f;
-    for (int q = 0; q < 16; ++q) t += red[q][o];
-    gb[i] = t;
-  }
+  if (g == 0 && i < a.cout) total(a.gb + i);
 }
 
 // The same for at most kFewShares shares: four consecutive outputs per thread, the
 // shares in order; the threads after the weight gradients' take the biases, one each.
 // len is a multiple of 4 (cout is one of 8).
-__global__ __launch_bounds__(256) void k_wgrad_reduce_few(const float *__restrict__ part,
-                                                          const float *__restrict__ part_b,
-                                                          int splits, int64_t len, int cout,
-                                                          float *__restrict__ gw,
-                                                          float *__restrict__ gb) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x, n4 = len / 4;
+__device__ __forceinline__ void sum_few(const SumJob &a, unsigned block) {
+  const int64_t i = (int64_t)block * 256 + threadIdx.x, n4 = a.len / 4;
   if (i < n4) {
     float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll 8
-    for (int k = 0; k < splits; ++k) {
-      const float4 v = *reinterpret_cast<const float4 *>(part + (size_t)k * len + 4 * i);
+    for (int k = 0; k < a.splits; ++k) {
+      const float4 v = *reinterpret_cast<const float4 *>(a.part + (size_t)k * a.len + 4 * i);
       s = make_float4(s.x + v.x, s.y + v.y, s.z + v.z, s.w + v.w);
     }
-    float *d = gw + 4 * i;  // (gw need not be 16-byte aligned)
+    float *d = a.gw + 4 * i;  // (gw need not be 16-byte aligned)
     d[0] = s.x; d[1] = s.y; d[2] = s.z; d[3] = s.w;
-  } else if (gb && i < n4 + cout) {
+  } else if (a.gb && i < n4 + a.cout) {
     float s = 0.f;
-    for (int k = 0; k < splits; ++k) s += part_b[(size_t)k * cout + (i - n4)];
-    gb[i - n4] = s;
+    for (int k = 0; k < a.splits; ++k) s += a.part_b[(size_t)k * a.cout + (i - n4)];
+    a.gb[i - n4] = s;
   }
+}
+
+// The sums of one or several layers.  A layer's shares are 5 to 19 MB, which a launch of
+// its own added in 7.5 us, much of it start and drain: the 15 layers of 512 x 512 RGB
+// took 109 us in 15 launches, 85 us in two (those with one float per lane and load), and
+// take 59 us in two with four (247 MB: 4.2 TB/s; 5.2 TB/s is a large copy's rate).
+__global__ __launch_bounds__(256) void k_wgrad_reduce(SumJobs js) {
+  int k = 0;
+  while (k + 1 < js.count && blockIdx.x >= js.job[k + 1].first) ++k;
+  const SumJob &a = js.job[k];
+  const unsigned block = blockIdx.x - a.first;
+  if (a.splits <= kFewShares)
+    sum_few(a, block);
+  else
+    sum_many(a, block);
 }
 
 __global__ void k_flip(const uint16_t *__restrict__ w, int cout, int cin,
@@ -1002,6 +1026,7 @@ unsigned blocks_of(int64_t n, int t) { return (unsigned)((n + t - 1) / t); }
 struct WgPlan {
   int tiles_x, tiles, splits;
   size_t part, part_b, bytes;
+  size_t shares_b, shares;  // the shares alone: the bias's offset, bytes
 };
 size_t round256(size_t b) { return (b + 255) & ~(size_t)255; }
 WgPlan wgrad_plan(int H, int W, int cin, int cout) {
@@ -1021,6 +1046,8 @@ WgPlan wgrad_plan(int H, int W, int cin, int cout) {
   const size_t len = (size_t)cout * 9 * cin;
   p.part = 0;
   p.part_b = round256(room * len * sizeof(float));
+  p.shares_b = round256((size_t)p.splits * len * sizeof(float));
+  p.shares = p.shares_b + round256((size_t)p.splits * cout * sizeof(float));
   p.bytes = p.part_b + round256((size_t)room * cout * sizeof(float)) +
             round256((size_t)cout * H * Wr * sizeof(uint16_t)) +
             round256((size_t)3 * cin * (H + 2) * Wr * sizeof(uint16_t));
@@ -1114,11 +1141,33 @@ size_t cgh_net_wgrad_workspace(int32_t H, int32_t W, int32_t cin, int32_t cout) 
   return wgrad_plan(H, W, cin, cout).bytes;
 }
 
+// the products of one layer's weight gradient: a share of the sums per workgroup plane
+static cgh_status wgrad_shares(const cgh_bf16 *x1, int c1, int up, const cgh_bf16 *x2, int c2,
+                               int H, int W, const cgh_bf16 *gy, int cout, const WgPlan &pl,
+                               float *part, float *part_b, hipStream_t s) {
+  const int cin = c1 + c2;
+  const WgradArgs wa{x1, x2, gy,   c1,         c2,       up,        H,
+                     W,  cout, pl.tiles_x, pl.tiles, pl.splits, part, part_b};
+  hipLaunchKernelGGL(k_conv3x3_wgrad, dim3((cin + 31) / 32, (cout + 31) / 32, pl.splits),
+                     dim3(256), 0, s, wa);
+  NET_LAUNCHED("conv3x3_wgrad");
+  return CGH_OK;
+}
+
+// appends a layer's sums to js; returns the workgroups so far
+static unsigned add_sums(SumJobs &js, unsigned blocks, const float *part, const float *part_b,
+                         int splits, int cin, int cout, float *gw, float *gb) {
+  const int64_t len = (int64_t)cout * 9 * cin;
+  js.job[js.count++] = SumJob{part, part_b, gw, gb, len, splits, cout, blocks};
+  return blocks + (splits <= kFewShares ? blocks_of(len / 4 + cout, 256)
+                                        : blocks_of(std::max<int64_t>(len, cout), 64));
+}
+
 cgh_status cgh_net_conv3x3_wgrad(const cgh_bf16 *x1, int32_t c1, int32_t up, const cgh_bf16 *x2,
                                  int32_t c2, int32_t H, int32_t W, const cgh_bf16 *gy,
                                  int32_t cout, float *gw, float *gb, void *workspace,
                                  size_t workspace_bytes, void *stream) {
-  const cgh_status st = check_conv_shape(x1, c1, up, x2, c2, H, W);
+  cgh_status st = check_conv_shape(x1, c1, up, x2, c2, H, W);
   if (st != CGH_OK) return st;
   NET_CHECK(gy && gw && cout > 0 && cout % 8 == 0, "gy/gw NULL or cout = %d not a multiple of 8",
             cout);
@@ -1128,22 +1177,59 @@ cgh_status cgh_net_conv3x3_wgrad(const cgh_bf16 *x1, int32_t c1, int32_t up, con
     return report(CGH_ERR_WORKSPACE, "wgrad workspace has %zu bytes, needs %zu", workspace_bytes,
                   pl.bytes);
   NET_CHECK(al16(workspace) && al16(gy), "workspace and gy must be 16-byte aligned");
-  const int64_t len = (int64_t)cout * 9 * cin;
-  char *base = (char *)workspace;
-  const WgradArgs wa{x1,  x2,   gy,        c1,        c2,        up,
-                     H,   W,    cout,      pl.tiles_x, pl.tiles, pl.splits,
-                     (float *)(base + pl.part), (float *)(base + pl.part_b)};
+  float *part = (float *)((char *)workspace + pl.part);
+  float *part_b = (float *)((char *)workspace + pl.part_b);
   hipStream_t s = (hipStream_t)stream;
-  hipLaunchKernelGGL(k_conv3x3_wgrad, dim3((cin + 31) / 32, (cout + 31) / 32, pl.splits),
-                     dim3(256), 0, s, wa);
-  NET_LAUNCHED("conv3x3_wgrad");
-  if (pl.splits <= kFewShares)
-    hipLaunchKernelGGL(k_wgrad_reduce_few, dim3(blocks_of(len / 4 + cout, 256)), dim3(256), 0, s,
-                       wa.part, wa.part_b, pl.splits, len, cout, gw, gb);
-  else
-    hipLaunchKernelGGL(k_wgrad_reduce, dim3(blocks_of(std::max<int64_t>(len, cout), 16)),
-                       dim3(256), 0, s, wa.part, wa.part_b, pl.splits, len, cout, gw, gb);
+  st = wgrad_shares(x1, c1, up, x2, c2, H, W, gy, cout, pl, part, part_b, s);
+  if (st != CGH_OK) return st;
+  SumJobs js{};
+  const unsigned blocks = add_sums(js, 0, part, part_b, pl.splits, cin, cout, gw, gb);
+  hipLaunchKernelGGL(k_wgrad_reduce, dim3(blocks), dim3(256), 0, s, js);
   NET_LAUNCHED("wgrad_reduce");
+  return CGH_OK;
+}
+
+size_t cgh_net_wgrad_shares_bytes(int32_t H, int32_t W, int32_t cin, int32_t cout) {
+  if (H < 1 || W < 1 || cin < 1 || cout < 1) return 0;
+  return wgrad_plan(H, W, cin, cout).shares;
+}
+
+cgh_status cgh_net_wgrad_shares(const cgh_bf16 *x1, int32_t c1, int32_t up, const cgh_bf16 *x2,
+                                int32_t c2, int32_t H, int32_t W, const cgh_bf16 *gy,
+                                int32_t cout, void *shares, size_t shares_bytes, void *stream) {
+  const cgh_status st = check_conv_shape(x1, c1, up, x2, c2, H, W);
+  if (st != CGH_OK) return st;
+  NET_CHECK(gy && cout > 0 && cout % 8 == 0, "gy NULL or cout = %d not a multiple of 8", cout);
+  const WgPlan pl = wgrad_plan(H, W, c1 + c2, cout);
+  if (!shares || shares_bytes < pl.shares)
+    return report(CGH_ERR_WORKSPACE, "the shares have %zu bytes, need %zu", shares_bytes,
+                  pl.shares);
+  NET_CHECK(al16(shares) && al16(gy), "shares and gy must be 16-byte aligned");
+  return wgrad_shares(x1, c1, up, x2, c2, H, W, gy, cout, pl, (float *)shares,
+                      (float *)((char *)shares + pl.shares_b), (hipStream_t)stream);
+}
+
+cgh_status cgh_net_wgrad_sums(const cgh_net_wgrad_job *jobs, int32_t count, void *stream) {
+  NET_CHECK(count >= 0 && (count == 0 || jobs), "bad arguments");
+  for (int k = 0; k < count; ++k) {
+    const cgh_net_wgrad_job &j = jobs[k];
+    NET_CHECK(j.H > 0 && j.W > 0 && j.cin > 0 && j.cin % 8 == 0 && j.cout > 0 && j.cout % 8 == 0,
+              "job %d: bad shape", k);
+    NET_CHECK(j.shares && j.gw && al16(j.shares), "job %d: shares/gw NULL or misaligned", k);
+  }
+  for (int k = 0; k < count;) {
+    SumJobs js{};
+    unsigned blocks = 0;
+    for (; k < count && js.count < kSumJobs; ++k) {
+      const cgh_net_wgrad_job &j = jobs[k];
+      const WgPlan pl = wgrad_plan(j.H, j.W, j.cin, j.cout);
+      blocks = add_sums(js, blocks, (const float *)j.shares,
+                        (const float *)((const char *)j.shares + pl.shares_b), pl.splits, j.cin,
+                        j.cout, j.gw, j.gb);
+    }
+    hipLaunchKernelGGL(k_wgrad_reduce, dim3(blocks), dim3(256), 0, (hipStream_t)stream, js);
+    NET_LAUNCHED("wgrad_reduce");
+  }
   return CGH_OK;
 }
 

@@ -56,6 +56,12 @@ def _p(t):
     return None if t is None else ctypes.c_void_p(t.data_ptr())
 
 
+# Most memory for the weight gradients' shares of layers that wait for one sum: half of
+# the 256 MB last-level cache (512 x 512 RGB pass: 861 us with 32 MB, 851 to 855 us with
+# 64 MB and more).
+SHARES_BYTES = 128 << 20
+
+
 class UNet:
     """The network on one device for an H x W input (H, W divisible by 8)."""
 
@@ -96,10 +102,14 @@ class UNet:
         self.pooled = {l: torch.zeros((H >> (l + 1), W >> (l + 1), widths[l]), dtype=torch.bfloat16,
                                       device=self.dev) for l in range(len(widths) - 1)}
         self.out = torch.zeros((H, W, c_out), **f32)
-        ws = max(self.L.cgh_net_wgrad_workspace(H >> self._lev(nm), W >> self._lev(nm), cu + cs, co)
-                 for nm, cu, cs, co, _ in self.layers)
-        self.scratch = torch.empty(ws // 4 + 64, **f32)
-        self.ws_bytes = ws
+        # the layers' shares of the weight gradients, summed together as many at a time as
+        # fit SHARES_BYTES
+        self.share_bytes = {nm: -(-self.L.cgh_net_wgrad_shares_bytes(
+            H >> self._lev(nm), W >> self._lev(nm), cu + cs, co) // 256) * 256
+            for nm, cu, cs, co, _ in self.layers}
+        self.shares = torch.empty(max(max(self.share_bytes.values()),
+                                      min(sum(self.share_bytes.values()), SHARES_BYTES)),
+                                  dtype=torch.uint8, device=self.dev)
         self.set_weights(he_weights(self.layers, seed))
 
     @staticmethod
@@ -182,13 +192,29 @@ class UNet:
         def zbuf(h, w, c):
             return torch.empty((h, w, c), dtype=torch.bfloat16, device=self.dev)
 
+        jobs = []
+
         def wgrad(name, x1, up, x2, gy):
             _, cu, cs, co, _ = self.by_name[name]
             lev = self._lev(name)
-            self._chk(self.L.cgh_net_conv3x3_wgrad(
-                _p(x1), cu, int(up), _p(x2), cs, self.H >> lev, self.W >> lev, _p(gy), co,
-                _p(self._view(self.grad, name)), _p(self._view(self.grad, name + ".b")),
-                _p(self.scratch), self.ws_bytes, s))
+            need = self.share_bytes[name]
+            at = sum(self.share_bytes[nm] for nm, _ in jobs)
+            if at + need > self.shares.numel():
+                sums()
+                at = 0
+            at = ctypes.c_void_p(self.shares.data_ptr() + at)
+            h, w = self.H >> lev, self.W >> lev
+            self._chk(self.L.cgh_net_wgrad_shares(_p(x1), cu, int(up), _p(x2), cs, h, w, _p(gy),
+                                                  co, at, need, s))
+            jobs.append((name, binding.cgh_net_wgrad_job(
+                h, w, cu + cs, co, at, _p(self._view(self.grad, name)),
+                _p(self._view(self.grad, name + ".b")))))
+
+        def sums():
+            """the gradients of the layers whose shares are waiting"""
+            arr = (binding.cgh_net_wgrad_job * len(jobs))(*(j for _, j in jobs))
+            self._chk(self.L.cgh_net_wgrad_sums(arr, len(jobs), s))
+            jobs.clear()
 
         def dgrad(name, gy):
             """dL/d(input) of layer `name` in FP32"""
@@ -248,6 +274,7 @@ class UNet:
             wgrad(name, x_in, False, None, z)
             if l > 0:
                 g = dgrad(name, z)
+        sums()
         return self.grad
 
     def step(self, lr, beta1=0.9, beta2=0.999, eps=1e-8):

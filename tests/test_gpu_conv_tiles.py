@@ -128,6 +128,42 @@ def test_weight_gradients_match_float64(H, W, c1, up, c2, cout):
     assert float((gb.double() - g64.sum(0)).norm() / g64.sum(0).norm()) <= 6e-6
 
 
+def test_wgrad_sums_of_many_layers():
+    """The shares of several layers, summed in one call, give the values of the calls one
+    by one: few and many shares, channels that are no multiple of 32, a missing bias,
+    and more layers than one launch takes."""
+    L = binding.lib()
+    shapes = [(38, 70, 24, 40), (16, 32, 32, 32), (200, 264, 8, 8), (64, 64, 96, 32), (8, 8, 64, 128),
+              (130, 100, 32, 64)]
+    jobs, keep, want = [], [], []
+    for k in range(19):
+        H, W, cin, cout = shapes[k % len(shapes)]
+        x, _, _, _ = inputs(H, W, cin, 0, 0, cout)
+        gy = torch.randn(H, W, cout, device="cuda").bfloat16()
+        out = lambda: (torch.full((cout, 9, cin), 7.0, device="cuda"),
+                       torch.full((cout,), 7.0, device="cuda"))
+        (gw, gb), (rw, rb) = out(), out()
+        nb = L.cgh_net_wgrad_workspace(H, W, cin, cout)
+        ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+        binding._check(L.cgh_net_conv3x3_wgrad(ptr(x), cin, 0, None, 0, H, W, ptr(gy), cout, ptr(rw),
+                                               None if k == 3 else ptr(rb), ptr(ws), nb, stream()))
+        ns = L.cgh_net_wgrad_shares_bytes(H, W, cin, cout)
+        sh = torch.empty(ns, dtype=torch.uint8, device="cuda")
+        assert L.cgh_net_wgrad_shares(ptr(x), cin, 0, None, 0, H, W, ptr(gy), cout, ptr(sh), ns - 1,
+                                      stream()) != 0
+        binding._check(L.cgh_net_wgrad_shares(ptr(x), cin, 0, None, 0, H, W, ptr(gy), cout, ptr(sh),
+                                              ns, stream()))
+        jobs.append(binding.cgh_net_wgrad_job(H, W, cin, cout, ptr(sh), ptr(gw),
+                                              None if k == 3 else ptr(gb)))
+        keep += [x, gy, ws, sh]
+        want.append((gw, rw, gb, rb))
+    say("wgrad sums", len(jobs))
+    binding._check(L.cgh_net_wgrad_sums((binding.cgh_net_wgrad_job * len(jobs))(*jobs), len(jobs),
+                                        stream()))
+    for gw, rw, gb, rb in want:
+        assert torch.equal(gw, rw) and torch.equal(gb, rb)
+
+
 def test_fused_passes_equal_their_parts():
     """The pooled convolution, the gated input adjoint, the gated upsampling adjoint
     and the gated combination give the values of the separate calls."""
