@@ -83,8 +83,8 @@ def in_support_pairs(p, H, W, k):
 
 
 # kernel class -> source file holding its kernel (for matching committed counters)
-KERNEL_SOURCE = {"col_pass": "fft_kernels.hip", "row_loss": "fft_kernels.hip",
-                 "row_fft": "fft_kernels.hip", "raster": "raster_kernels.hip",
+KERNEL_SOURCE = {"col_pass": "fft_chain.h", "row_loss": "fft_chain.h",
+                 "row_fft": "fft_chain.h", "raster": "raster_kernels.hip",
                  "raster_adjoint": "raster_kernels.hip"}
 
 
