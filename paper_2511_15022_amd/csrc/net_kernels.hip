@@ -616,7 +616,7 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3_wgrad(WgradArgs a) {
 #pragma unroll
       for (int k = 0; k < KG; ++k) {
         const int i = (tid + 256 * k) >> 2;
-        out_g |= (y0 + i / kWgCols < H) & (x0 + i % kWgCols < W) ? 0u : 1u << k;
+        out_g |= ((y0 + i / kWgCols < H) & (x0 + i % kWgCols < W)) ? 0u : 1u << k;
       }
     }
     lds_sync();  // every wave is done with the previous tile
