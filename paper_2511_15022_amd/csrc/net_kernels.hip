@@ -68,7 +68,12 @@ bool al16(const void *p) { return ((uintptr_t)p & 15u) == 0; }
 //
 // For every output the products are added in the order input block, tap
 // (ky, kx), channel group of the instruction, whatever the tile: results do not
-// depend on NB and R.
+// depend on NB, R and FAR.
+//
+// A slot's offset from its tile's first pixel has 32 bits.  FAR: for images whose
+// staged rows lie further apart than that (far_rows), each wave's slots, which lie in
+// at most two staged rows, are loaded from a 64-bit base per row, and offsets count
+// from the row's first staged pixel.
 //
 // Measured (1080 x 1920, C = 3, per layer, before and now): 24 -> 32 channels 96 and
 // 53 us (4.4 TB/s), 32 -> 32 84 and 60 us, 96 -> 32 209 and 128 us; 128 -> 128 at
@@ -125,9 +130,25 @@ struct ConvArgs {
   int tiles_x, nco, items;  // column tiles, channel tiles, tiles in all (channel tile fastest)
 };
 
-template <int R, int NB, int KC, int NBUF, bool TWO, bool GEN>
+// Whether a tile's staged pixels (at most 18 rows and 34 columns) may lie past the end of
+// a buffer from its first one, in an image of W columns and c channels.
+bool far_rows(int W, int c) { return 2 * (int64_t)c * (18 * (int64_t)W + 64) > kBufferBytes; }
+
+// 16 bytes per lane to LDS at `dst`, as load_to_lds, from byte `off` + `sof` of the staged
+// row `row` of each lane, which is r0 or r0 + 1 (wave-uniform); from(r) is the (uniform)
+// address of the first staged pixel of row r
+template <class FROM>
+__device__ __forceinline__ void load_two_rows(int row, int r0, FROM from, uint32_t off, int sof,
+                                              v8s *dst) {
+#pragma unroll
+  for (int e = 0; e < 2; ++e)
+    if (row == r0 + e) load_to_lds(buffer_of(from(r0 + e), kBufferBytes), off, sof, dst);
+}
+
+template <int R, int NB, int KC, int NBUF, bool TWO, bool GEN, bool FAR = false>
 __global__ __launch_bounds__(256, 2) void k_conv3x3(ConvArgs a) {
   constexpr bool THIN = KC == 2;
+  static_assert(!FAR || (!THIN && NBUF == 2), "far rows: one number of loads per wave is not kept");
   static_assert(!THIN || (!TWO && NB == 1 && NBUF == 2), "one input of at most 32 channels");
   constexpr int CO = 32 * NB, TY = 4 * R, SR = TY + 2, SC = 34, SP = 2 * KC;  // SP: slots per pixel
   constexpr int NA = SR * SC * SP, NW = THIN ? 0 : 9 * CO * 2;  // 16-byte slots
@@ -160,10 +181,10 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3(ConvArgs a) {
     const int s = tid + 256 * k, i = s / SP, row = i / SC, col = i - row * SC;
     const int g = (s % SP) ^ (THIN ? (col >> 2) & 3 : (col >> 3) & 1);
     if (g & 1) ah |= 1u << k;
-    int q = row * W + col;
+    int q = FAR ? col : row * W + col;
     if constexpr (TWO) {
       o2[k] = s < NA ? 2u * (uint32_t)(q * a.c2 + 8 * g) : kOutside;
-      if (a.up) q = ((row + 1) >> 1) * W1 + ((col + 1) >> 1);
+      if (a.up) q = FAR ? (col + 1) >> 1 : ((row + 1) >> 1) * W1 + ((col + 1) >> 1);
     }
     o1[k] = s < NA && (!THIN || 8 * g < cin) ? 2u * (uint32_t)(q * a.c1 + 8 * g) : kOutside;
   }
@@ -177,6 +198,7 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3(ConvArgs a) {
   }
   // the tile being loaded
   __amdgpu_buffer_rsrc_t b1, b2, bw;
+  const uint16_t *f1 = nullptr, *f2 = nullptr;  // FAR: the bases of b1 and b2
   uint32_t out = 0;  // bit k: slot k's pixel lies outside the image
   auto aim = [&](int it) {
     const int tile = THIN ? it : it / a.nco, ty = tile / a.tiles_x;
@@ -196,14 +218,29 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3(ConvArgs a) {
     const int64_t q2 = (int64_t)ay * W + ax;
     if constexpr (TWO) {
       const int64_t q1 = a.up ? (int64_t)(((ay + 1) >> 1) - 1) * W1 + ((ax + 1) >> 1) - 1 : q2;
-      b1 = buffer_of(a.x1 + q1 * a.c1, kBufferBytes);
-      b2 = buffer_of(a.x2 + q2 * a.c2, kBufferBytes);
+      b1 = buffer_of(f1 = a.x1 + q1 * a.c1, kBufferBytes);
+      b2 = buffer_of(f2 = a.x2 + q2 * a.c2, kBufferBytes);
     } else {
       b1 = buffer_of(a.x1 + q2 * a.c1, kBufferBytes);
     }
     if constexpr (!THIN) {
       const int co = (it - tile * a.nco) * CO;
-      bw = buffer_of(a.w + (size_t)co * 9 * cin, (a.cout - co) * 9 * cin * 2);
+      bw = buffer_of(a.w + (size_t)co * 9 * cin, min(a.cout - co, CO) * 9 * cin * 2);
+    }
+  };
+  // slot k's 16 bytes at offset o + sof of x1 (or, with `second`, of x2) to LDS
+  auto load_pixel = [&](bool second, uint32_t o, int sof, int k, v8s *dst) {
+    if constexpr (FAR) {
+      static_assert(64 / SP <= SC, "a wave's slots lie in at most two rows");
+      load_two_rows(
+          (tid + 256 * k) / SP / SC, (64 * wave + 256 * k) / SP / SC,
+          [&](int r) {
+            return second ? f2 + (int64_t)r * W * a.c2
+                          : f1 + (int64_t)(a.up ? (r + 1) >> 1 : r) * W1 * a.c1;
+          },
+          o, sof, dst);
+    } else {
+      load_to_lds(second ? b2 : b1, o, sof, dst);
     }
   };
   // offset o of slot k, past the buffer where its pixel is outside
@@ -214,12 +251,11 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3(ConvArgs a) {
     if (!GEN || (c0 + 8 < cin && (c0 + 8 < a.c1 || c0 >= a.c1))) {
       // uniform: sixteen channels of one input
       const bool in1 = !TWO || c0 < a.c1;
-      const __amdgpu_buffer_rsrc_t src = in1 ? b1 : b2;
       const int sof = 2 * (in1 ? c0 : c0 - a.c1);
 #pragma unroll
       for (int k = 0; k < KA; ++k)
         if (PAD || 256 * (k + 1) <= NA || tid + 256 * k < NA)
-          load_to_lds(src, masked(in1 ? o1[k] : o2[TWO ? k : 0], k), sof, sa + 256 * k);
+          load_pixel(!in1, masked(in1 ? o1[k] : o2[TWO ? k : 0], k), sof, k, sa + 256 * k);
     } else {
       // the last eight channels, or x1's last eight and x2's first
       const bool both = TWO && c0 < a.c1 && c0 + 8 >= a.c1 && c0 + 8 < cin;
@@ -229,11 +265,11 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3(ConvArgs a) {
         const bool up8 = (ah >> k) & 1;
         const uint32_t p1 = masked(o1[k], k), p2 = TWO ? masked(o2[k], k) : kOutside;
         if (TWO && (up8 || c0 >= a.c1))
-          load_to_lds(b2, up8 ? (both && p2 < kOutside ? p2 - 16u : kOutside)
-                              : p2 + 2u * (uint32_t)(c0 - a.c1),
-                      0, sa + 256 * k);
+          load_pixel(true, up8 ? (both && p2 < kOutside ? p2 - 16u : kOutside)
+                               : p2 + 2u * (uint32_t)(c0 - a.c1),
+                     0, k, sa + 256 * k);
         else
-          load_to_lds(b1, up8 ? kOutside : p1, 2 * c0, sa + 256 * k);
+          load_pixel(false, up8 ? kOutside : p1, 2 * c0, k, sa + 256 * k);
       }
     }
     if constexpr (!THIN) {
@@ -478,11 +514,13 @@ ConvTile conv_tile(int H, int W, bool thin, int cout) {
 
 hipError_t launch_conv(ConvArgs a, hipStream_t s) {
   // an upsampled input without a skip runs as one with an absent skip
+  const bool far = far_rows(a.W, std::max(a.c1, a.c2));
   const bool two = a.c2 > 0 || a.up;
-  const bool thin = !two && a.c1 <= 32;
+  const bool thin = !two && a.c1 <= 32 && !far;
   const bool gen = a.c1 % 16 != 0 || a.c2 % 16 != 0;
   ConvTile t = conv_tile(a.H, a.W, thin, a.cout);
   if (gen) t.nb = 1;
+  if (far) t = {2, 1};
   a.tiles_x = (a.W + 31) / 32;
   a.nco = (a.cout + 32 * t.nb - 1) / (32 * t.nb);
   const int tiles = a.tiles_x * ((a.H + 4 * t.r - 1) / (4 * t.r));
@@ -501,7 +539,9 @@ hipError_t launch_conv(ConvArgs a, hipStream_t s) {
     else go(k_conv3x3<2, 1, 1, 3, TWO, GEN>);
   };
   using std::bool_constant;
-  if (thin) {
+  if (far) {
+    go(k_conv3x3<2, 1, 1, 2, true, true, true>);
+  } else if (thin) {
     if (t.r == 4) go(k_conv3x3<4, 1, 2, 2, false, false>);
     else go(k_conv3x3<2, 1, 2, 2, false, false>);
   } else if (two) {
@@ -543,6 +583,9 @@ struct WgradArgs {
 
 constexpr int kWgRows = 16, kWgCols = 32;  // pixels of a tile
 
+// FAR: as the convolution's (a wave's slots lie in one row of dL/dout and in at most
+// two of the input).
+template <bool FAR>
 __global__ __launch_bounds__(256, 2) void k_conv3x3_wgrad(WgradArgs a) {
   constexpr int SC = kWgCols + 2, NI = (kWgRows + 2) * SC * 4, NG = kWgRows * kWgCols * 4;
   constexpr int KI = (NI + 255) / 256, KG = NG / 256;
@@ -563,10 +606,11 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3_wgrad(WgradArgs a) {
     if (s >= NI || c >= cin) {
       oi[k] = kOutside;
     } else if (c < a.c1) {
-      const int q = a.up ? ((row + 1) >> 1) * W1 + ((col + 1) >> 1) : row * W + col;
+      const int q = a.up ? (FAR ? 0 : ((row + 1) >> 1) * W1) + ((col + 1) >> 1)
+                         : (FAR ? 0 : row * W) + col;
       oi[k] = 2u * (uint32_t)(q * a.c1 + c);
     } else {
-      oi[k] = 2u * (uint32_t)((row * W + col) * a.c2 + c - a.c1);
+      oi[k] = 2u * (uint32_t)(((FAR ? 0 : row * W) + col) * a.c2 + c - a.c1);
       from2 |= 1u << k;
     }
   }
@@ -574,7 +618,7 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3_wgrad(WgradArgs a) {
   for (int k = 0; k < KG; ++k) {
     const int s = tid + 256 * k, i = s >> 2, row = i / kWgCols, col = i % kWgCols;
     const int c = co0 + 8 * (s & 3);
-    og[k] = c < a.cout ? 2u * (uint32_t)((row * W + col) * a.cout + c) : kOutside;
+    og[k] = c < a.cout ? 2u * (uint32_t)(((FAR ? 0 : row * W) + col) * a.cout + c) : kOutside;
   }
   // this lane's part of a transposed read's address: pixel 8 (lane / 32) + (lane % 16) / 4,
   // channels 16 (lane / 16 % 2) + 4 (lane % 4)
@@ -601,9 +645,11 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3_wgrad(WgradArgs a) {
     const int ty = tile / a.tiles_x, x0 = (tile - ty * a.tiles_x) * kWgCols, y0 = ty * kWgRows;
     const int64_t q2 = (int64_t)(y0 - 1) * W + x0 - 1;
     const int64_t q1 = a.up ? (int64_t)((y0 >> 1) - 1) * W1 + (x0 >> 1) - 1 : q2;
-    const auto b1 = buffer_of(a.x1 + q1 * a.c1, kBufferBytes);
-    const auto b2 = buffer_of(a.x2 + q2 * a.c2, kBufferBytes);
-    const auto bg = buffer_of(a.gy + ((int64_t)y0 * W + x0) * a.cout, kBufferBytes);
+    const uint16_t *const f1 = a.x1 + q1 * a.c1, *const f2 = a.x2 + q2 * a.c2;
+    const uint16_t *const fg = a.gy + ((int64_t)y0 * W + x0) * a.cout;
+    const auto b1 = buffer_of(f1, kBufferBytes);
+    const auto b2 = buffer_of(f2, kBufferBytes);
+    const auto bg = buffer_of(fg, kBufferBytes);
     uint32_t out_i = 0, out_g = 0;  // slots whose pixel lies outside the image
     if (y0 == 0 || x0 == 0 || y0 + kWgRows + 1 > H || x0 + kWgCols + 1 > W) {
 #pragma unroll
@@ -625,12 +671,30 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3_wgrad(WgradArgs a) {
     for (int k = 0; k < KI; ++k) {
       if (256 * (k + 1) > NI && tid + 256 * k >= NI) continue;
       const uint32_t o = oi[k] | ((out_i << (31 - k)) & kOutside);
-      if ((from2 >> k) & 1) load_to_lds(b2, o, 0, li + 256 * k);
-      else load_to_lds(b1, o, 0, li + 256 * k);
+      if constexpr (FAR) {
+        const int row = (tid + 256 * k) / 4 / SC, r0 = (64 * wave + 256 * k) / 4 / SC;
+        if ((from2 >> k) & 1)
+          load_two_rows(row, r0, [&](int r) { return f2 + (int64_t)r * W * a.c2; }, o, 0,
+                        li + 256 * k);
+        else
+          load_two_rows(
+              row, r0, [&](int r) { return f1 + (int64_t)(a.up ? (r + 1) >> 1 : r) * W1 * a.c1; },
+              o, 0, li + 256 * k);
+      } else {
+        if ((from2 >> k) & 1) load_to_lds(b2, o, 0, li + 256 * k);
+        else load_to_lds(b1, o, 0, li + 256 * k);
+      }
     }
 #pragma unroll
-    for (int k = 0; k < KG; ++k)
-      load_to_lds(bg, og[k] | ((out_g << (31 - k)) & kOutside), 0, lg + 256 * k);
+    for (int k = 0; k < KG; ++k) {
+      const uint32_t o = og[k] | ((out_g << (31 - k)) & kOutside);
+      if constexpr (FAR) {
+        const int r = (64 * wave + 256 * k) / 4 / kWgCols;
+        load_to_lds(buffer_of(fg + (int64_t)r * W * a.cout, kBufferBytes), o, 0, lg + 256 * k);
+      } else {
+        load_to_lds(bg, o, 0, lg + 256 * k);
+      }
+    }
     wait_vm<0>();
     lds_sync();
 #pragma unroll
@@ -1148,8 +1212,10 @@ static cgh_status wgrad_shares(const cgh_bf16 *x1, int c1, int up, const cgh_bf1
   const int cin = c1 + c2;
   const WgradArgs wa{x1, x2, gy,   c1,         c2,       up,        H,
                      W,  cout, pl.tiles_x, pl.tiles, pl.splits, part, part_b};
-  hipLaunchKernelGGL(k_conv3x3_wgrad, dim3((cin + 31) / 32, (cout + 31) / 32, pl.splits),
-                     dim3(256), 0, s, wa);
+  const auto kern = far_rows(W, std::max(std::max(c1, c2), cout)) ? k_conv3x3_wgrad<true>
+                                                                  : k_conv3x3_wgrad<false>;
+  hipLaunchKernelGGL(kern, dim3((cin + 31) / 32, (cout + 31) / 32, pl.splits), dim3(256), 0, s,
+                     wa);
   NET_LAUNCHED("conv3x3_wgrad");
   return CGH_OK;
 }

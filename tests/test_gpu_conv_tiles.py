@@ -200,3 +200,79 @@ def test_fused_passes_equal_their_parts():
     chk(L.cgh_net_relu_grad(ptr(cmb), ptr(act), cmb.numel(), ptr(q), stream()))
     chk(L.cgh_net_grad_combine_gated(ptr(gp), ptr(g32), co, 40, H, W, 24, ptr(act), ptr(q2), stream()))
     assert torch.equal(q, q2)
+
+
+# Images so wide that the rows of a tile lie further apart than 32-bit byte offsets reach
+# (17 rows of 2^20 x 64 channels are 2.1 GB): one input, a skip of 136 channels beside an
+# upsampled input, an upsampled input of 264 with a skip that shares its last block.
+FAR_W = 1 << 20
+FAR = [(18, 64, 0, 0, 8), (18, 8, 1, 136, 8), (18, 264, 1, 8, 16)]
+WINDOWS = [(0, 70), (FAR_W // 2 - 36, FAR_W // 2 + 34), (FAR_W - 70, FAR_W)]
+
+
+def far_inputs(H, c1, up, c2, cout):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(4)
+    bf = lambda *s: torch.empty(*s, dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+    return (bf(H >> up, FAR_W >> up, c1), bf(H, FAR_W, c2) if c2 else None, bf(cout, 9, c1 + c2),
+            torch.randn(cout, generator=g, device="cuda"))
+
+
+def window(x1, x2, up, a, b):
+    """the inputs of columns a .. b - 1, two more on each side that has them"""
+    lo, hi = max(0, a - 2), min(FAR_W, b + 2)
+    return x1[:, lo >> up:hi >> up], None if x2 is None else x2[:, lo:hi], lo, hi
+
+
+@pytest.mark.parametrize("H,c1,up,c2,cout", FAR)
+def test_conv_of_far_rows_matches_float64(H, c1, up, c2, cout):
+    """Bar: as above."""
+    say("far conv", H, c1, up, c2, cout)
+    x1, x2, w, bias = far_inputs(H, c1, up, c2, cout)
+    o32 = torch.full((H, FAR_W, cout), float("nan"), device="cuda")
+    o16 = torch.zeros(H, FAR_W, cout, dtype=torch.bfloat16, device="cuda")
+    binding._check(binding.lib().cgh_net_conv3x3(
+        ptr(x1), c1, up, ptr(x2), c2, H, FAR_W, ptr(w), ptr(bias), cout, 1, ptr(o32), ptr(o16),
+        stream()))
+    for a, b in WINDOWS:
+        y1, y2, lo, hi = window(x1, x2, up, a, b)
+        ref = reference(y1, y2, w, bias, up, H, hi - lo)[:, a - lo:b - lo]
+        got = o32[:, a:b].double()
+        # each row on its own: a wrong row cannot hide in the others' norm
+        err = (got - ref).norm(dim=(1, 2)) / ref.norm(dim=(1, 2))
+        assert float(err.max()) <= 2e-6, (a, err.tolist())
+    assert torch.equal(o16, o32.clamp(min=0).bfloat16())
+
+
+@pytest.mark.parametrize("H,c1,up,c2,cout", [(18, 8, 1, 72, 8), (18, 264, 1, 8, 8), (18, 8, 0, 0, 72)])
+def test_weight_gradients_of_far_rows_match_float64(H, c1, up, c2, cout):
+    """dL/dout is zero outside the windows, so that the sums run over them alone (3780
+    products); bar as for the weight gradients above."""
+    say("far wgrad", H, c1, up, c2, cout)
+    x1, x2, _, _ = far_inputs(H, c1, up, c2, cout)
+    L, cin = binding.lib(), c1 + c2
+    gy = torch.zeros(H, FAR_W, cout, dtype=torch.bfloat16, device="cuda")
+    gw, gb = torch.empty(cout, 9, cin, device="cuda"), torch.empty(cout, device="cuda")
+    want, want_b = torch.zeros(cout, 9, cin, dtype=torch.double, device="cuda"), 0
+    for a, b in WINDOWS:
+        gy[:, a:b] = torch.randn(H, b - a, cout, device="cuda").bfloat16()
+        y1, y2, lo, hi = window(x1, x2, up, a, b)
+        x = y1.double()
+        if up:
+            x = x.repeat_interleave(2, 0).repeat_interleave(2, 1)
+        if y2 is not None:
+            x = torch.cat([x, y2.double()], -1)
+        xp = torch.nn.functional.pad(x, (0, 0, 1, 1, 1, 1))
+        g64 = gy[:, a:b].double().reshape(-1, cout)
+        want += torch.stack(
+            [g64.T @ xp[t // 3:t // 3 + H, a - lo + t % 3:b - lo + t % 3].reshape(-1, cin)
+             for t in range(9)], 1)
+        want_b = want_b + g64.sum(0)
+    nb = L.cgh_net_wgrad_shares_bytes(H, FAR_W, cin, cout)
+    sh = torch.empty(nb, dtype=torch.uint8, device="cuda")
+    binding._check(L.cgh_net_wgrad_shares(ptr(x1), c1, up, ptr(x2), c2, H, FAR_W, ptr(gy), cout,
+                                          ptr(sh), nb, stream()))
+    job = binding.cgh_net_wgrad_job(H, FAR_W, cin, cout, ptr(sh), ptr(gw), ptr(gb))
+    binding._check(L.cgh_net_wgrad_sums((binding.cgh_net_wgrad_job * 1)(job), 1, stream()))
+    assert float((gw.double() - want).norm() / want.norm()) <= 6e-6
+    assert float((gb.double() - want_b).norm() / want_b.norm()) <= 6e-6
