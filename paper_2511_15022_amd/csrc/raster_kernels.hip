@@ -1342,12 +1342,18 @@ hipError_t launch_raster_fwd(const Ctx &c, float2 *field, hipStream_t s) {
 constexpr int kAdjBatch = 64;
 constexpr int kAdjSeg = 8;    // pixels per segment
 constexpr int kAdjRowPad = 1;  // float2 of padding after each staged tile row (bank spread)
-// Waves per tile (wave w takes part w of NW of the tile's list): 3, or 8 where there are
-// at most kAdjFewTiles tiles per CU, whose waves would be too few to cover their own
-// latencies.  Measured with 3, 6, 8 and 12 waves: one tile per CU (256 x 256 gray) 14.8,
-// 11.4, 10.6 and 11.2 us; 2.7 (333 x 517 gray) 19.1, 16.1, 16.6 and 20.6 us; 10 (640 x
-// 1024 RGB) 35, 55, 60 and 105 us.
-constexpr int kAdjWaves = 3, kAdjManyWaves = 8, kAdjFewTiles = 3;
+// Waves per tile (wave w takes part w of NW of the tile's list): 3, or 4 where a hologram
+// has at most kAdjFewTiles tiles per CU, whose waves would be too few to cover their own
+// latencies.  The cut of a list decides the order of a pair's sums, so the rule looks at
+// one hologram's tiles and not at a batch's: a hologram gives the same bits alone and in
+// any batch.  Measured with 3, 4, 5, 6 and 8 waves, pixels / 5 Gaussians (adjoint and
+// per-Gaussian stage, us; tiles per CU in brackets): 256 x 256 gray [1] 19.1, 14.6, 14.7,
+// 14.2, 13.8; RGB 21.4, 16.7, 17.0, 16.5, 16.3; 333 x 517 gray [2.7] 21.1, 19.0, 19.7,
+// 20.0, 20.4; RGB 31.3, 25.4, 26.5, 29.1, 28.1; 640 x 1024 RGB [10] 55.2, 52.8, 61.7, 66.4,
+// 66.8; with pixels / 10 Gaussians 38.4, 39.6, 49.3, 55.9, 61.8; 1080p RGB [32] 135, 135,
+// 164, 179, 188 and 87.5, 96.5, 132, 151, 172.  Batches of 256 x 256 gray with 3, 4 and 8:
+// four 25.6, 23.1, 25.2; eight 35.4, 33.7, 39.1; thirty-two 91, 90, 120.
+constexpr int kAdjWaves = 3, kAdjManyWaves = 4, kAdjFewTiles = 3;
 
 // per-pair quantities kept in LDS for the walk (floats):
 //   0-1 offx, offy (tile origin - floor(mean) - frac(mean))
@@ -2013,7 +2019,7 @@ hipError_t launch_raster_adjoint(const Ctx &c, const float2 *grad_field, hipStre
         else if (clamp) go(k_raster_adj<CC, true, false, TW, TH, NW>);
         else go(k_raster_adj<CC, false, false, TW, TH, NW>);
       };
-      if (c.num_tiles <= kAdjFewTiles * c.num_cu)
+      if (c.tiles_per <= kAdjFewTiles * c.num_cu)
         waves(std::integral_constant<int, kAdjManyWaves>{});
       else
         waves(std::integral_constant<int, kAdjWaves>{});

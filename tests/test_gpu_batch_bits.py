@@ -1,0 +1,69 @@
+"""A hologram gives the same bits alone and in a batch, also where a rule that looks at
+the size of the work lies between the two: the waves per tile of the rasterizer adjoint
+(tiles per compute unit of one hologram against those of the batch)."""
+import sys
+
+import pytest
+import torch
+
+from paper_2511_15022_amd import binding, synth
+
+pytestmark = pytest.mark.gpu
+
+LAM = [639e-9, 515e-9, 473e-9]
+
+
+def say(*a):
+    print("[gpu-case]", *a, flush=True)
+    sys.stdout.flush()
+
+
+def contexts(B, H, W, C, zs, n, **kw):
+    """a batch and its holograms' own contexts, with optics that differ"""
+    optics = [([LAM[(b + c) % 3] for c in range(C)], [z * (1 + 0.1 * b) for z in zs])
+              for b in range(B)]
+    pairs = kw.pop("max_pairs", 0)
+    batch = binding.Context(H, W, C, 8e-6, *optics[0], max_gaussians=n, batch=B,
+                            max_pairs=B * pairs, **kw)
+    for b in range(B):
+        batch.set_hologram_optics(b, *optics[b])
+    return batch, [binding.Context(H, W, C, 8e-6, *o, max_gaussians=n, max_pairs=pairs, **kw)
+                   for o in optics]
+
+
+# up to 256 tiles alone (one per compute unit of 256) and 1024 together, 576 and 1152, and
+# tiles of 8 x 8; the exponent's clamp needs a support beyond ten sigma
+@pytest.mark.parametrize("B,H,W,C,n,kw", [
+    (4, 256, 256, 1, 13107, {}),
+    (4, 256, 256, 3, 6000, {}),
+    (2, 384, 384, 1, 20000, {}),
+    (4, 128, 128, 1, 3000, dict(tile=(8, 8))),
+    (4, 256, 256, 1, 6000, dict(paper_alpha=True)),
+    (4, 256, 256, 1, 500, dict(support_sigma=12.0, max_pairs=60000)),
+])
+def test_batch_equals_single_across_tile_counts(B, H, W, C, n, kw):
+    say("batch bits", B, H, W, C, n, kw)
+    batch, single = contexts(B, H, W, C, [2e-3], n, **kw)
+    Ps = [binding.pack(synth.params(50 + b, n, H, W, C), device="cuda") for b in range(B)]
+    Ts = [torch.from_numpy(synth.target(60 + b, C, H, W, L=1)).cuda() for b in range(B)]
+    P, T = torch.cat(Ps), torch.stack(Ts, 1).contiguous()
+    field = batch.rasterize(P, n)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(7)
+    gf = torch.randn(field.shape, generator=gen, device="cuda", dtype=torch.complex64)
+    adj = batch.rasterize_adjoint(P, n, gf)
+    grads = batch.backward(P, n, field, T)
+    m, v = torch.zeros_like(P), torch.zeros_like(P)
+    batch.backward_step(P, n, field, T, m, v, 1, 1e-3)
+    _, ok = batch.read_status()
+    assert ok
+    per = binding.param_count(n, C)
+    for b, ctx in enumerate(single):
+        mine = slice(b * per, (b + 1) * per)
+        f1 = ctx.rasterize(Ps[b], n)
+        assert torch.equal(field[b], f1)
+        assert torch.equal(adj[mine], ctx.rasterize_adjoint(Ps[b], n, gf[b].contiguous())), b
+        assert torch.equal(grads[mine], ctx.backward(Ps[b], n, f1, Ts[b])), b
+        m1, v1 = torch.zeros_like(Ps[b]), torch.zeros_like(Ps[b])
+        ctx.backward_step(Ps[b], n, f1, Ts[b], m1, v1, 1, 1e-3)
+        assert torch.equal(P[mine], Ps[b]) and torch.equal(m[mine], m1) and torch.equal(v[mine], v1)
