@@ -145,6 +145,7 @@ cgh_status setup(const cgh_config *cfg, cgh::Ctx *c) {
   int64_t cap = f.max_pairs ? f.max_pairs : per * B * f.max_gaussians + 65536;
   if (cap > 0x7fffffffLL) cap = 0x7fffffffLL;
   c->pair_cap = cap;
+  c->own_pairs = f.max_pairs ? cap / B : std::min<int64_t>(cap / B, per * f.max_gaussians);
   c->sort_blocks = (int)((cap + kSortItems - 1) / kSortItems);
   c->rec_stride = rec_stride(c->C);
   c->part_stride = partial_stride(c->C);
@@ -246,6 +247,10 @@ size_t carve(Ctx *c, char *base) {
   // written).  Where all planes fit, they are propagated together and the adjoint's sum
   // takes the place of the row spectrum, which every plane has used by then; otherwise
   // the first spectrum is the sum and the others hold a group of planes at a time.
+  // The groups decide which kernels a plane goes through and the order in which the
+  // adjoint adds the planes, so they follow from one hologram's share of the pair
+  // partials (without the constant part of the default capacity, which a batch has once):
+  // a hologram gives the same bits alone and in any batch.
   const int rg = row_group_rows(*c);
   const size_t loss_bytes = sizeof(double) * c->L * c->CF * (size_t)((c->H + rg - 1) / rg);
   const size_t part_bytes = std::max(sizeof(float) * c->part_stride * cap,
@@ -259,7 +264,11 @@ size_t carve(Ctx *c, char *base) {
   c->plane_group = 1;
   c->spec_plane = c->spec_acc = c->spec;
   if (c->L > 1) {
-    const int fit = (int)std::min((size_t)c->L, loss_at / spec_bytes);
+    // (512 bytes per hologram more than its share cover the rounding of loss_at)
+    const size_t own = sizeof(float) * c->part_stride * (size_t)c->own_pairs;
+    const size_t other = loss_bytes / c->B + 512;
+    const int fit = (int)std::min(
+        (size_t)c->L, 2 + (own > other ? (own - other) / (spec_bytes / c->B) : 0));
     c->plane_group = fit == c->L ? fit : fit - 1;
     c->spec_plane = (float2 *)region + (fit == c->L ? 0 : spec_len);
     if (fit < c->L) c->spec_acc = (float2 *)region;

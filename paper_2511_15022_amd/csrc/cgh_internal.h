@@ -104,6 +104,7 @@ struct Ctx {
   double lam[kMaxBatch][CGH_MAX_CHANNELS];  // wavelength of (hologram, colour)
   double zd[kMaxBatch][CGH_MAX_PLANES];     // distance of (hologram, plane)
   int64_t pair_cap;
+  int64_t own_pairs;                // pairs of one hologram's share (the rule of plane_group)
   int sort_blocks;                  // radix-sort grid (covers pair_cap)
   int rec_stride, part_stride;
   FftPlan plan_x, plan_y, plan_m;   // lengths Wp, Hp, Hp/2 (plan_m unused for odd Hp)
@@ -121,7 +122,7 @@ struct Ctx {
                                     // planes (spec itself when L = 1)
   float2 *spec_acc;                 // adjoint sum over planes (spec itself when one group
                                     // holds them all)
-  int plane_group;                  // planes propagated together
+  int plane_group;                  // planes propagated together, by one hologram's sizes
   float2 *gfield_tmp;               // [B C][H][W]
   float *rec;                       // [B max_gaussians + 1][rec_stride]; the last is all zeros
   float2 *alim;                     // CGH_PAPER_ALPHA only, else null: [B max_gaussians + 1]

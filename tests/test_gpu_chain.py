@@ -183,3 +183,9 @@ def test_planes_match_oracle(O, H, W, Hp, Wp, C, L, pairs):
     d = np.abs(ref) ** 2 - T
     assert abs(loss[0].item() - np.mean(w * d * d)) <= GRAD_TOL * np.mean(w * d * d)
     assert rel(gf.cpu().numpy(), O.propagate_adjoint(4.0 * w * d * ref / d.size, opt)) <= GRAD_TOL
+
+
+@pytest.mark.parametrize("H,W,Hp,Wp,C,L", [c[:6] for c in PLANES if c[6] == 0 and c[5] > 2])
+def test_planes_together_match_oracle(O, H, W, Hp, Wp, C, L):
+    """The same with room for all planes at once in the pairs' memory."""
+    test_planes_match_oracle(O, H, W, Hp, Wp, C, L, 65536)
