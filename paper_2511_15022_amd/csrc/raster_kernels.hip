@@ -1419,8 +1419,9 @@ __global__ __launch_bounds__(64 * NW) void k_raster_adj(
     rg = make_uint2(rg.x + (uint32_t)(((uint64_t)len * wave) / NW),
                     rg.x + (uint32_t)(((uint64_t)len * (wave + 1)) / NW));
   }
-  // a batch's Gaussian ids are loaded a batch ahead, the first with the tile
-  uint32_t gid = rg.x + lane < rg.y ? vals[rg.x + lane] : 0u;
+  // a batch's Gaussian ids are loaded a batch ahead, the first with the tile (compared by
+  // length: rg.x + lane would wrap where a tile without pairs starts at 0xffffffff)
+  uint32_t gid = (uint32_t)lane < rg.y - rg.x ? vals[rg.x + lane] : 0u;
   {
     // all loads of a thread are issued before the first is stored
     constexpr int NT = 64 * NW, K = (C * TP + NT - 1) / NT;
