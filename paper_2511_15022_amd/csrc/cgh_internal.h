@@ -177,7 +177,7 @@ hipError_t launch_build_twiddles_full(float2 *tw, int n, hipStream_t s);
 int row_group_rows(const Ctx &c);   // rows per row-pass workgroup
 // transfer tables of holograms [b0, b1) from c.lam, c.zd
 hipError_t launch_build_transfer(const Ctx &c, int b0, int b1, hipStream_t s);
-// the row-major table of (propagation channel, plane) for its current optics -> out
+// the table of (propagation channel, plane) that the column pass reads, row-major -> out
 hipError_t launch_read_transfer(const Ctx &c, int channel, int plane, float2 *out, hipStream_t s);
 // `planes` fields -> their row spectra, each after the other in field and dst
 hipError_t launch_row_fwd(const Ctx &c, const float2 *field, float2 *dst, hipStream_t s,

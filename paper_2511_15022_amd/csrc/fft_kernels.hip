@@ -216,15 +216,19 @@ hipError_t launch_build_twiddles_full(float2 *tw, int n, hipStream_t s) {
 // 1 / (Hp Wp) of the inverse transform, applied in FP64).  The chain column pass
 // reads only the column-major table, the other column kernels only the
 // row-major one, so a context holds one of them.  optics: where lambda and z are
-// kept on the device (2 doubles): written from the arguments, or, with
-// from_optics, read instead of them (cgh_get_transfer: the table of the optics
-// that are current in stream order).
+// kept on the device (2 doubles): written from the arguments, or, with `held`, read
+// instead of them.
+//
+// held (cgh_get_transfer): the column-major table that the column pass reads.  Its
+// entries carry t_scale, which cannot be divided out to the last bit, so an entry is
+// worked out anew from the optics that are current in stream order and returned where
+// `held` has its scaled value; elsewhere `held`'s own value, divided by t_scale, is.
 __global__ void k_transfer(float2 *out, float2 *out_t, double t_scale, int Hq, int Wq, int Hp,
                            int Wp, double pitch, double lambda, double z, double aperture,
-                           double *optics, int from_optics) {
+                           double *optics, const float2 *held) {
   const int fast = blockIdx.x * blockDim.x + threadIdx.x, slow = blockIdx.y;
   const int qx = out_t ? slow : fast, qy = out_t ? fast : slow;
-  if (from_optics) {
+  if (held) {
     lambda = optics[0];
     z = optics[1];
   } else if (optics && fast == 0 && slow == 0) {
@@ -244,6 +248,13 @@ __global__ void k_transfer(float2 *out, float2 *out_t, double t_scale, int Hq, i
     const double ph = 6.283185307179586476925 * z * sqrt(arg);  // 2 pi z sqrt(arg)
     sincos(ph, &sn, &cs);
   }
+  if (held) {
+    const float2 t = held[(size_t)qx * Hq + qy];
+    if (t.x != (float)(cs * t_scale) || t.y != (float)(sn * t_scale)) {
+      cs = t.x / t_scale;
+      sn = t.y / t_scale;
+    }
+  }
   if (out) out[(size_t)qy * Wq + qx] = make_float2((float)cs, (float)sn);
   if (out_t)
     out_t[(size_t)qx * Hq + qy] = make_float2((float)(cs * t_scale), (float)(sn * t_scale));
@@ -260,7 +271,7 @@ hipError_t launch_build_transfer(const Ctx &c, int b0, int b1, hipStream_t s) {
         hipLaunchKernelGGL(k_transfer, grid, dim3(256), 0, s, t ? nullptr : c.htab + at,
                            t ? c.htab_t + at : nullptr, 1.0 / ((double)c.Hp * (double)c.Wp), c.Hq,
                            c.Wq, c.Hp, c.Wp, c.cfg.pitch_m, c.lam[b][ch], c.zd[b][l],
-                           c.cfg.aperture, c.optics + 2 * k, 0);
+                           c.cfg.aperture, c.optics + 2 * k, nullptr);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
       }
@@ -269,9 +280,13 @@ hipError_t launch_build_transfer(const Ctx &c, int b0, int b1, hipStream_t s) {
 
 hipError_t launch_read_transfer(const Ctx &c, int channel, int plane, float2 *out,
                                 hipStream_t s) {
+  const size_t k = (size_t)channel * c.L + plane, elems = (size_t)c.Hq * c.Wq;
+  if (c.htab)
+    return hipMemcpyAsync(out, c.htab + k * elems, elems * sizeof(float2),
+                          hipMemcpyDeviceToDevice, s);
   hipLaunchKernelGGL(k_transfer, dim3((c.Wq + 255) / 256, c.Hq), dim3(256), 0, s, out, nullptr,
-                     1.0, c.Hq, c.Wq, c.Hp, c.Wp, c.cfg.pitch_m, 0.0, 0.0, c.cfg.aperture,
-                     c.optics + 2 * ((size_t)channel * c.L + plane), 1);
+                     1.0 / ((double)c.Hp * (double)c.Wp), c.Hq, c.Wq, c.Hp, c.Wp, c.cfg.pitch_m,
+                     0.0, 0.0, c.cfg.aperture, c.optics + 2 * k, c.htab_t + k * elems);
   return hipGetLastError();
 }
 

@@ -189,3 +189,37 @@ def test_planes_match_oracle(O, H, W, Hp, Wp, C, L, pairs):
 def test_planes_together_match_oracle(O, H, W, Hp, Wp, C, L):
     """The same with room for all planes at once in the pairs' memory."""
     test_planes_match_oracle(O, H, W, Hp, Wp, C, L, 65536)
+
+
+@pytest.mark.parametrize("H,W,Hp,Wp", [(45, 80, 90, 160), (64, 64, 128, 128), (50, 40, 75, 90)])
+def test_get_transfer_reads_the_table_of_the_column_pass(H, W, Hp, Wp):
+    """An entry changed in the workspace shows in get_transfer, and no other does: the
+    column-major, scaled table of the chain passes and the row-major one of the others."""
+    say("transfer table in the workspace", H, W, Hp, Wp)
+    ctx = binding.Context(H, W, 1, 8e-6, [515e-9], [2e-3], pad=(Hp, Wp), max_gaussians=1)
+    before = ctx.get_transfer()
+    w = ctx.workspace[:ctx.workspace.numel() // 8 * 8].view(torch.complex64)
+    chain = Hp % 2 == 0
+    rows = before.T.contiguous() / (Hp * Wp) if chain else before
+    first = rows.reshape(-1)[:8]
+    hit = torch.ones(w.numel() - 8, dtype=torch.bool, device="cuda")
+    for k in range(8):
+        hit &= (w[k:w.numel() - 8 + k] - first[k]).abs() <= 1e-6 * first[k].abs()
+    at = hit.nonzero().reshape(-1).tolist()
+    assert len(at) == 1, at
+    w[at[0] + 3] *= 2
+    after = ctx.get_transfer()
+    y, x = (3, 0) if chain else (0, 3)
+    assert abs(after[y, x].item() - 2 * before[y, x].item()) <= 1e-6
+    after[y, x] = before[y, x]
+    assert torch.equal(after, before)
+
+
+def test_get_transfer_is_unscaled_to_the_last_bit():
+    """The scaled, column-major table gives the values of the row-major one: the same
+    padded grid with a canvas that splits into chains and with one that does not."""
+    say("transfer table, both layouts")
+    a, b = (binding.Context(H, 80, 1, 8e-6, [515e-9], [2e-3], pad=(90, 160), max_gaussians=1,
+                            aperture=70.0) for H in (45, 80))
+    ta, tb = a.get_transfer(), b.get_transfer()
+    assert torch.equal(ta, tb) and 0 < int((ta != 0).sum()) < ta.numel()
