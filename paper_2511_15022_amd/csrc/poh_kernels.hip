@@ -196,7 +196,9 @@ cgh_status cgh_poh_phase_grad(const float *phase, const cgh_c64 *grad_field, int
   return CGH_OK;
 }
 
-int64_t cgh_poh_extract_partials(int64_t count) { return count > 0 ? (count + 255) / 256 : 0; }
+int64_t cgh_poh_extract_partials(int64_t count) {
+  return count > 0 ? (count + 256 * kExtractPer - 1) / (256 * kExtractPer) : 0;
+}
 
 cgh_status cgh_poh_extract_seed(const cgh_c64 *u, const cgh_c64 *u_rand, const float *target,
                                 const float *mask, int32_t L, int32_t C, int32_t H, int32_t W,
@@ -208,7 +210,7 @@ cgh_status cgh_poh_extract_seed(const cgh_c64 *u, const cgh_c64 *u_rand, const f
   POH_CHECK(l_comp >= 0.f && l_field >= 0.f && std::isfinite(l_comp) && std::isfinite(l_field),
             "weights must be >= 0 and finite");
   const int64_t n = (int64_t)L * C * H * W;
-  const int64_t k = (n + 256 * kExtractPer - 1) / (256 * kExtractPer);  // partials used
+  const int64_t k = cgh_poh_extract_partials(n);
   hipStream_t s = (hipStream_t)stream;
   hipLaunchKernelGGL(k_extract, dim3((unsigned)k), dim3(256), 0, s,
                      reinterpret_cast<const float2 *>(u), reinterpret_cast<const float2 *>(u_rand),

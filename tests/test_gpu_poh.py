@@ -131,3 +131,26 @@ def test_random_poh_step_gradients_match_oracle():
     e = rel(rp.gphase.cpu().numpy(), gphase)
     say("phase gradient rel", e)
     assert e <= 1e-3
+
+
+@pytest.mark.parametrize("n", [1, 1023, 1024, 1025, 5000])
+def test_extract_seed_keeps_to_its_partials(n):
+    """cgh_poh_extract_seed writes as many partial sums as cgh_poh_extract_partials says,
+    and no more; their sum is the loss (FP64: 1e-12 of it)."""
+    say("extract partials", n)
+    rng = np.random.default_rng(5)
+    u, ur = ((rng.standard_normal(n) + 1j * rng.standard_normal(n)).astype(np.complex64)
+             for _ in range(2))
+    T = rng.uniform(0, 1, n).astype(np.float32)
+    Lb = binding.lib()
+    k = Lb.cgh_poh_extract_partials(n)
+    part = torch.full((k + 64,), -7.0, dtype=torch.float64, device="cuda")
+    tu, tur, tT = (torch.from_numpy(a).cuda() for a in (u, ur, T))
+    gu, gur = torch.empty_like(tu), torch.empty_like(tu)
+    loss = torch.zeros(1, dtype=torch.float64, device="cuda")
+    assert Lb.cgh_poh_extract_seed(tu.data_ptr(), tur.data_ptr(), tT.data_ptr(), None, 1, 1, 1, n,
+                                   0.1, 0.01, gu.data_ptr(), gur.data_ptr(), part.data_ptr(),
+                                   loss.data_ptr(), torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+    assert bool((part[:k] >= 0).all()) and bool((part[k:] == -7.0).all())
+    assert abs(part[:k].sum().item() / n - loss.item()) <= 1e-12 * loss.item()
