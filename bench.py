@@ -88,16 +88,33 @@ KERNEL_SOURCE = {"col_pass": "fft_chain.h", "row_loss": "fft_chain.h",
                  "raster_adjoint": "raster_kernels.hip"}
 
 
+def kernel_digest(cls):
+    """sha256 over the source of kernel class ``cls`` and the csrc headers it
+    includes, directly or not; None for a class without a source."""
+    import hashlib
+    import re
+    csrc = os.path.join(ROOT, "paper_2511_15022_amd", "csrc")
+    todo, seen = [KERNEL_SOURCE.get(cls)], {}
+    while todo:
+        name = todo.pop()
+        if not name or name in seen or not os.path.isfile(os.path.join(csrc, name)):
+            continue
+        with open(os.path.join(csrc, name), "rb") as f:
+            seen[name] = f.read()
+        todo += re.findall(r'^#include "([^"]+)"', seen[name].decode(), re.M)
+    if not seen:
+        return None
+    return hashlib.sha256(b"".join(seen[k] for k in sorted(seen))).hexdigest()
+
+
 def committed_figure(kind, cls, pattern):
     """A per-launch figure of kernel class ``cls`` from a committed rocprofv3
     summary under profiles/ (lines ``<kind> <class> <value> <sha256>``), if it
     was taken on the current source of that kernel; else None."""
     import glob
-    import hashlib
-    src = os.path.join(ROOT, "paper_2511_15022_amd", "csrc", KERNEL_SOURCE.get(cls, ""))
-    if not os.path.isfile(src):
+    digest = kernel_digest(cls)
+    if digest is None:
         return None
-    digest = hashlib.sha256(open(src, "rb").read()).hexdigest()
     for path in glob.glob(os.path.join(ROOT, "profiles", pattern)):
         for line in open(path):
             parts = line.split()
