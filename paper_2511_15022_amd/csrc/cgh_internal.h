@@ -34,9 +34,10 @@ struct FftPlan {
 bool make_plan(int n, FftPlan *plan);
 bool smooth235(int n);
 
-// Column-pass limits: even Hp runs as two Hp/2-point chains (Hp/2 <= 1152 in a
-// 77 KB LDS block, <= 2400 in 150 KB); odd Hp runs one Hp-point transform
-// (<= 2400).  1024-thread workgroups.
+// Limits of the padded height.  They are the runtime-plan column kernels': even Hp runs
+// there as two Hp/2-point transforms (Hp/2 <= 1152 in a 77 KB LDS block, <= 2400 in
+// 150 KB), odd Hp as one (<= 2400).  Most heights run the chain kernels (fft_chain.h)
+// instead, within the same limits.
 constexpr int kColHalfSmall = 1152;
 constexpr int kColHalfMax = 2400;
 constexpr int kColFullMax = 2400;

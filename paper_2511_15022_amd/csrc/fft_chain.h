@@ -230,7 +230,8 @@ constexpr RowPlan row_plan(int M, int P, int T) {
   return best;
 }
 
-// Threads per row workgroup: 8 to 16 values per thread, 512 threads at most.  Measured
+// Threads per row workgroup: from 400 values on 3 to 16 per thread, 512 threads at most; one
+// wave below.  Measured
 // (row_loss, row_inv): padded 2048 with 512 threads 31.5 / 2 and 12.0 us, with 256
 // 30.0 / 2 and 11.2 us (640 x 1024 RGB); 2560 17.5 and 17.2 us; 3840 60.7 and 28.5
 // against 60.5 and 30.8 us (1080p RGB).
@@ -247,10 +248,13 @@ constexpr bool smooth_c(int n) {
 
 // The chain lengths the passes are compiled for.
 constexpr int kMinChain = 16;
-constexpr int kMaxColChain = 1215;  // one wave per chain: M / 27 <= 64 lanes
+// the longest odd chain whose fused stage takes one butterfly per lane (1215 / 27 = 45; the
+// next odd length, 1875, needs 75); chains of four end with the padded heights of col_supported
+constexpr int kMaxColChain = 1215;
 constexpr int kMaxRowChain4 = 2048, kMaxRowChain2 = 4095;  // kMaxFft / P
 constexpr bool col_chain(int M, int P) {
-  return M >= kMinChain && M <= kMaxColChain && smooth_c(M) && (P == 4 || M % 2);
+  return M >= kMinChain && M <= kMaxColChain && P * M <= 2 * kColHalfMax && smooth_c(M) &&
+         (P == 4 || M % 2);
 }
 constexpr bool row_chain(int M, int P) {
   return M >= kMinChain && M <= (P == 4 ? kMaxRowChain4 : kMaxRowChain2) && smooth_c(M) &&

@@ -14,10 +14,15 @@
 //   B1  column pass with conj(H) (the adjoint, supplementary BLASM Backward Pass)
 //   B2  row IFFT, crop W -> dL/dU0
 // S is column-tiled: [C][ceil(Wp/8)][H][8] complex, so a column workgroup
-// reads and writes one contiguous block and a row workgroup (two rows) moves
-// whole 128-byte lines.
+// reads and writes pieces of one contiguous block.
 //
-// Column pass for even Hp = 2M: the input occupies rows [0, H) and only rows
+// Lengths that split into chains run the kernels of fft_chain.h (four or two chains per
+// row or column, plans compiled for each length).  The kernels below are for the other
+// shapes: more samples than half the padded length, odd padded lengths, chains shorter or
+// longer than those tables.  There a row workgroup takes two rows (or four), whose 64-byte
+// pieces of a tile make whole 128-byte lines.
+//
+// Column pass there for even Hp = 2M: the input occupies rows [0, H) and only rows
 // [0, H) of the output are kept, so the Hp-point transform splits into two
 // M-point chains (radix-2 first and last stages done in registers):
 //   even chain: FFT_M(x[n] + x[n+M])             -> x H(ky = 2m)   -> IFFT_M -> e
