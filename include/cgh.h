@@ -18,7 +18,8 @@
  *  - Streams: `stream` is a hipStream_t (NULL = legacy default stream).  Every
  *    call only enqueues work on it and returns without waiting, except
  *    cgh_create (which builds its tables on the stream and waits for them)
- *    and cgh_read_status (which waits for the stream).
+ *    and cgh_read_status (which waits for the stream).  The calls of a context
+ *    share its workspace: on different streams they are ordered by the caller.
  *  - Errors: argument errors are detected on the host before anything is
  *    enqueued and return a non-zero cgh_status; cgh_last_error() then returns
  *    a message (thread-local).  Launch failures return CGH_ERR_DEVICE.

@@ -3,12 +3,10 @@
 // sums), their weight gradients, and the pooling, upsampling, ReLU and
 // lattice glue around them.
 //
-// Matrix instructions (one wave, D = A B + D, D 32 x 32 FP32): in
-// v_mfma_f32_32x32x8 bf16 (A 32 x 8, B 8 x 32) lane l supplies
-// A[l % 32][4 (l / 32) + i] and B[4 (l / 32) + i][l % 32] (i < 4); in
-// v_mfma_f32_32x32x16 bf16 (A 32 x 16, B 16 x 32) it supplies
-// A[l % 32][8 (l / 32) + i] and B[8 (l / 32) + i][l % 32] (i < 8).  Both leave
-// D[8 (v / 4) + 4 (l / 32) + v % 4][l % 32] in accumulator v < 16.
+// Matrix instruction (one wave, D = A B + D, D 32 x 32 FP32): in v_mfma_f32_32x32x16
+// bf16 (A 32 x 16, B 16 x 32) lane l supplies A[l % 32][8 (l / 32) + i] and
+// B[8 (l / 32) + i][l % 32] (i < 8) and holds D[8 (v / 4) + 4 (l / 32) + v % 4][l % 32] in
+// accumulator v < 16.
 #include <algorithm>
 #include <cmath>
 #include <type_traits>
@@ -73,7 +71,8 @@ bool al16(const void *p) { return ((uintptr_t)p & 15u) == 0; }
 // A slot's offset from its tile's first pixel has 32 bits.  FAR: for images whose
 // staged rows lie further apart than that (far_rows), each wave's slots, which lie in
 // at most two staged rows, are loaded from a 64-bit base per row, and offsets count
-// from the row's first staged pixel.
+// from the row's first staged pixel (64 -> 32 channels, 18 x 2^20 pixels: 1.95 ms, weight
+// gradients 1.66 ms; as many pixels at 1024 x 18432, without it, 1.17 and 1.15 ms).
 //
 // Measured (1080 x 1920, C = 3, per layer, before and now): 24 -> 32 channels 96 and
 // 53 us (4.4 TB/s), 32 -> 32 84 and 60 us, 96 -> 32 209 and 128 us; 128 -> 128 at
@@ -218,18 +217,20 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3(ConvArgs a) {
     const int64_t q2 = (int64_t)ay * W + ax;
     if constexpr (TWO) {
       const int64_t q1 = a.up ? (int64_t)(((ay + 1) >> 1) - 1) * W1 + ((ax + 1) >> 1) - 1 : q2;
-      b1 = buffer_of(f1 = a.x1 + q1 * a.c1, kBufferBytes);
-      b2 = buffer_of(f2 = a.x2 + q2 * a.c2, kBufferBytes);
+      b1 = buffer_of(a.x1 + q1 * a.c1, kBufferBytes);
+      b2 = buffer_of(a.x2 + q2 * a.c2, kBufferBytes);
+      if constexpr (FAR) f1 = a.x1 + q1 * a.c1, f2 = a.x2 + q2 * a.c2;
     } else {
       b1 = buffer_of(a.x1 + q2 * a.c1, kBufferBytes);
     }
     if constexpr (!THIN) {
       const int co = (it - tile * a.nco) * CO;
-      bw = buffer_of(a.w + (size_t)co * 9 * cin, min(a.cout - co, CO) * 9 * cin * 2);
+      bw = buffer_of(a.w + (size_t)co * 9 * cin, (a.cout - co) * 9 * cin * 2);
     }
   };
-  // slot k's 16 bytes at offset o + sof of x1 (or, with `second`, of x2) to LDS
-  auto load_pixel = [&](bool second, uint32_t o, int sof, int k, v8s *dst) {
+  // slot k's 16 bytes at offset o + sof of src, which is b1 (or, with `second`, b2), to LDS
+  auto load_pixel = [&](__amdgpu_buffer_rsrc_t src, bool second, uint32_t o, int sof, int k,
+                        v8s *dst) {
     if constexpr (FAR) {
       static_assert(64 / SP <= SC, "a wave's slots lie in at most two rows");
       load_two_rows(
@@ -240,7 +241,7 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3(ConvArgs a) {
           },
           o, sof, dst);
     } else {
-      load_to_lds(second ? b2 : b1, o, sof, dst);
+      load_to_lds(src, o, sof, dst);
     }
   };
   // offset o of slot k, past the buffer where its pixel is outside
@@ -251,11 +252,12 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3(ConvArgs a) {
     if (!GEN || (c0 + 8 < cin && (c0 + 8 < a.c1 || c0 >= a.c1))) {
       // uniform: sixteen channels of one input
       const bool in1 = !TWO || c0 < a.c1;
+      const __amdgpu_buffer_rsrc_t src = in1 ? b1 : b2;
       const int sof = 2 * (in1 ? c0 : c0 - a.c1);
 #pragma unroll
       for (int k = 0; k < KA; ++k)
         if (PAD || 256 * (k + 1) <= NA || tid + 256 * k < NA)
-          load_pixel(!in1, masked(in1 ? o1[k] : o2[TWO ? k : 0], k), sof, k, sa + 256 * k);
+          load_pixel(src, !in1, masked(in1 ? o1[k] : o2[TWO ? k : 0], k), sof, k, sa + 256 * k);
     } else {
       // the last eight channels, or x1's last eight and x2's first
       const bool both = TWO && c0 < a.c1 && c0 + 8 >= a.c1 && c0 + 8 < cin;
@@ -265,11 +267,11 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3(ConvArgs a) {
         const bool up8 = (ah >> k) & 1;
         const uint32_t p1 = masked(o1[k], k), p2 = TWO ? masked(o2[k], k) : kOutside;
         if (TWO && (up8 || c0 >= a.c1))
-          load_pixel(true, up8 ? (both && p2 < kOutside ? p2 - 16u : kOutside)
-                               : p2 + 2u * (uint32_t)(c0 - a.c1),
+          load_pixel(b2, true, up8 ? (both && p2 < kOutside ? p2 - 16u : kOutside)
+                                   : p2 + 2u * (uint32_t)(c0 - a.c1),
                      0, k, sa + 256 * k);
         else
-          load_pixel(false, up8 ? kOutside : p1, 2 * c0, k, sa + 256 * k);
+          load_pixel(b1, false, up8 ? kOutside : p1, 2 * c0, k, sa + 256 * k);
       }
     }
     if constexpr (!THIN) {
@@ -645,11 +647,9 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3_wgrad(WgradArgs a) {
     const int ty = tile / a.tiles_x, x0 = (tile - ty * a.tiles_x) * kWgCols, y0 = ty * kWgRows;
     const int64_t q2 = (int64_t)(y0 - 1) * W + x0 - 1;
     const int64_t q1 = a.up ? (int64_t)((y0 >> 1) - 1) * W1 + (x0 >> 1) - 1 : q2;
-    const uint16_t *const f1 = a.x1 + q1 * a.c1, *const f2 = a.x2 + q2 * a.c2;
-    const uint16_t *const fg = a.gy + ((int64_t)y0 * W + x0) * a.cout;
-    const auto b1 = buffer_of(f1, kBufferBytes);
-    const auto b2 = buffer_of(f2, kBufferBytes);
-    const auto bg = buffer_of(fg, kBufferBytes);
+    const auto b1 = buffer_of(a.x1 + q1 * a.c1, kBufferBytes);
+    const auto b2 = buffer_of(a.x2 + q2 * a.c2, kBufferBytes);
+    const auto bg = buffer_of(a.gy + ((int64_t)y0 * W + x0) * a.cout, kBufferBytes);
     uint32_t out_i = 0, out_g = 0;  // slots whose pixel lies outside the image
     if (y0 == 0 || x0 == 0 || y0 + kWgRows + 1 > H || x0 + kWgCols + 1 > W) {
 #pragma unroll
@@ -674,11 +674,13 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3_wgrad(WgradArgs a) {
       if constexpr (FAR) {
         const int row = (tid + 256 * k) / 4 / SC, r0 = (64 * wave + 256 * k) / 4 / SC;
         if ((from2 >> k) & 1)
-          load_two_rows(row, r0, [&](int r) { return f2 + (int64_t)r * W * a.c2; }, o, 0,
-                        li + 256 * k);
+          load_two_rows(
+              row, r0, [&](int r) { return a.x2 + (q2 + (int64_t)r * W) * a.c2; }, o, 0,
+              li + 256 * k);
         else
           load_two_rows(
-              row, r0, [&](int r) { return f1 + (int64_t)(a.up ? (r + 1) >> 1 : r) * W1 * a.c1; },
+              row, r0,
+              [&](int r) { return a.x1 + (q1 + (int64_t)(a.up ? (r + 1) >> 1 : r) * W1) * a.c1; },
               o, 0, li + 256 * k);
       } else {
         if ((from2 >> k) & 1) load_to_lds(b2, o, 0, li + 256 * k);
@@ -690,7 +692,8 @@ __global__ __launch_bounds__(256, 2) void k_conv3x3_wgrad(WgradArgs a) {
       const uint32_t o = og[k] | ((out_g << (31 - k)) & kOutside);
       if constexpr (FAR) {
         const int r = (64 * wave + 256 * k) / 4 / kWgCols;
-        load_to_lds(buffer_of(fg + (int64_t)r * W * a.cout, kBufferBytes), o, 0, lg + 256 * k);
+        load_to_lds(buffer_of(a.gy + ((int64_t)(y0 + r) * W + x0) * a.cout, kBufferBytes), o, 0,
+                    lg + 256 * k);
       } else {
         load_to_lds(bg, o, 0, lg + 256 * k);
       }

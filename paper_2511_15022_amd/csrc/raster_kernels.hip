@@ -1334,10 +1334,10 @@ hipError_t launch_raster_fwd(const Ctx &c, float2 *field, hipStream_t s) {
 // one, and a step's values are read from LDS while the step before it is summed.
 // What bounds it: VALU issue and, from three channels on, the LDS reads (8 C bytes
 // per pixel and lane, at addresses that spread over the banks like random ones).
-// Three waves per tile where there are many: two leave too few waves (152 us), four cut
-// a tile's list into batches too short (139 us).  Measured before (one pixel per step) and now: 1080p
-// RGB, 415k Gaussians, 137 -> 133 us; 512 x 512 gray, 52k Gaussians x 8 holograms,
-// 84 -> 74 us.
+// Three waves per tile where there are many: two leave too few waves (152 us at 1080p
+// RGB), more cut a tile's list into batches too short (kAdjWaves).  One pixel per step and
+// two: 1080p RGB, 415k Gaussians, 136.6 -> 135.6 us; 512 x 512 gray, 52k Gaussians x 8
+// holograms, 84 -> 74 us.
 // ----------------------------------------------------------------------------
 constexpr int kAdjBatch = 64;
 constexpr int kAdjSeg = 8;    // pixels per segment
